@@ -232,7 +232,7 @@ template <int L, bool INT8, int U>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sweep_min_waves<L>(), 8))) void b_sweep(const Item* __restrict__ items, const RunDev* __restrict__ runs,
                                                const StepDev* __restrict__ steps, const ResultDev* __restrict__ res)
 {
-    extern __shared__ uint32_t lds_dyn[];
+    extern __shared__ __align__(16) uint32_t lds_dyn[];
     const Item it = items[blockIdx.x];
     const StepDev st = steps[it.run];
     if (!st.active) return;

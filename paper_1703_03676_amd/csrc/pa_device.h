@@ -49,9 +49,7 @@ __device__ __forceinline__ U4 philox10(uint32_t c0, uint32_t c1, uint32_t c2, ui
 // the wave (only c0 differs).  In the first three rounds some products and
 // xors then involve wave-uniform values only; written as plain xors with the
 // uniform operands combined first, those parts compile to scalar
-// instructions.  The arithmetic is that of philox10.  (The LDS path gains from
-// it; the register path, with its uniform branch per bit plane, measured
-// slower with it and keeps philox10.)
+// instructions.  The arithmetic is that of philox10.
 __device__ __forceinline__ U4 philox10u(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                         uint32_t k1)
 {
@@ -132,7 +130,39 @@ __device__ __forceinline__ PhiloxHalf philox_half(uint32_t c1, uint32_t c2, uint
     return h;
 }
 
-__device__ __forceinline__ U4 philox10_h(uint32_t c0, uint32_t c3, const PhiloxHalf& h, uint32_t k0, uint32_t k1)
+// The keys of rounds 4 to 10 of the sweep's Philox blocks, each in a vector
+// register of its own.  gfx950 issues instructions of two waves of a SIMD
+// together only where their operands are all in vector registers (measured:
+// a three-way xor takes 2.4 cycles that way and 4.2 with one scalar operand; a
+// chain of Philox rounds 3.9 cycles per instruction at five waves per SIMD
+// against 5.0 with the keys in scalar registers, the multiplier staying
+// there).  The values go through an opaque move so that the compiler leaves
+// them in vector registers.  Sweeps of 20000 replicas: L = 64 1.11 -> 0.98 ms
+// (theta = 100), L = 32 0.085 -> 0.080 ms (theta = 20).
+struct PhiloxKeys {
+    uint32_t k0[7], k1[7];
+};
+
+__device__ __forceinline__ uint32_t in_vgpr(uint32_t x)
+{
+    uint32_t v;
+    __asm__("v_mov_b32 %0, %1" : "=v"(v) : "s"(x));
+    return v;
+}
+
+__device__ __forceinline__ PhiloxKeys philox_keys(uint32_t key0, uint32_t key1)
+{
+    PhiloxKeys k;
+#pragma unroll
+    for (uint32_t r = 0; r < 7u; ++r) {
+        k.k0[r] = in_vgpr(key0 + (r + 3u) * kW0);
+        k.k1[r] = in_vgpr(key1 + (r + 3u) * kW1);
+    }
+    return k;
+}
+
+__device__ __forceinline__ U4 philox10_h(uint32_t c0, uint32_t c3, const PhiloxHalf& h, uint32_t k0, uint32_t k1,
+                                         const PhiloxKeys& K)
 {
     // round 1 (word 0 and word 1 of its output are h.a0, h.a1)
     const uint64_t P0 = (uint64_t)kM0 * c0;
@@ -152,47 +182,36 @@ __device__ __forceinline__ U4 philox10_h(uint32_t c0, uint32_t c3, const PhiloxH
     {
         const uint64_t p0 = (uint64_t)kM0 * x0;
         const uint64_t p1 = (uint64_t)kM1 * x2;
-        const uint32_t n0 = xor3((uint32_t)(p1 >> 32), x1, k0);
+        const uint32_t n0 = (uint32_t)(p1 >> 32) ^ (x1 ^ k0);
         const uint32_t n2 = (uint32_t)(p0 >> 32) ^ (x3 ^ k1);
         x1 = (uint32_t)p1;
         x3 = (uint32_t)p0;
         x0 = n0;
         x2 = n2;
-        k0 += kW0;
-        k1 += kW1;
     }
 #pragma unroll
-    for (int r = 3; r < 10; ++r) {
+    for (int r = 0; r < 7; ++r) {
         const uint64_t p0 = (uint64_t)kM0 * x0;
         const uint64_t p1 = (uint64_t)kM1 * x2;
-        const uint32_t n0 = xor3((uint32_t)(p1 >> 32), x1, k0);
-        const uint32_t n2 = xor3((uint32_t)(p0 >> 32), x3, k1);
+        const uint32_t n0 = xor3((uint32_t)(p1 >> 32), x1, K.k0[r]);
+        const uint32_t n2 = xor3((uint32_t)(p0 >> 32), x3, K.k1[r]);
         x1 = (uint32_t)p1;
         x3 = (uint32_t)p0;
         x0 = n0;
         x2 = n2;
-        k0 += kW0;
-        k1 += kW1;
     }
     return {x0, x1, x2, x3};
 }
 
 // Philox blocks of one half sweep on the register path, counter (c0, 2g + c, j,
-// c3): with one replica per wave (Half) the per-half-sweep values of
-// philox_half are shared by every block, with several (replicas differ
-// between lanes) each block is plain philox10, which measured a few
-// instructions cheaper there.
+// c3): the per-half-sweep values of philox_half are shared by every block.
 struct HalfBlocks {
     PhiloxHalf h;
     uint32_t k0, k1;
-    __device__ __forceinline__ U4 operator()(uint32_t c0, uint32_t c3) const { return philox10_h(c0, c3, h, k0, k1); }
-};
-
-struct PlainBlocks {
-    uint32_t c1, c2, k0, k1;
+    const PhiloxKeys& K;
     __device__ __forceinline__ U4 operator()(uint32_t c0, uint32_t c3) const
     {
-        return philox10(c0, c1, c2, c3, k0, k1);
+        return philox10_h(c0, c3, h, k0, k1, K);
     }
 };
 
@@ -210,6 +229,10 @@ constexpr uint32_t kStreamInit = 2;
 constexpr uint32_t kStreamSweepLow = 3;
 constexpr uint32_t kStreamLcgSeed = 4;
 
+// Entries of a wave's tie queue on the LDS path (four words each, queue_ties).
+constexpr int kTieQueue = 128;
+constexpr int kTieQueueWords = 4 * kTieQueue;
+
 template <int L>
 struct Geo {
     static constexpr int N = L * L;
@@ -225,12 +248,10 @@ struct Geo {
     static constexpr size_t BITS_BYTES = N / 8;       // bytes per replica, bit store
     static constexpr int RPWV = (K == 1) ? REPW : 1;  // replicas per wave
     // LDS path: a lane decides up to 8 of its K words before the words with
-    // sites still tied are resolved through the wave's tie queue (QCAP entries
-    // of four words each).
+    // sites still tied are resolved through the wave's tie queue.
     static constexpr int SLOTS = (K == 1) ? 1 : (K < 8 ? K : 8);
-    static constexpr int QCAP = 128;
     // LDS words of one wave on the LDS path: replica [2][NW], then the queue
-    static constexpr int WAVE_LDS_WORDS = (K == 1) ? 0 : 2 * NW + 4 * QCAP;
+    static constexpr int WAVE_LDS_WORDS = (K == 1) ? 0 : 2 * NW + kTieQueueWords;
     static constexpr int lds_words(int wpb) { return wpb * WAVE_LDS_WORDS; }
     static_assert(L % 16 == 0 && L >= 16 && L <= 256, "lattice size");
     static_assert(K >= 1 && NW % G == 0, "lane mapping");
@@ -327,34 +348,77 @@ struct Neighbours {
 };
 
 // One bit plane of the bit-serial comparison "uniform < threshold", high bit
-// first, for the sites still tied.  k = 2 sites (cls1) compare against T_2,
-// k = 4 sites against T_4; `tb` holds the two threshold bits of this plane
-// (bit 1: T_2, bit 0: T_4) and is uniform, so each case is straight-line code.
-//   threshold bit 1: plane bit 0 -> below (accept), plane bit 1 -> still tied
-//   threshold bit 0: plane bit 1 -> above (reject), plane bit 0 -> still tied
-__device__ __forceinline__ void compare_plane(uint32_t x, uint32_t tb, uint32_t cls1, uint32_t& eq, uint32_t& acc)
+// first, for NG words together.  k = 2 sites (cls1) compare against T_2, k = 4
+// sites against T_4.  acc holds the sites accepted so far and open those not
+// rejected so far, so acc is a subset of open and open & ~acc are the sites
+// still tied.  A threshold bit 1 accepts the tied sites whose plane bit is 0, a
+// threshold bit 0 rejects those whose plane bit is 1; with
+//   m = acc | (open & ~x)
+// a plane therefore replaces acc (bit 1) or open (bit 0) by m: one operation
+// per word where both classes have the same threshold bit and three where they
+// differ (select by class into both masks).  tb holds the two threshold bits of
+// the plane (bit 1: T_2, bit 0: T_4) and is uniform.  Its four cases are one
+// block of assembly, arithmetic and branches only: written as a switch, the
+// compiler joins the cases with five register moves per plane of four words
+// (L = 128, R = 50000: 144 -> 131 vector instructions per word and half sweep,
+// 1.68 -> 1.63 ms per launch of 20 sweeps).
+#define PA_PLANE_M(i, t) "v_bitop3_b32 %[" t "], %[a" i "], %[o" i "], %[x" i "] bitop3:0xf4\n\t"
+#define PA_PLANE_SEL(d, i, p, q) "v_bitop3_b32 %[" d i "], %[c" i "], %[" p "], %[" q "] bitop3:0xca\n\t"
+#define PA_PLANE_0(i) PA_PLANE_M(i, "o" i)
+#define PA_PLANE_3(i) PA_PLANE_M(i, "a" i)
+#define PA_PLANE_2(i, t) PA_PLANE_M(i, t) PA_PLANE_SEL("a", i, t, "a" i) PA_PLANE_SEL("o", i, "o" i, t)
+#define PA_PLANE_1(i, t) PA_PLANE_M(i, t) PA_PLANE_SEL("a", i, "a" i, t) PA_PLANE_SEL("o", i, t, "o" i)
+#define PA_PLANE_ASM(C0, C1, C2, C3)                                                                              \
+    "s_cmp_lt_u32 %[tb], 2\n\t"                                                                                   \
+    "s_cbranch_scc1 .Lpa_plane_low%=\n\t"                                                                         \
+    "s_cmp_eq_u32 %[tb], 3\n\t"                                                                                   \
+    "s_cbranch_scc1 .Lpa_plane_3%=\n\t" C2                                                                        \
+    "s_branch .Lpa_plane_end%=\n"                                                                                 \
+    ".Lpa_plane_low%=:\n\t"                                                                                       \
+    "s_cmp_eq_u32 %[tb], 0\n\t"                                                                                   \
+    "s_cbranch_scc1 .Lpa_plane_0%=\n\t" C1                                                                        \
+    "s_branch .Lpa_plane_end%=\n"                                                                                 \
+    ".Lpa_plane_3%=:\n\t" C3                                                                                      \
+    "s_branch .Lpa_plane_end%=\n"                                                                                 \
+    ".Lpa_plane_0%=:\n\t" C0                                                                                      \
+    ".Lpa_plane_end%=:\n\t"
+
+template <int NG>
+__device__ __forceinline__ void open_plane(const uint32_t (&x)[NG], uint32_t tb, const uint32_t (&cls1)[NG],
+                                           uint32_t (&acc)[NG], uint32_t (&open)[NG])
 {
-    // Every case writes its results with its own three-input operation, so the
-    // compiler cannot pull a shared AND/OR out of the branches (which costs
-    // extra moves on the merge paths).  Truth tables over (a, b, c) with
-    // a = 0xF0, b = 0xCC, c = 0xAA.
-    switch (tb) {
-    case 0:
-        eq = __builtin_amdgcn_bitop3_b32(eq, x, x, 0x30);  // eq & ~x
-        break;
-    case 3:
-        acc = __builtin_amdgcn_bitop3_b32(acc, eq, x, 0xF4);  // acc | (eq & ~x)
-        eq = __builtin_amdgcn_bitop3_b32(eq, x, x, 0xC0);     // eq & x
-        break;
-    case 2:  // T_2 bit set, T_4 bit clear
-        acc |= __builtin_amdgcn_bitop3_b32(eq, cls1, x, 0x40);  // eq & cls1 & ~x
-        eq = __builtin_amdgcn_bitop3_b32(eq, x, cls1, 0x90);    // eq & ~(x ^ cls1)
-        break;
-    default:  // T_4 bit set, T_2 bit clear
-        acc |= __builtin_amdgcn_bitop3_b32(eq, cls1, x, 0x10);  // eq & ~cls1 & ~x
-        eq = __builtin_amdgcn_bitop3_b32(eq, x, cls1, 0x60);    // eq & (x ^ cls1)
-        break;
+    static_assert(NG == 1 || NG == 2 || NG == 4, "words of a group");
+    uint32_t t0;
+    if constexpr (NG == 1) {
+        __asm__(PA_PLANE_ASM(PA_PLANE_0("0"), PA_PLANE_1("0", "t0"), PA_PLANE_2("0", "t0"), PA_PLANE_3("0"))
+                : [a0] "+v"(acc[0]), [o0] "+v"(open[0]), [t0] "=&v"(t0)
+                : [x0] "v"(x[0]), [c0] "v"(cls1[0]), [tb] "s"(tb)
+                : "scc");
+    } else if constexpr (NG == 2) {
+        __asm__(PA_PLANE_ASM(PA_PLANE_0("0") PA_PLANE_0("1"), PA_PLANE_1("0", "t0") PA_PLANE_1("1", "t0"),
+                             PA_PLANE_2("0", "t0") PA_PLANE_2("1", "t0"), PA_PLANE_3("0") PA_PLANE_3("1"))
+                : [a0] "+v"(acc[0]), [o0] "+v"(open[0]), [a1] "+v"(acc[1]), [o1] "+v"(open[1]), [t0] "=&v"(t0)
+                : [x0] "v"(x[0]), [c0] "v"(cls1[0]), [x1] "v"(x[1]), [c1] "v"(cls1[1]), [tb] "s"(tb)
+                : "scc");
+    } else {
+        __asm__(PA_PLANE_ASM(PA_PLANE_0("0") PA_PLANE_0("1") PA_PLANE_0("2") PA_PLANE_0("3"),
+                             PA_PLANE_1("0", "t0") PA_PLANE_1("1", "t0") PA_PLANE_1("2", "t0") PA_PLANE_1("3", "t0"),
+                             PA_PLANE_2("0", "t0") PA_PLANE_2("1", "t0") PA_PLANE_2("2", "t0") PA_PLANE_2("3", "t0"),
+                             PA_PLANE_3("0") PA_PLANE_3("1") PA_PLANE_3("2") PA_PLANE_3("3"))
+                : [a0] "+v"(acc[0]), [o0] "+v"(open[0]), [a1] "+v"(acc[1]), [o1] "+v"(open[1]), [a2] "+v"(acc[2]),
+                  [o2] "+v"(open[2]), [a3] "+v"(acc[3]), [o3] "+v"(open[3]), [t0] "=&v"(t0)
+                : [x0] "v"(x[0]), [c0] "v"(cls1[0]), [x1] "v"(x[1]), [c1] "v"(cls1[1]), [x2] "v"(x[2]),
+                  [c2] "v"(cls1[2]), [x3] "v"(x[3]), [c3] "v"(cls1[3]), [tb] "s"(tb)
+                : "scc");
     }
+}
+
+// The threshold bits of plane q (0: the highest of the 16 high bits) as
+// open_plane takes them.
+__device__ __forceinline__ uint32_t plane_bits(const SweepArgs& a, int q)
+{
+    const int bit = 15 - q;
+    return (((a.t2h >> bit) & 1u) << 1) | ((a.t4h >> bit) & 1u);
 }
 
 // Metropolis acceptance mask of one 32-site word.  A site flips if at least two
@@ -369,60 +433,42 @@ __device__ __forceinline__ uint32_t accept_mask(uint32_t w, const Nb& n, uint32_
     const uint32_t o12 = d1 | d2, a12 = d1 & d2, o34 = d3 | d4, a34 = d3 & d4;
     const uint32_t ge2 = a12 | a34 | (o12 & o34);
     const uint32_t any = o12 | o34;
-    const uint32_t cls1 = any & ~ge2;  // k = 2
-    uint32_t eq = ~ge2;                // sites still tied with their threshold
-    uint32_t acc = ge2;
-    if (__builtin_expect((a.t2h | a.t4h) > 0xFFFFu, 0)) {  // a threshold is 2^32 (beta ~ 0)
-        if (a.t2h > 0xFFFFu) {  // T_2 = 2^32: always accepted
-            acc |= cls1;
-            eq &= ~cls1;
-        }
-        if (a.t4h > 0xFFFFu) {
-            acc |= ~any;
-            eq &= any;
-        }
+    const uint32_t cls1[1] = {any & ~ge2};  // k = 2
+    uint32_t acc[1] = {ge2}, open[1] = {0xFFFFFFFFu};  // open & ~acc: sites still tied with their threshold
+    if (__builtin_expect((a.t2h | a.t4h) > 0xFFFFu, 0)) {  // a threshold is 2^32 (beta ~ 0): always accepted
+        if (a.t2h > 0xFFFFu) acc[0] |= cls1[0];
+        if (a.t4h > 0xFFFFu) acc[0] |= ~any;
     }
-    if (__any(eq != 0u)) {
+    if (__any(open[0] != acc[0])) {
         // blocks 0, 1 and 2 are computed together (three independent chains),
         // since the first eight planes leave some site of the wave tied almost
         // surely (the wave holds about 2000 sites that need a uniform)
         const U4 P0 = blk(4u * v, a.tag | kStreamSweepHigh);
         const U4 P1 = blk(4u * v + 1u, a.tag | kStreamSweepHigh);
         const U4 P2 = blk(4u * v + 2u, a.tag | kStreamSweepHigh);
-        const uint32_t pl[12] = {P0.x, P0.y, P0.z, P0.w, P1.x, P1.y, P1.z, P1.w, P2.x, P2.y, P2.z, P2.w};
+        const uint32_t pl[12][1] = {{P0.x}, {P0.y}, {P0.z}, {P0.w}, {P1.x}, {P1.y},
+                                    {P1.z}, {P1.w}, {P2.x}, {P2.y}, {P2.z}, {P2.w}};
 #pragma unroll
-        for (int q = 0; q < 12; ++q) {
-            const int bit = 15 - q;
-            const uint32_t tb = (((a.t2h >> bit) & 1u) << 1) | ((a.t4h >> bit) & 1u);
-            compare_plane(pl[q], tb, cls1, eq, acc);
-        }
+        for (int q = 0; q < 12; ++q) open_plane<1>(pl[q], plane_bits(a, q), cls1, acc, open);
+        if (__any(open[0] != acc[0])) {
+            const U4 P = blk(4u * v + 3u, a.tag | kStreamSweepHigh);
+            const uint32_t pq[4][1] = {{P.x}, {P.y}, {P.z}, {P.w}};
 #pragma unroll
-        for (int kk = 3; kk < 4; ++kk) {
-            if (!__any(eq != 0u)) break;
-            const U4 P = blk(4u * v + (uint32_t)kk, a.tag | kStreamSweepHigh);
-            const uint32_t pq[4] = {P.x, P.y, P.z, P.w};
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int bit = 15 - (4 * kk + q);
-                const uint32_t tb = (((a.t2h >> bit) & 1u) << 1) | ((a.t4h >> bit) & 1u);
-                compare_plane(pq[q], tb, cls1, eq, acc);
-            }
+            for (int q = 0; q < 4; ++q) open_plane<1>(pq[q], plane_bits(a, 12 + q), cls1, acc, open);
         }
     }
-    if (__any(eq != 0u)) {
-        uint32_t tie = eq;
-        while (tie) {
-            const int b = __builtin_ctz(tie);
-            tie &= tie - 1u;
-            const uint32_t q = 32u * v + (uint32_t)b;
-            const U4 P = blk(q >> 3, a.tag | kStreamSweepLow);
-            const uint32_t word = pick(P, (q >> 1) & 3u);
-            const uint32_t lo = (q & 1u) ? (word & 0xFFFFu) : (word >> 16);
-            const uint32_t tl = ((cls1 >> b) & 1u) ? a.t2l : a.t4l;
-            if (lo < tl) acc |= 1u << b;
-        }
+    uint32_t tie = open[0] & ~acc[0];
+    while (tie) {
+        const int b = __builtin_ctz(tie);
+        tie &= tie - 1u;
+        const uint32_t q = 32u * v + (uint32_t)b;
+        const U4 P = blk(q >> 3, a.tag | kStreamSweepLow);
+        const uint32_t word = pick(P, (q >> 1) & 3u);
+        const uint32_t lo = (q & 1u) ? (word & 0xFFFFu) : (word >> 16);
+        const uint32_t tl = ((cls1[0] >> b) & 1u) ? a.t2l : a.t4l;
+        if (lo < tl) acc[0] |= 1u << b;
     }
-    return acc;
+    return acc[0];
 }
 
 // Neighbour classes of the heat-bath update.  With a the number of
@@ -460,46 +506,41 @@ __device__ __forceinline__ uint32_t heatbath_mask(uint32_t w, const Nb& n, uint3
                                                   const SweepArgs& a)
 {
     const HbClass c = hb_classes(w, n);
-    uint32_t eq = ~c.zero;
+    const uint32_t cls1[1] = {c.cls1};
     // blocks 0, 1 and 2 together (three independent chains), as in accept_mask
     const U4 P0 = blk(4u * v, a.tag | kStreamSweepHigh);
     const U4 P1 = blk(4u * v + 1u, a.tag | kStreamSweepHigh);
     const U4 P2 = blk(4u * v + 2u, a.tag | kStreamSweepHigh);
     const uint32_t pl[12] = {P0.x, P0.y, P0.z, P0.w, P1.x, P1.y, P1.z, P1.w, P2.x, P2.y, P2.z, P2.w};
-    uint32_t acc = c.zero & ~pl[0];  // U_0 = 2^31: x < U_0 iff its top bit is 0
+    uint32_t acc[1] = {c.zero & ~pl[0]};  // U_0 = 2^31: x < U_0 iff its top bit is 0
+    uint32_t open[1] = {acc[0] | ~c.zero};
 #pragma unroll
     for (int q = 0; q < 12; ++q) {
-        const int bit = 15 - q;
-        const uint32_t tb = (((a.t2h >> bit) & 1u) << 1) | ((a.t4h >> bit) & 1u);
-        compare_plane(pl[q] ^ c.neg, tb, c.cls1, eq, acc);
+        const uint32_t x[1] = {pl[q] ^ c.neg};
+        open_plane<1>(x, plane_bits(a, q), cls1, acc, open);
     }
-#pragma unroll
-    for (int kk = 3; kk < 4; ++kk) {
-        if (!__any(eq != 0u)) break;
-        const U4 P = blk(4u * v + (uint32_t)kk, a.tag | kStreamSweepHigh);
+    if (__any(open[0] != acc[0])) {
+        const U4 P = blk(4u * v + 3u, a.tag | kStreamSweepHigh);
         const uint32_t pq[4] = {P.x, P.y, P.z, P.w};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int bit = 15 - (4 * kk + q);
-            const uint32_t tb = (((a.t2h >> bit) & 1u) << 1) | ((a.t4h >> bit) & 1u);
-            compare_plane(pq[q] ^ c.neg, tb, c.cls1, eq, acc);
+            const uint32_t x[1] = {pq[q] ^ c.neg};
+            open_plane<1>(x, plane_bits(a, 12 + q), cls1, acc, open);
         }
     }
-    if (__any(eq != 0u)) {
-        uint32_t tie = eq;
-        while (tie) {
-            const int b = __builtin_ctz(tie);
-            tie &= tie - 1u;
-            const uint32_t q = 32u * v + (uint32_t)b;
-            const U4 P = blk(q >> 3, a.tag | kStreamSweepLow);
-            const uint32_t word = pick(P, (q >> 1) & 3u);
-            uint32_t lo = (q & 1u) ? (word & 0xFFFFu) : (word >> 16);
-            if ((c.neg >> b) & 1u) lo ^= 0xFFFFu;
-            const uint32_t tl = ((c.cls1 >> b) & 1u) ? a.t2l : a.t4l;
-            if (lo < tl) acc |= 1u << b;
-        }
+    uint32_t tie = open[0] & ~acc[0];
+    while (tie) {
+        const int b = __builtin_ctz(tie);
+        tie &= tie - 1u;
+        const uint32_t q = 32u * v + (uint32_t)b;
+        const U4 P = blk(q >> 3, a.tag | kStreamSweepLow);
+        const uint32_t word = pick(P, (q >> 1) & 3u);
+        uint32_t lo = (q & 1u) ? (word & 0xFFFFu) : (word >> 16);
+        if ((c.neg >> b) & 1u) lo ^= 0xFFFFu;
+        const uint32_t tl = ((c.cls1 >> b) & 1u) ? a.t2l : a.t4l;
+        if (lo < tl) acc[0] |= 1u << b;
     }
-    return acc ^ c.neg;
+    return acc[0] ^ c.neg;
 }
 
 // In-line LCG variant of the multi-spin-coded sweep (Sec. 4): the generator
@@ -571,17 +612,12 @@ __device__ __forceinline__ void half_sweep_lcg(uint32_t (&own)[1], const uint32_
 
 template <int L, int C, bool HB>
 __device__ __forceinline__ void half_sweep(uint32_t (&own)[Geo<L>::K], const uint32_t (&oth)[Geo<L>::K], int lane,
-                                           int gl, uint32_t g, uint32_t j, const SweepArgs& a)
+                                           int gl, uint32_t g, uint32_t j, const SweepArgs& a, const PhiloxKeys& K)
 {
     using Gm = Geo<L>;
     const Neighbours<L, C> nb(oth, lane, gl);
     const uint32_t ctr1 = 2u * g + (uint32_t)C;
-    const auto blocks = [&]() {
-        if constexpr (Gm::REPW == 1)
-            return HalfBlocks{philox_half(ctr1, j, a.key0), a.key0, a.key1};
-        else
-            return PlainBlocks{ctr1, j, a.key0, a.key1};
-    }();
+    const HalfBlocks blocks{philox_half(ctr1, j, a.key0), a.key0, a.key1, K};
 #pragma unroll
     for (int k = 0; k < Gm::K; ++k) {
         const uint32_t v = (uint32_t)(gl * Gm::K + k);
@@ -598,19 +634,19 @@ __device__ __forceinline__ void half_sweep(uint32_t (&own)[Geo<L>::K], const uin
 // anti-aligned (k = s h <= 0); a site with one anti-aligned neighbour (k = 2,
 // `cls1`) or none (k = 4) flips if its uniform x is below T_2 or T_4.  The
 // planes are compared high bit first with one uniform branch per plane over the
-// two threshold bits, shared by the NG words: 2-3 operations per word and
-// plane.  The words are updated with their decided flips; `tie` receives the
-// sites whose 8 high bits equal the threshold's (probability 2^-8 each),
-// decided later by decide_word_tail.  With HB (heat-bath, the update of
-// heatbath_mask) every site draws, the k = 0 sites are decided by plane 0, the
-// k < 0 sites compare the complemented planes (`ng`) and are flipped
-// provisionally, so that the tail's result xored on top gives their decision.
-template <int NG, bool HB>
-__device__ __forceinline__ void decide8_group(uint32_t (&w)[NG], const Nb (&n)[NG], const uint32_t (&v)[NG],
-                                              uint32_t ctr1, uint32_t j, const SweepArgs& a, uint32_t (&tie)[NG],
-                                              uint32_t (&cls1)[NG], uint32_t (&ng)[NG])
+// two threshold bits, shared by the NG words.  The words are updated with
+// their decided flips; `tie` receives the sites whose 8 high bits equal the
+// threshold's (probability 2^-8 each), decided later by decide_word_tail.  With
+// HB (heat-bath, the update of heatbath_mask) every site draws, the k = 0 sites
+// are decided by plane 0, the k < 0 sites compare the complemented planes
+// (`ng`) and are flipped provisionally, so that the tail's result xored on top
+// gives their decision.  blk(g, kk) is Philox block kk of word g.
+template <int NG, bool HB, class BLK>
+__device__ __forceinline__ void decide8_group(uint32_t (&w)[NG], const Nb (&n)[NG], const BLK& blk,
+                                              const SweepArgs& a, uint32_t (&tie)[NG], uint32_t (&cls1)[NG],
+                                              uint32_t (&ng)[NG])
 {
-    uint32_t eq[NG], acc[NG], zero[NG];
+    uint32_t acc[NG], open[NG], zero[NG];  // zero: heat-bath k = 0 sites; Metropolis: any anti-aligned neighbour
     uint32_t need = 0u;
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
@@ -619,77 +655,52 @@ __device__ __forceinline__ void decide8_group(uint32_t (&w)[NG], const Nb (&n)[N
             cls1[g] = c.cls1;
             ng[g] = c.neg;
             zero[g] = c.zero;
-            eq[g] = ~c.zero;
-            acc[g] = 0u;
         } else {
             const uint32_t d1 = w[g] ^ n[g].up, d2 = w[g] ^ n[g].dn, d3 = w[g] ^ n[g].same, d4 = w[g] ^ n[g].side;
             const uint32_t o12 = d1 | d2, a12 = d1 & d2, o34 = d3 | d4, a34 = d3 & d4;
             const uint32_t ge2 = a12 | a34 | (o12 & o34);
             const uint32_t any = o12 | o34;
             cls1[g] = any & ~ge2;
-            const uint32_t cls2 = ~any;
-            const uint32_t all2 = (a.t2h > 0xFFFFu) ? cls1[g] : 0u;  // T = 2^32: always accepted
-            const uint32_t all4 = (a.t4h > 0xFFFFu) ? cls2 : 0u;
-            eq[g] = (cls1[g] & ~all2) | (cls2 & ~all4);
-            acc[g] = ge2 | all2 | all4;
             ng[g] = 0u;
-            zero[g] = 0u;
+            zero[g] = any;
+            acc[g] = ge2;
+            open[g] = 0xFFFFFFFFu;
         }
-        need |= eq[g];
+    }
+    if constexpr (!HB) {
+        if (__builtin_expect((a.t2h | a.t4h) > 0xFFFFu, 0)) {  // a threshold is 2^32 (beta ~ 0): always accepted
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                if (a.t2h > 0xFFFFu) acc[g] |= cls1[g];
+                if (a.t4h > 0xFFFFu) acc[g] |= ~zero[g];
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < NG; ++g) need |= ~acc[g];
     }
     // heat-bath draws for every site: its k = 0 sites are decided by plane 0
     // even when no site of the wave is left for the later planes
     if (HB || __any(need != 0u)) {
-        uint32_t pl[NG][8];
+        uint32_t pl[8][NG];
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
-            const U4 P0 = philox10u(4u * v[g], ctr1, j, a.tag | kStreamSweepHigh, a.key0, a.key1);
-            const U4 P1 = philox10u(4u * v[g] + 1u, ctr1, j, a.tag | kStreamSweepHigh, a.key0, a.key1);
-            pl[g][0] = P0.x, pl[g][1] = P0.y, pl[g][2] = P0.z, pl[g][3] = P0.w;
-            pl[g][4] = P1.x, pl[g][5] = P1.y, pl[g][6] = P1.z, pl[g][7] = P1.w;
+            const U4 P0 = blk(g, 0u), P1 = blk(g, 1u);
+            pl[0][g] = P0.x, pl[1][g] = P0.y, pl[2][g] = P0.z, pl[3][g] = P0.w;
+            pl[4][g] = P1.x, pl[5][g] = P1.y, pl[6][g] = P1.z, pl[7][g] = P1.w;
             if constexpr (HB) {
-                acc[g] = zero[g] & ~pl[g][0];  // U_0 = 2^31: x < U_0 iff its top bit is 0
+                acc[g] = zero[g] & ~pl[0][g];  // U_0 = 2^31: x < U_0 iff its top bit is 0
+                open[g] = acc[g] | ~zero[g];
 #pragma unroll
-                for (int q = 0; q < 8; ++q) pl[g][q] ^= ng[g];
+                for (int q = 0; q < 8; ++q) pl[q][g] ^= ng[g];
             }
         }
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int bit = 15 - q;
-            const uint32_t tb = (((a.t2h >> bit) & 1u) << 1) | ((a.t4h >> bit) & 1u);
-            switch (tb) {
-            case 0:
-#pragma unroll
-                for (int g = 0; g < NG; ++g) eq[g] = __builtin_amdgcn_bitop3_b32(eq[g], pl[g][q], pl[g][q], 0x30);
-                break;
-            case 3:
-#pragma unroll
-                for (int g = 0; g < NG; ++g) {
-                    acc[g] = __builtin_amdgcn_bitop3_b32(acc[g], eq[g], pl[g][q], 0xF4);
-                    eq[g] = __builtin_amdgcn_bitop3_b32(eq[g], pl[g][q], pl[g][q], 0xC0);
-                }
-                break;
-            case 2:
-#pragma unroll
-                for (int g = 0; g < NG; ++g) {
-                    acc[g] |= __builtin_amdgcn_bitop3_b32(eq[g], cls1[g], pl[g][q], 0x40);
-                    eq[g] = __builtin_amdgcn_bitop3_b32(eq[g], pl[g][q], cls1[g], 0x90);
-                }
-                break;
-            default:
-#pragma unroll
-                for (int g = 0; g < NG; ++g) {
-                    acc[g] |= __builtin_amdgcn_bitop3_b32(eq[g], cls1[g], pl[g][q], 0x10);
-                    eq[g] = __builtin_amdgcn_bitop3_b32(eq[g], pl[g][q], cls1[g], 0x60);
-                }
-                break;
-            }
-        }
+        for (int q = 0; q < 8; ++q) open_plane<NG>(pl[q], plane_bits(a, q), cls1, acc, open);
     }
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
-        w[g] ^= acc[g] ^ ng[g];
-        tie[g] = eq[g];
+        w[g] ^= HB ? acc[g] ^ ng[g] : acc[g];
+        tie[g] = open[g] & ~acc[g];
     }
 }
 
@@ -704,110 +715,113 @@ __device__ __forceinline__ void wave_lds_sync()
 
 // Remaining comparison of the tied sites `mask` of word v (all tied after 8
 // planes): Philox block 2 (planes 8-11) once for the word, block 3 (planes
-// 12-15) once if a site is still tied, then the SWEEP-LOW half of each site
-// still tied.  k2m marks the sites of class k = 2, ngm those that compare the
-// complement of their uniform (heat-bath, k < 0).  Returns the sites whose
-// (complemented) uniform is below their threshold, each decided exactly as a
-// comparison of its whole 32-bit uniform would decide it.
-__device__ __forceinline__ uint32_t decide_word_tail(uint32_t v, uint32_t mask, uint32_t k2m, uint32_t ngm,
-                                                     uint32_t ctr1, uint32_t j, const SweepArgs& a)
+// 12-15) once if a site of the wave is still tied, then the SWEEP-LOW half of
+// each site still tied.  cls1 marks the sites of class k = 2, ngm (heat-bath)
+// those that compare the complement of their uniform, k < 0.  Returns the
+// sites whose (complemented) uniform is below their threshold, each decided
+// exactly as a comparison of its whole 32-bit uniform would decide it.  The
+// planes are compared for the whole word at once: the sites that are not
+// tied have open = acc = 0 and stay so (deciding each tied site by itself, bit
+// by bit, took 161 vector instructions per word and half sweep at L = 128
+// against 144, and 2.10 ms per launch of 20 sweeps at R = 50000 against 1.68).
+template <bool HB>
+__device__ __forceinline__ uint32_t decide_word_tail(uint32_t v, uint32_t mask, uint32_t cls1, uint32_t ngm,
+                                                     const PhiloxHalf& h, const SweepArgs& a, const PhiloxKeys& K)
 {
-    uint32_t below = 0u;
+    uint32_t acc[1] = {0u}, open[1] = {mask};
+    const uint32_t c1[1] = {cls1};
 #pragma unroll
     for (int kk = 2; kk < 4; ++kk) {
-        if (mask == 0u) return below;
-        const U4 P = philox10u(4u * v + (uint32_t)kk, ctr1, j, a.tag | kStreamSweepHigh, a.key0, a.key1);
-        uint32_t rem = mask;
-        while (rem) {
-            const uint32_t b = (uint32_t)__builtin_ctz(rem);
-            rem &= rem - 1u;
-            const uint32_t th = ((k2m >> b) & 1u) ? a.t2h : a.t4h;
-            const uint32_t x = ((((P.x >> b) & 1u) << 3) | (((P.y >> b) & 1u) << 2) | (((P.z >> b) & 1u) << 1) |
-                                ((P.w >> b) & 1u)) ^ (((ngm >> b) & 1u) * 15u);
-            const uint32_t t = (th >> (12 - 4 * kk)) & 15u;
-            if (x != t) {
-                mask &= ~(1u << b);
-                if (x < t) below |= 1u << b;
-            }
+        if (!__any(open[0] != acc[0])) return acc[0];
+        const U4 P = philox10_h(4u * v + (uint32_t)kk, a.tag | kStreamSweepHigh, h, a.key0, a.key1, K);
+        uint32_t x[4][1] = {{P.x}, {P.y}, {P.z}, {P.w}};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if constexpr (HB) x[q][0] ^= ngm;
+            open_plane<1>(x[q], plane_bits(a, 4 * kk + q), c1, acc, open);
         }
     }
+    uint32_t below = acc[0];
+    mask = open[0] & ~acc[0];
     while (mask) {
         const uint32_t b = (uint32_t)__builtin_ctz(mask);
         mask &= mask - 1u;
         const uint32_t q = 32u * v + b;
-        const U4 P = philox10u(q >> 3, ctr1, j, a.tag | kStreamSweepLow, a.key0, a.key1);
+        const U4 P = philox10_h(q >> 3, a.tag | kStreamSweepLow, h, a.key0, a.key1, K);
         const uint32_t word = pick(P, (q >> 1) & 3u);
-        const uint32_t lo = ((q & 1u) ? (word & 0xFFFFu) : (word >> 16)) ^ (((ngm >> b) & 1u) * 0xFFFFu);
-        if (lo < (((k2m >> b) & 1u) ? a.t2l : a.t4l)) below |= 1u << b;
+        uint32_t lo = (q & 1u) ? (word & 0xFFFFu) : (word >> 16);
+        if (HB && ((ngm >> b) & 1u)) lo ^= 0xFFFFu;
+        if (lo < (((cls1 >> b) & 1u) ? a.t2l : a.t4l)) below |= 1u << b;
     }
     return below;
 }
 
 // Tie queue of one wave.  The sites still tied after decide8_group are rare
 // (2^-8 each), so instead of evaluating the later Philox blocks for every
-// word, every word of the lanes' S words that holds a tied site is queued in
-// LDS and decided by one lane, which evaluates the later blocks once for all
-// of the word's tied sites.  Entry i of the queue is four words:
-//   queue[i]            lane | slot << 6   (slot: which of the lane's S words)
-//   queue[Q + i]        the word's tied sites
-//   queue[2 Q + i]      the tied sites of class k = 2
-//   queue[3 Q + i]      the tied sites that compare the complement of their
-//                       uniform (heat-bath, k < 0)
-// with Q = QCAP.  Each slot's entries are placed by a wave vote: the lanes with
-// a tie in that slot take consecutive entries in lane order.
-//
-// vj(lane, slot, &v, &j) gives the word and replica of a lane's slot, and
-// word(lane, slot) the LDS address of that word, into which the resolving lane
-// xors the additional flips (each word is in one entry, so no two lanes touch
-// the same word).  If the queue would hold more than min(a.qcap, QCAP)
-// entries, every lane decides its own tied sites instead and extra[s] receives
-// its additional flips (zero otherwise).
-template <int S, int QCAP, class VJ, class WORD>
-__device__ __forceinline__ void resolve_ties_wave(const uint32_t (&tie)[S], const uint32_t (&cls1)[S],
-                                                  const uint32_t (&ng)[S], int lane, uint32_t ctr1, const SweepArgs& a,
-                                                  uint32_t* queue, uint32_t (&extra)[S], const VJ& vj, const WORD& word)
+// word, every word that holds a tied site is queued in LDS and decided by one
+// lane, which evaluates the later blocks once for all of the word's tied
+// sites.  Entry i of the queue is the four words
+//   q[4 i]      the word's number in the wave (the caller's encoding)
+//   q[4 i + 1]  the word's tied sites
+//   q[4 i + 2]  its sites of class k = 2
+//   q[4 i + 3]  its sites that compare the complement of their uniform
+// Each word's entries are placed by a wave vote: the lanes with a tie take
+// consecutive entries in lane order.
+// Queues the tied words of one group of NG words, id[g] their numbers, after
+// the nq entries already queued.  If the queue would then hold more than
+// min(a.qcap, kTieQueue) entries, every lane decides the group's words itself:
+// own(g, tie, cls1, ng) does so for word g.
+template <int NG, class OWN>
+__device__ __forceinline__ void queue_ties(const uint32_t (&tie)[NG], const uint32_t (&cls1)[NG],
+                                           const uint32_t (&ng)[NG], const uint32_t (&id)[NG], const SweepArgs& a,
+                                           uint32_t* queue, uint32_t& nq, const OWN& own)
 {
-    const uint32_t cap = min(a.qcap, (uint32_t)QCAP);
-    uint64_t vote[S];
+    uint64_t vote[NG];
     uint32_t total = 0u;
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-        extra[s] = 0u;
-        vote[s] = __ballot(tie[s] != 0u);
-        total += (uint32_t)__popcll(vote[s]);
+    for (int g = 0; g < NG; ++g) {
+        vote[g] = __ballot(tie[g] != 0u);
+        total += (uint32_t)__popcll(vote[g]);
     }
-    if (total == 0u) return;
-    if (total > cap) {
+    if (__builtin_expect(nq + total > min(a.qcap, (uint32_t)kTieQueue), 0)) {
+#pragma unroll 1
+        for (int g = 0; g < NG; ++g) {
+            uint32_t t = 0u, c = 0u, n = 0u;
 #pragma unroll
-        for (int s = 0; s < S; ++s) {
-            if (tie[s] == 0u) continue;
-            uint32_t v, j;
-            vj(lane, s, &v, &j);
-            extra[s] = decide_word_tail(v, tie[s], cls1[s] & tie[s], ng[s] & tie[s], ctr1, j, a);
+            for (int i = 0; i < NG; ++i) {
+                t = (i == g) ? tie[i] : t;
+                c = (i == g) ? cls1[i] : c;
+                n = (i == g) ? ng[i] : n;
+            }
+            own(g, t, c, n);
         }
         return;
     }
-    uint32_t base = 0u;
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-        if (tie[s] != 0u) {
-            const uint32_t lo = (uint32_t)vote[s], hi = (uint32_t)(vote[s] >> 32);
-            const uint32_t i = base + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
-            queue[i] = (uint32_t)lane | ((uint32_t)s << 6);
-            queue[QCAP + i] = tie[s];
-            queue[2 * QCAP + i] = cls1[s] & tie[s];
-            queue[3 * QCAP + i] = ng[s] & tie[s];
+    for (int g = 0; g < NG; ++g) {
+        if (tie[g] != 0u) {
+            const uint32_t lo = (uint32_t)vote[g], hi = (uint32_t)(vote[g] >> 32);
+            const uint32_t i = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, nq));
+            reinterpret_cast<uint4*>(queue)[i] = make_uint4(id[g], tie[g], cls1[g], ng[g]);
         }
-        base += (uint32_t)__popcll(vote[s]);
+        nq += (uint32_t)__popcll(vote[g]);
     }
+}
+
+// Decides the nq queued words, one per lane: half(id, &v) gives a word's index
+// in its replica and the shared part of its Philox blocks, and apply(id, f)
+// takes the additional flips of a word (each word is in one entry, so no two
+// lanes touch the same word).
+template <bool HB, class HALF, class APPLY>
+__device__ __forceinline__ void resolve_ties(uint32_t nq, const SweepArgs& a, const PhiloxKeys& K,
+                                             const uint32_t* queue, int lane, const HALF& half, const APPLY& apply)
+{
     wave_lds_sync();
-    for (uint32_t i = (uint32_t)lane; i < total; i += 64u) {
-        const uint32_t e = queue[i];
-        const int owner = (int)(e & 63u), s = (int)(e >> 6);
-        uint32_t v, j;
-        vj(owner, s, &v, &j);
-        const uint32_t f = decide_word_tail(v, queue[QCAP + i], queue[2 * QCAP + i], queue[3 * QCAP + i], ctr1, j, a);
-        if (f) atomicXor(word(owner, s), f);
+    for (uint32_t i = (uint32_t)lane; i < nq; i += 64u) {
+        const uint4 e = reinterpret_cast<const uint4*>(queue)[i];
+        uint32_t v;
+        const PhiloxHalf h = half(e.x, &v);
+        apply(e.x, decide_word_tail<HB>(v, e.y, e.z, e.w, h, a, K));
     }
     wave_lds_sync();
 }
@@ -1035,6 +1049,7 @@ __device__ __forceinline__ void sweep_regs(const SweepArgs& a, const LaneInfo& l
     } else {
         s0[0] = s1[0] = 0u;
     }
+    const PhiloxKeys K = philox_keys(a.key0, a.key1);
     for (int t = 0; t < a.nsweeps; ++t) {
         const uint32_t g = a.g0 + (uint32_t)t;
         if constexpr (LCG) {
@@ -1042,8 +1057,8 @@ __device__ __forceinline__ void sweep_regs(const SweepArgs& a, const LaneInfo& l
             half_sweep_lcg<L, 0>(s0, s1, li.lane, li.gl, P.x, a);
             half_sweep_lcg<L, 1>(s1, s0, li.lane, li.gl, P.y, a);
         } else {
-            half_sweep<L, 0, HB>(s0, s1, li.lane, li.gl, g, li.j, a);
-            half_sweep<L, 1, HB>(s1, s0, li.lane, li.gl, g, li.j, a);
+            half_sweep<L, 0, HB>(s0, s1, li.lane, li.gl, g, li.j, a, K);
+            half_sweep<L, 1, HB>(s1, s0, li.lane, li.gl, g, li.j, a, K);
         }
     }
     const Neighbours<L, 0> nb(s1, li.lane, li.gl);
@@ -1089,48 +1104,47 @@ struct LdsRep {
 // SLOTS, each chunk followed by the wave's tie resolution.
 template <int L, int C, bool HB>
 __device__ __forceinline__ void half_sweep_lds(const LdsRep<L>& rep, int gl, uint32_t g, uint32_t j,
-                                               const SweepArgs& a, uint32_t* queue)
+                                               const SweepArgs& a, const PhiloxKeys& K, uint32_t* queue)
 {
     using Gm = Geo<L>;
-    constexpr int S = Gm::SLOTS;
-    static_assert(Gm::K % S == 0, "slots divide the words of a lane");
-    const uint32_t ctr1 = 2u * g + (uint32_t)C;
+    constexpr int S = Gm::SLOTS, NG = 4;  // groups of four words share the branches of decide8_group
+    static_assert(Gm::K % S == 0 && S % NG == 0, "slots divide the words of a lane");
+    const PhiloxHalf h = philox_half(2u * g + (uint32_t)C, j, a.key0);
 #pragma unroll 1
     for (int k0 = 0; k0 < Gm::K; k0 += S) {
-        uint32_t tie[S], k2[S], ng[S], extra[S];
-        // groups of four words share the per-plane branches of decide8_group
-        // (L = 128: one group, L = 256: two)
-        constexpr int NG = 4;
-        static_assert(S % NG == 0, "slot groups");
+        uint32_t nq = 0u;
 #pragma unroll
         for (int s0 = 0; s0 < S; s0 += NG) {
-            uint32_t w[NG], v[NG], tg[NG], cg[NG], ngg[NG];
+            uint32_t w[NG], tie[NG], cls1[NG], ng[NG], id[NG];
             Nb n[NG];
 #pragma unroll
-            for (int g = 0; g < NG; ++g) {
-                const int k = k0 + s0 + g;
-                n[g] = rep.template nb<C>(k, gl);
-                w[g] = rep.at(C, k, gl);
-                v[g] = (uint32_t)(gl * Gm::K + k);
+            for (int i = 0; i < NG; ++i) {
+                n[i] = rep.template nb<C>(k0 + s0 + i, gl);
+                w[i] = rep.at(C, k0 + s0 + i, gl);
+                id[i] = (uint32_t)((k0 + s0 + i) * 64 + gl);  // the word's place in the LDS replica
             }
-            decide8_group<NG, HB>(w, n, v, ctr1, j, a, tg, cg, ngg);
+            const auto blk = [&](int i, uint32_t kk) {
+                return philox10_h(4u * (uint32_t)(gl * Gm::K + k0 + s0 + i) + kk, a.tag | kStreamSweepHigh, h,
+                                  a.key0, a.key1, K);
+            };
+            decide8_group<NG, HB>(w, n, blk, a, tie, cls1, ng);
 #pragma unroll
-            for (int g = 0; g < NG; ++g) {
-                rep.at(C, k0 + s0 + g, gl) = w[g];
-                tie[s0 + g] = tg[g];
-                k2[s0 + g] = cg[g];
-                ng[s0 + g] = ngg[g];
-            }
+            for (int i = 0; i < NG; ++i) rep.at(C, k0 + s0 + i, gl) = w[i];
+            const auto own = [&](int i, uint32_t t, uint32_t c, uint32_t m) {
+                rep.at(C, k0 + s0 + i, gl) ^=
+                    decide_word_tail<HB>((uint32_t)(gl * Gm::K + k0 + s0 + i), t, c, m, h, a, K);
+            };
+            queue_ties<NG>(tie, cls1, ng, id, a, queue, nq, own);
         }
-        const auto vj = [&](int owner, int s, uint32_t* vo, uint32_t* jo) {
-            *vo = (uint32_t)(owner * Gm::K + k0 + s);
-            *jo = j;
+        if (nq == 0u) continue;
+        const auto half = [&](uint32_t w, uint32_t* v) {
+            *v = (w & 63u) * (uint32_t)Gm::K + (w >> 6);
+            return h;
         };
-        const auto word = [&](int owner, int s) { return &rep.at(C, k0 + s, owner); };
-        resolve_ties_wave<S, Gm::QCAP>(tie, k2, ng, gl, ctr1, a, queue, extra, vj, word);
-#pragma unroll
-        for (int s = 0; s < S; ++s)
-            if (extra[s]) rep.at(C, k0 + s, gl) ^= extra[s];
+        const auto apply = [&](uint32_t w, uint32_t f) {
+            if (f) atomicXor(&rep.w[C * Gm::NW + w], f);
+        };
+        resolve_ties<HB>(nq, a, K, queue, gl, half, apply);
     }
     wave_lds_sync();
 }
@@ -1153,7 +1167,7 @@ __device__ __forceinline__ void half_sweep_lds_lcg(const LdsRep<L>& rep, int gl,
     wave_lds_sync();
 }
 
-// The wave's LDS: replica [2][NW], then the tie queue and the slot results.
+// The wave's LDS: replica [2][NW], then the tie queue.
 template <int L, bool INT8, bool HB, bool LCG>
 __device__ __forceinline__ void sweep_lds(const SweepArgs& a, uint32_t j, uint32_t* lds)
 {
@@ -1177,14 +1191,15 @@ __device__ __forceinline__ void sweep_lds(const SweepArgs& a, uint32_t j, uint32
         rep.at(1, k, gl) = w1;
     }
     wave_lds_sync();
+    const PhiloxKeys K = philox_keys(a.key0, a.key1);
     for (int t = 0; t < a.nsweeps; ++t) {
         const uint32_t g = a.g0 + (uint32_t)t;
         if constexpr (LCG) {
             half_sweep_lds_lcg<L, 0>(rep, gl, g, j, a);
             half_sweep_lds_lcg<L, 1>(rep, gl, g, j, a);
         } else {
-            half_sweep_lds<L, 0, HB>(rep, gl, g, j, a, queue);
-            half_sweep_lds<L, 1, HB>(rep, gl, g, j, a, queue);
+            half_sweep_lds<L, 0, HB>(rep, gl, g, j, a, K, queue);
+            half_sweep_lds<L, 1, HB>(rep, gl, g, j, a, K, queue);
         }
     }
     uint32_t anti = 0, downs = 0;
@@ -1205,13 +1220,15 @@ __device__ __forceinline__ void sweep_lds(const SweepArgs& a, uint32_t j, uint32
 }
 
 // Minimum waves per SIMD the sweep kernels are compiled for.  At L = 128 the
-// grouped decision needs a few more registers than fit three waves per SIMD;
-// holding the kernel to three (a few values go to scratch outside the inner
-// loops) is faster than two waves without the cap.
+// grouped decision with the round keys in vector registers needs two registers
+// more than fit four waves per SIMD; holding the kernel to four (two values go
+// to scratch outside the inner loops) takes 1.59 ms per launch at R = 50000,
+// theta = 20, against 1.78 with three waves (2.10 before the keys, the tail by
+// planes and the plane block).
 template <int L>
 constexpr int sweep_min_waves()
 {
-    return L == 128 ? 3 : 1;
+    return L == 128 ? 4 : 1;
 }
 
 // Threads per block of the single-run sweep kernel.

@@ -30,7 +30,7 @@ __attribute__((amdgpu_waves_per_eu(sweep_min_waves<L>(), 8))) void sweep_kernel(
 {
     using Gm = Geo<L>;
     constexpr int WPB = sweep_block<L>() / 64;
-    __shared__ uint32_t lds[Gm::lds_words(WPB) > 0 ? Gm::lds_words(WPB) : 1];
+    __shared__ __align__(16) uint32_t lds[Gm::lds_words(WPB) > 0 ? Gm::lds_words(WPB) : 1];
     if (a.n_dev) a.n_rep = min(a.n_rep, (int32_t)*a.n_dev);
     sweep_waves<L, INT8, U == kHeatbath, U == kLcg>(a, (int)blockIdx.x * WPB, WPB, lds);
 }
