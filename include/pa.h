@@ -59,10 +59,9 @@ typedef enum {
     PA_SPIN_BITS = 1,   /* one bit per spin, per-colour 32-site words (multi-spin coding) */
     PA_SPIN_INTERLEAVED = 2  /* one signed byte per spin, the same spin of all replicas adjacent
                                 (spin (x, y) of replica j at byte (y L + x) * stride + j, stride the
-                                capacity rounded up to 64), swept replica-parallel: each replica
-                                goes through its lattice site by site on its own thread (four lanes
-                                sharing a colour's sites from L = 64 on; Sec. 3, the
-                                replica-parallel setup, the paper's general fall-back); single runs
+                                capacity rounded up to 64; Sec. 3, the replica-parallel setup);
+                                sweeps pack the population into the words of PA_SPIN_BITS and
+                                unpack it again (once per pa_sweep or pa_anneal call); single runs
                                 only (pa_batch_init refuses it) */
 } pa_layout;
 
@@ -134,11 +133,11 @@ pa_status pa_init(const pa_params* p, void* d_workspace, size_t bytes, void* hip
  * paper's multi-spin-coded variant (Sec. 4): per sweep and per 32-site word of
  * one colour, one Philox draw seeds r' = 1664525 r + 1013904223 mod 2^32, and
  * the word's site b takes the (b+1)-th output; a different Markov chain with
- * the same stationary distribution.  Updates E_j and M_j.  Asynchronous; on
- * the int8 and bit stores the sweep kernel also queues the statistics of the
- * swept population (histogram and integer sums), which the next
- * pa_observables, pa_alpha, pa_adapt_beta or pa_resample reads after waiting
- * for the stream.
+ * the same stationary distribution.  Updates E_j and M_j.  Asynchronous;
+ * where the statistics are taken in the sweep's epilogue (pa_set_stats_path)
+ * it also queues those of the swept population (histogram and integer sums),
+ * which the next pa_observables, pa_alpha, pa_adapt_beta or pa_resample reads
+ * after waiting for the stream.
  * Errors: PA_EINVAL (nsweeps < 0), PA_ESTATE, PA_EHIP. */
 pa_status pa_sweep(pa_run* r, int32_t nsweeps);
 
@@ -269,14 +268,13 @@ pa_status pa_download_counts(pa_run* r, uint32_t* counts, int32_t* n);
 pa_status pa_set_tie_queue_cap(pa_run* r, int32_t cap);
 
 /* Test and tuning hook for the population statistics of Sec. 2.1 (energy
- * histogram and integer moment sums of each new population).  The int8 and
- * bit stores can take them in the epilogue of the sweep that makes the
- * population (every wave adds its replicas with device atomics, then one
- * block sums them) or in a separate pass over E and M.  PA_STATS_AUTO (the
+ * histogram and integer moment sums of each new population).  They are taken
+ * in the epilogue of the sweep that makes the population (every wave adds its
+ * replicas with device atomics, then one block sums them) or in a separate
+ * pass over E and M.  PA_STATS_AUTO (the
  * default) takes the epilogue where it measured faster: one replica per wave
  * (L >= 64) and R <= 32768, or L = 256.  PA_STATS_EPILOGUE and PA_STATS_PASS
- * force one of them (the interleaved store always uses the pass).  Results do
- * not depend on the choice.
+ * force one of them.  Results do not depend on the choice.
  * Errors: PA_EINVAL (unknown mode), PA_ESTATE. */
 typedef enum { PA_STATS_AUTO = 0, PA_STATS_EPILOGUE = 1, PA_STATS_PASS = 2 } pa_stats_path;
 pa_status pa_set_stats_path(pa_run* r, int32_t mode);

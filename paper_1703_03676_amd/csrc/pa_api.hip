@@ -8,6 +8,7 @@
 // bisection) are computed with a fixed operation order, ascending energy bins,
 // and without contraction (-ffp-contract=off), so a run is reproducible bit for
 // bit from its seed and schedule.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -184,20 +185,47 @@ void key_of(const pa_run* r, uint32_t* k0, uint32_t* k1, uint32_t* tag)
 // sweep.
 bool stats_in_epilogue(const pa_run* r)
 {
-    if (r->p.layout == PA_SPIN_INTERLEAVED) return false;
     if (r->stats_path != PA_STATS_AUTO) return r->stats_path == PA_STATS_EPILOGUE;
     return r->L == 256 || (r->L >= 64 && r->p.R <= 32768);
 }
 
-// The sweep kernel of the run's spin store: bit-sliced (int8 and bit stores)
-// or replica-parallel (interleaved store).
-hipError_t launch_sweep_of(const pa_run* r, pa::SweepArgs& a)
+// The two ping-pong stores the sweeps and the replica copy of a call work on
+// (element r->cur holds the population): the run's own, or, for the interleaved
+// store, two bit stores side by side in the half that does not hold the
+// population (each N/8 bytes per replica; the half has N per replica).
+struct SpinView {
+    uint8_t* spin[2];
+    int32_t layout;
+    size_t rep_bytes;
+};
+
+SpinView own_view(const pa_run* r) { return SpinView{{r->spin[0], r->spin[1]}, r->p.layout, r->lo.rep_bytes}; }
+
+SpinView sweep_view(const pa_run* r)
 {
-    if (r->p.layout == PA_SPIN_INTERLEAVED) {
-        a.stride = r->lo.stride;
-        return pa::launch_sweep_rp(r->L, update_of(r->p), a, r->stream);
-    }
-    return pa::launch_sweep(r->L, r->p.layout, update_of(r->p), a, r->stream);
+    if (r->p.layout != PA_SPIN_INTERLEAVED) return own_view(r);
+    SpinView v;
+    v.layout = PA_SPIN_BITS;
+    v.rep_bytes = (size_t)r->N / 8;
+    uint8_t* half = r->spin[r->cur ^ 1];
+    v.spin[r->cur] = half;
+    v.spin[r->cur ^ 1] = half + align_up((size_t)r->lo.capacity * v.rep_bytes);
+    return v;
+}
+
+// The population of an interleaved store into its sweep view, and the view's
+// population back (nothing to do for the other stores, whose view is the
+// store).
+hipError_t enter_view(const pa_run* r, const SpinView& v)
+{
+    if (r->p.layout != PA_SPIN_INTERLEAVED) return hipSuccess;
+    return pa::launch_pack(r->L, r->spin[r->cur], r->lo.stride, (int32_t)r->R_cur, v.spin[r->cur], r->stream);
+}
+
+hipError_t leave_view(const pa_run* r, const SpinView& v)
+{
+    if (r->p.layout != PA_SPIN_INTERLEAVED) return hipSuccess;
+    return pa::launch_unpack(r->L, v.spin[r->cur], r->lo.stride, (int32_t)r->R_cur, r->spin[r->cur], r->stream);
 }
 
 // Queues nsweeps sweeps of the current population (or, with `init`, the
@@ -207,9 +235,11 @@ hipError_t launch_sweep_of(const pa_run* r, pa::SweepArgs& a)
 // (refresh_stats).
 pa_status launch_sweeps(pa_run* r, int32_t nsweeps, bool init, uint64_t ver)
 {
+    const SpinView view = sweep_view(r);
+    if (!init) HIPCHK(enter_view(r, view));
     pa::SweepArgs a;
     std::memset(&a, 0, sizeof(a));
-    a.spin = r->spin[r->cur];
+    a.spin = view.spin[r->cur];
     a.E = r->E[r->cur];
     a.M = r->M[r->cur];
     a.n_rep = (int32_t)r->R_cur;
@@ -227,7 +257,8 @@ pa_status launch_sweeps(pa_run* r, int32_t nsweeps, bool init, uint64_t ver)
         a.nbins = r->nbins;
     }
     r->gathered_version = 0;
-    HIPCHK(launch_sweep_of(r, a));
+    HIPCHK(pa::launch_sweep(r->L, view.layout, update_of(r->p), a, r->stream));
+    if (init || nsweeps > 0) HIPCHK(leave_view(r, view));
     if (epilogue) {
         HIPCHK(pa::launch_stats_gather(r->acc, r->acc_hist, r->nbins, r->N, r->stats, r->hist, r->hstats_dev,
                                        r->stream));
@@ -287,7 +318,8 @@ host::Hist window(const pa_run* r) { return host::hist_window(r->h_hist.data(), 
 // Without `copy` the caller's next sweep gathers the parents itself.  The
 // scatter also clears the statistics block and the histogram, so the
 // statistics of the resampled population need no separate reset.
-pa_status queue_resample(pa_run* r, double beta_next, bool copy, double* lnQ, int32_t* Emin, const Scratch& sc)
+pa_status queue_resample(pa_run* r, const SpinView& view, double beta_next, bool copy, double* lnQ, int32_t* Emin,
+                         const Scratch& sc)
 {
     const host::Hist h = window(r);
     const int bmin = h.bmin, nwin = h.bmax - h.bmin + 1;
@@ -303,13 +335,13 @@ pa_status queue_resample(pa_run* r, double beta_next, bool copy, double* lnQ, in
                              sc.counts, sc.bsum, r->stream));
     HIPCHK(pa::launch_scatter(sc.counts, sc.bsum, n, r->lo.capacity, sc.parent, r->stats, r->hist, r->nbins,
                               r->stream));
-    if (copy && r->p.layout == PA_SPIN_INTERLEAVED)
-        HIPCHK(pa::launch_copy_rp(r->spin[r->cur], r->E[r->cur], r->M[r->cur], sc.parent, &r->stats->r_new,
-                                  r->lo.capacity, r->N, r->lo.stride, r->spin[nxt], r->E[nxt], r->M[nxt],
-                                  r->stream));
+    if (copy && view.layout == PA_SPIN_INTERLEAVED)
+        HIPCHK(pa::launch_copy_interleaved(view.spin[r->cur], r->E[r->cur], r->M[r->cur], sc.parent,
+                                           &r->stats->r_new, r->lo.capacity, r->N, r->lo.stride, view.spin[nxt],
+                                           r->E[nxt], r->M[nxt], r->stream));
     else if (copy)
-        HIPCHK(pa::launch_copy(r->spin[r->cur], r->E[r->cur], r->M[r->cur], sc.parent, &r->stats->r_new,
-                               r->lo.capacity, r->lo.rep_bytes, r->spin[nxt], r->E[nxt], r->M[nxt], r->stream));
+        HIPCHK(pa::launch_copy(view.spin[r->cur], r->E[r->cur], r->M[r->cur], sc.parent, &r->stats->r_new,
+                               r->lo.capacity, view.rep_bytes, view.spin[nxt], r->E[nxt], r->M[nxt], r->stream));
     r->counts_n = n;
     return PA_OK;
 }
@@ -462,7 +494,7 @@ static pa_status resample_with(pa_run* r, double beta_next, pa_resample_info* ou
 
     double lnQ;
     int32_t Emin;
-    st = queue_resample(r, beta_next, true, &lnQ, &Emin, sc);
+    st = queue_resample(r, own_view(r), beta_next, true, &lnQ, &Emin, sc);
     if (st != PA_OK) return st;
     // the host waits only for the total; the copy runs on meanwhile
     uint32_t* rn = (uint32_t*)(r->pinned + r->pinned_bytes - 8);
@@ -489,29 +521,13 @@ pa_status pa_resample(pa_run* r, double beta_next, pa_resample_info* out)
     return resample_with(r, beta_next, out, run_scratch(r));
 }
 
-pa_status pa_anneal(pa_run* r, const pa_schedule* sc, int32_t max_steps, pa_obs* out, float* sweep_ms, int32_t cap,
-                    int32_t* nsteps)
+// The steps of pa_anneal (arguments validated, statistics of the current
+// population on the host) on the stores of `view`.
+static pa_status anneal_steps(pa_run* r, const SpinView& view, const pa_schedule* sc, int32_t max_steps, pa_obs* out,
+                              float* sweep_ms, int32_t cap, int32_t* nsteps)
 {
-    if (nsteps) *nsteps = 0;
-    pa_status st = usable(r);
-    if (st != PA_OK) return st;
-    if (!sc || max_steps < 0 || cap < 0 || (cap > 0 && !out) || sc->theta < 0 || !std::isfinite(sc->beta_f) ||
-        sc->beta_f < r->beta)
-        return PA_EINVAL;
-    if (sc->mode == PA_STEP_FIXED) {
-        if (!(sc->dbeta > 0.0) || !std::isfinite(sc->dbeta)) return PA_EINVAL;
-    } else if (sc->mode == PA_STEP_ADAPTIVE) {
-        if (!(sc->alpha_star > 0.0 && sc->alpha_star < 1.0)) return PA_EINVAL;
-    } else {
-        return PA_EINVAL;
-    }
+    pa_status st;
     const bool record = (r->p.flags & PA_FLAG_MHR) != 0;
-    st = refresh_stats(r, false, r->parts);
-    if (st != PA_OK) return st;
-    if (sweep_ms && cap > 0 && !r->ev_t0) {
-        HIPCHK(hipEventCreate(&r->ev_t0));
-        HIPCHK(hipEventCreate(&r->ev_t1));
-    }
     uint32_t k0, k1, tag;
     key_of(r, &k0, &k1, &tag);
     int32_t done = 0;
@@ -538,25 +554,23 @@ pa_status pa_anneal(pa_run* r, const pa_schedule* sc, int32_t max_steps, pa_obs*
         double lnQ;
         int32_t Emin;
         // with sweeps, the sweep kernel loads every child from its parent: the
-        // replica copy and the sweep's load are one pass over the store (the
-        // replica-parallel sweep of the interleaved store works in place and
-        // takes the copy first)
-        const bool gather = sc->theta > 0 && r->p.layout != PA_SPIN_INTERLEAVED;
+        // replica copy and the sweep's load are one pass over the store
+        const bool gather = sc->theta > 0;
         const bool epilogue = sc->theta > 0 && stats_in_epilogue(r);
-        st = queue_resample(r, bn, !gather, &lnQ, &Emin, run_scratch(r));
+        st = queue_resample(r, view, bn, !gather, &lnQ, &Emin, run_scratch(r));
         if (st != PA_OK) return st;
         const int nxt = r->cur ^ 1;
         const uint32_t* n_dev = &r->stats->r_new;
         if (sc->theta > 0) {
             pa::SweepArgs a;
             std::memset(&a, 0, sizeof(a));
-            a.spin = r->spin[nxt];
+            a.spin = view.spin[nxt];
             a.E = r->E[nxt];
             a.M = r->M[nxt];
             a.n_rep = r->lo.capacity;
             a.n_dev = n_dev;
-            a.src = gather ? r->spin[r->cur] : nullptr;
-            a.parent = gather ? r->parent : nullptr;
+            a.src = view.spin[r->cur];
+            a.parent = r->parent;
             a.nsweeps = sc->theta;
             a.g0 = (uint32_t)r->sweeps;
             a.key0 = k0;
@@ -572,7 +586,7 @@ pa_status pa_anneal(pa_run* r, const pa_schedule* sc, int32_t max_steps, pa_obs*
             host::sweep_thresholds(hb, bn, &a.t2h, &a.t2l, &a.t4h, &a.t4l);
             const bool timed = sweep_ms && done < cap;
             if (timed) HIPCHK(hipEventRecord(r->ev_t0, r->stream));
-            HIPCHK(launch_sweep_of(r, a));
+            HIPCHK(pa::launch_sweep(r->L, view.layout, update_of(r->p), a, r->stream));
             if (timed) HIPCHK(hipEventRecord(r->ev_t1, r->stream));
         }
         // (the scatter of queue_resample has cleared the statistics); they are
@@ -624,6 +638,44 @@ pa_status pa_anneal(pa_run* r, const pa_schedule* sc, int32_t max_steps, pa_obs*
         if (nsteps) *nsteps = done;
     }
     return PA_OK;
+}
+
+pa_status pa_anneal(pa_run* r, const pa_schedule* sc, int32_t max_steps, pa_obs* out, float* sweep_ms, int32_t cap,
+                    int32_t* nsteps)
+{
+    if (nsteps) *nsteps = 0;
+    pa_status st = usable(r);
+    if (st != PA_OK) return st;
+    if (!sc || max_steps < 0 || cap < 0 || (cap > 0 && !out) || sc->theta < 0 || !std::isfinite(sc->beta_f) ||
+        sc->beta_f < r->beta)
+        return PA_EINVAL;
+    if (sc->mode == PA_STEP_FIXED) {
+        if (!(sc->dbeta > 0.0) || !std::isfinite(sc->dbeta)) return PA_EINVAL;
+    } else if (sc->mode == PA_STEP_ADAPTIVE) {
+        if (!(sc->alpha_star > 0.0 && sc->alpha_star < 1.0)) return PA_EINVAL;
+    } else {
+        return PA_EINVAL;
+    }
+    st = refresh_stats(r, false, r->parts);
+    if (st != PA_OK) return st;
+    if (sweep_ms && cap > 0 && !r->ev_t0) {
+        HIPCHK(hipEventCreate(&r->ev_t0));
+        HIPCHK(hipEventCreate(&r->ev_t1));
+    }
+    if (max_steps == 0 || !(r->beta < sc->beta_f)) return PA_OK;
+    // an interleaved population is packed once for all steps; afterwards the
+    // half that held it takes the population of the last completed step, so
+    // the halves change places if the buffers did
+    const SpinView view = sweep_view(r);
+    const int cur0 = r->cur;
+    HIPCHK(enter_view(r, view));
+    st = anneal_steps(r, view, sc, max_steps, out, sweep_ms, cap, nsteps);
+    if (r->p.layout == PA_SPIN_INTERLEAVED && !r->broken) {
+        if (r->cur != cur0) std::swap(r->spin[0], r->spin[1]);
+        HIPCHK(leave_view(r, view));
+        HIPCHK(hipStreamSynchronize(r->stream));
+    }
+    return st;
 }
 
 pa_status pa_alpha(pa_run* r, double beta_prime, double* alpha)

@@ -256,7 +256,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sweep_min_w
     a.key1 = rd.key1;
     a.tag = rd.tag;
     a.qcap = rd.qcap;
-    a.stride = 0u;
     a.acc = nullptr;  // the batch takes its statistics in b_stats
     a.acc_hist = nullptr;
     a.nbins = 0;

@@ -37,12 +37,13 @@ hipError_t launch_copy(const uint8_t* src, const int32_t* Esrc, const int32_t* M
                        const uint32_t* n_new, int32_t cap, size_t rep_bytes, uint8_t* dst, int32_t* Edst,
                        int32_t* Mdst, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, size_t n, hipStream_t s);
-// Interleaved store (pa_rp.hip): the replica-parallel sweep (a.stride set, no
-// fused gather), and the replica copy of resampling for that store.
-hipError_t launch_sweep_rp(int L, int update, const SweepArgs& a, hipStream_t s);
-hipError_t launch_copy_rp(const uint8_t* src, const int32_t* Esrc, const int32_t* Msrc, const uint32_t* parent,
-                          const uint32_t* n_new, int32_t cap, int32_t N, uint32_t stride, uint8_t* dst, int32_t* Edst,
-                          int32_t* Mdst, hipStream_t s);
+// Interleaved store (pa_interleaved.hip): n replicas of it into the bit store
+// (launch_pack) and back, and the replica copy of resampling for that store.
+hipError_t launch_pack(int L, const uint8_t* src, uint32_t stride, int32_t n, uint8_t* dst, hipStream_t s);
+hipError_t launch_unpack(int L, const uint8_t* src, uint32_t stride, int32_t n, uint8_t* dst, hipStream_t s);
+hipError_t launch_copy_interleaved(const uint8_t* src, const int32_t* Esrc, const int32_t* Msrc,
+                                   const uint32_t* parent, const uint32_t* n_new, int32_t cap, int32_t N,
+                                   uint32_t stride, uint8_t* dst, int32_t* Edst, int32_t* Mdst, hipStream_t s);
 // Statistics of the population a sweep launched with SweepArgs::acc has just
 // swept: the epilogue's accumulators summed into st and the histogram window
 // (hist cleared before, r_new kept), published to `host` as by launch_stats,
