@@ -1,11 +1,12 @@
 // Training and inference kernels of the learned temperature-step proposer
 // (MLP 8 -> 64 -> 64 -> 1, ReLU; layout in pa_mlp_dev.h).
 //
-// Training is FP32 with a deterministic fixed-order gradient reduction: one
-// thread per parameter sums its per-sample terms in sample order, so a
-// training run is reproducible bit for bit.  SGD with momentum updates the FP32
-// master weights and refreshes the BF16 copy used for inference.  The loss is
-// the mean squared error on the normalised target.
+// Training is FP32 with a deterministic fixed-order gradient reduction: each
+// block sums the gradient of its samples in matrix-core accumulators
+// (k_backprop), and one thread per parameter sums the blocks in order
+// (k_apply), so a training run is reproducible bit for bit.  SGD with momentum
+// updates the FP32 master weights and refreshes the BF16 copy used for
+// inference.  The loss is the mean squared error on the normalised target.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -21,115 +22,221 @@ namespace pa {
 namespace mlp {
 namespace {
 
-// x_all [n][8], t_all [n] raw -> xn [B][8], tn [B] normalised, for the samples idx[0..B).
-__global__ void k_gather_norm(const float* __restrict__ x_all, const float* __restrict__ t_all,
-                              const int32_t* __restrict__ idx, int B, const float* __restrict__ norm,
-                              float* __restrict__ xn, float* __restrict__ tn)
+// ---------------------------------------------------------------------------
+// Forward pass, deltas and gradient of the mean squared error
+// L = (1/B) sum_s (y_s - t_s)^2, for the samples idx[0..B) (0..B without idx).
+//
+// Block b of the nblk blocks that B samples have takes the tiles of 16 samples
+// b, b + nblk, ..., and leaves the sums over them in its part of the partials
+// (one entry per parameter, then the sum of squared errors).  Its four waves
+// own 16 hidden units each.  All contractions run on the FP32 matrix cores
+// (v_mfma_f32_16x16x4: inputs and accumulation in FP32): lane l holds
+// A[m = l % 16][k] and B[k][n = l % 16] for the k of its quarter q = l / 16 and
+// D[m = 4 q + i][n], i = 0..3.  A contraction over 64 units gives quarter q the
+// k of 16 q .. 16 q + 15, so its operands are contiguous.  The gradients of
+// the block's tiles stay in the accumulators.
+//
+// Bound by latency (two dependent loads, about 40 matrix instructions, six
+// barriers per tile), so a tile has a block of its own up to kMaxParts of them
+// (tiles of 32 samples on eight waves halve the partials but took 8.2 us
+// against 6.4).  One thread per parameter running over all samples kept 19
+// blocks busy for 65 us at B = 256 and 138 us at B = 500; these blocks take
+// 6.4 us at either, k_apply 3.5-4.7.  A training step of 256 samples took 92 us
+// (five launches, an upload and a wait) and takes 10 in two launches.
+// ---------------------------------------------------------------------------
+constexpr int kTile = 16;                // samples per tile
+constexpr int kPartStride = 4804;        // floats per block: parameters, squared error, padding
+constexpr int kMaxParts = 64;            // blocks, so that k_apply stays short
+constexpr int kLd = kHid + 4;            // row length of the tile's activations in LDS
+static_assert(kPartStride > kParams, "one partial per parameter and one for the loss");
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f4 mfma4(float a, float b, f4 c)
 {
-    const int s = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (s >= B) return;
-    const int i = idx ? idx[s] : s;
-    for (int k = 0; k < kIn; ++k) xn[s * kIn + k] = (x_all[i * kIn + k] - norm[k]) / norm[kIn + k];
-    if (t_all) tn[s] = (t_all[i] - norm[2 * kIn]) / norm[2 * kIn + 1];
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// One block of 64 threads per sample: hidden activations and the output.
-__global__ __launch_bounds__(64) void k_forward(const float* __restrict__ xn, const float* __restrict__ p,
-                                                float* __restrict__ h1o, float* __restrict__ h2o,
-                                                float* __restrict__ y)
+// Sum over the 16 lanes of a quarter, and over the four quarters.
+__device__ __forceinline__ float sum_quarter(float v)
 {
-    __shared__ float h[kHid];
-    const int s = (int)blockIdx.x, t = (int)threadIdx.x;
-    float a = p[kB1 + t];
-    for (int k = 0; k < kIn; ++k) a += p[kW1 + t * kIn + k] * xn[s * kIn + k];
-    const float h1 = a > 0.0f ? a : 0.0f;
-    h[t] = h1;
-    h1o[s * kHid + t] = h1;
-    __syncthreads();
-    float a2 = p[kB2 + t];
-    for (int v = 0; v < kHid; ++v) a2 += p[kW2 + t * kHid + v] * h[v];
-    const float h2 = a2 > 0.0f ? a2 : 0.0f;
-    h2o[s * kHid + t] = h2;
-    __syncthreads();
-    h[t] = p[kW3 + t] * h2;
-    __syncthreads();
-    if (t == 0) {
-        float o = p[kB3];
-        for (int v = 0; v < kHid; ++v) o += h[v];
-        y[s] = o;
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) v += __shfl_xor(v, off);
+    return v;
+}
+
+__device__ __forceinline__ float sum_quarters(float v)
+{
+    v += __shfl_xor(v, 16);
+    return v + __shfl_xor(v, 32);
+}
+
+__global__ __launch_bounds__(256) void k_backprop(const float* __restrict__ x_all, const float* __restrict__ t_all,
+                                                  const int32_t* __restrict__ idx, int B,
+                                                  const float* __restrict__ norm, const float* __restrict__ p, int blk0,
+                                                  int nblk, float* __restrict__ parts)
+{
+    __shared__ __align__(16) float sh1[kTile][kLd], sd2[kTile][kLd], sd1[kTile][kLd];
+    __shared__ float sx[kTile][kIn + 1], sy[4][kTile], sdy[kTile];
+    const int lane = (int)(threadIdx.x & 63u), w = (int)(threadIdx.x >> 6);
+    const int n = lane & 15, q = lane >> 4;
+    const int u = 16 * w + n;  // the hidden unit of this lane's column
+    // weights of this lane, the same for every tile
+    float w1[2], w2r[16], w2c[16];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) w1[i] = p[kW1 + u * kIn + 4 * i + q];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        w2r[i] = p[kW2 + u * kHid + 16 * q + i];    // row u: layer 2
+        w2c[i] = p[kW2 + (16 * q + i) * kHid + u];  // column u: its transpose, for the deltas of layer 1
+    }
+    const float b1 = p[kB1 + u], b2 = p[kB2 + u], w3 = p[kW3 + u], b3 = p[kB3];
+    const float t_mean = norm[2 * kIn], t_std = norm[2 * kIn + 1];
+    f4 gw2[4] = {}, gw1 = {};
+    float gb1 = 0.0f, gb2 = 0.0f, gw3 = 0.0f, gb3 = 0.0f, sq = 0.0f;
+
+    for (int s0 = (blk0 + (int)blockIdx.x) * kTile; s0 < B; s0 += nblk * kTile) {
+        // layer 1: A = the tile's normalised features (row n of the tile, features q and 4 + q)
+        const bool have = s0 + n < B;
+        const int row = have ? (idx ? idx[s0 + n] : s0 + n) : 0;
+        f4 z = {b1, b1, b1, b1};
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int k = 4 * i + q;
+            const float xn = have ? (x_all[(size_t)row * kIn + k] - norm[k]) / norm[kIn + k] : 0.0f;
+            if (w == 0) sx[n][k] = xn;
+            z = mfma4(xn, w1[i], z);
+        }
+        const float tn = (w == 0 && have) ? (t_all[row] - t_mean) / t_std : 0.0f;
+        f4 h1, h2, d2, d1;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            h1[i] = z[i] > 0.0f ? z[i] : 0.0f;
+            sh1[4 * q + i][u] = h1[i];
+        }
+        __syncthreads();
+        // layer 2
+        z = f4{b2, b2, b2, b2};
+#pragma unroll
+        for (int i = 0; i < 16; i += 4) {
+            const f4 a = *reinterpret_cast<const f4*>(&sh1[n][16 * q + i]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) z = mfma4(a[k], w2r[i + k], z);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            h2[i] = z[i] > 0.0f ? z[i] : 0.0f;
+            const float part = sum_quarter(w3 * h2[i]);
+            if (n == 0) sy[w][4 * q + i] = part;
+        }
+        __syncthreads();
+        // output and its delta
+        if (w == 0 && lane < kTile) {
+            const float d = b3 + sy[0][n] + sy[1][n] + sy[2][n] + sy[3][n] - tn;
+            sdy[n] = have ? 2.0f * d / (float)B : 0.0f;
+            if (have) sq += d * d;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float dy = sdy[4 * q + i];
+            d2[i] = h2[i] > 0.0f ? dy * w3 : 0.0f;
+            sd2[4 * q + i][u] = d2[i];
+            gw3 += dy * h2[i];
+            gb2 += d2[i];
+        }
+        if (w == 0 && lane < kTile) gb3 += sdy[n];
+        __syncthreads();
+        // deltas of layer 1
+        z = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int i = 0; i < 16; i += 4) {
+            const f4 a = *reinterpret_cast<const f4*>(&sd2[n][16 * q + i]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) z = mfma4(a[k], w2c[i + k], z);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            d1[i] = h1[i] > 0.0f ? z[i] : 0.0f;
+            sd1[4 * q + i][u] = d1[i];
+            gb1 += d1[i];
+        }
+        __syncthreads();
+        // gradient of W2: rows of this wave's units, all columns, over the 16 samples
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float a = sd2[4 * i + q][u];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) gw2[c] = mfma4(a, sh1[4 * i + q][16 * c + n], gw2[c]);
+        }
+        // gradient of W1
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            gw1 = mfma4(sd1[4 * i + q][u], n < kIn ? sx[4 * i + q][n] : 0.0f, gw1);
+        __syncthreads();  // the next tile reuses the tables
+    }
+
+    float* out = parts + (size_t)blockIdx.x * kPartStride;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[kW2 + (16 * w + 4 * q + i) * kHid + 16 * c + n] = gw2[c][i];
+    if (n < kIn)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[kW1 + (16 * w + 4 * q + i) * kIn + n] = gw1[i];
+    gb1 = sum_quarters(gb1);
+    gb2 = sum_quarters(gb2);
+    gw3 = sum_quarters(gw3);
+    if (q == 0) {
+        out[kB1 + u] = gb1;
+        out[kB2 + u] = gb2;
+        out[kW3 + u] = gw3;
+    }
+    gb3 = sum_quarter(gb3);
+    sq = sum_quarter(sq);
+    if (threadIdx.x == 0) {
+        out[kB3] = gb3;
+        out[kParams] = sq;
     }
 }
 
-// Per-sample deltas of the mean squared error L = (1/B) sum_s (y_s - t_s)^2.
-__global__ __launch_bounds__(64) void k_backward(const float* __restrict__ p, const float* __restrict__ h1,
-                                                 const float* __restrict__ h2, const float* __restrict__ y,
-                                                 const float* __restrict__ tn, int B, float* __restrict__ dy,
-                                                 float* __restrict__ d1, float* __restrict__ d2)
-{
-    __shared__ float sd2[kHid];
-    const int s = (int)blockIdx.x, t = (int)threadIdx.x;
-    const float g = 2.0f * (y[s] - tn[s]) / (float)B;
-    if (t == 0) dy[s] = g;
-    const float e2 = (h2[s * kHid + t] > 0.0f) ? g * p[kW3 + t] : 0.0f;
-    sd2[t] = e2;
-    d2[s * kHid + t] = e2;
-    __syncthreads();
-    float acc = 0.0f;
-    for (int u = 0; u < kHid; ++u) acc += p[kW2 + u * kHid + t] * sd2[u];
-    d1[s * kHid + t] = (h1[s * kHid + t] > 0.0f) ? acc : 0.0f;
-}
-
-// One thread per parameter: sum of its per-sample gradient terms in sample
-// order.  Thread kParams computes the loss.
-__global__ __launch_bounds__(256) void k_gradient(const float* __restrict__ xn, const float* __restrict__ h1,
-                                                  const float* __restrict__ h2, const float* __restrict__ d1,
-                                                  const float* __restrict__ d2, const float* __restrict__ dy,
-                                                  const float* __restrict__ y, const float* __restrict__ tn, int B,
-                                                  float* __restrict__ grad, float* __restrict__ loss_acc)
+// One thread per parameter: the partial sums of nparts blocks in order, after
+// those of the blocks before them in carry (with `carried`).  If more blocks
+// follow, the sum goes to carry; else either the gradient goes to `grad` (host
+// memory), or SGD with momentum updates the FP32 master weights and their BF16
+// copy.  The thread after the last parameter adds the loss of the minibatch to
+// *loss, or starts it (`start`).
+__global__ __launch_bounds__(64) void k_apply(const float* __restrict__ parts, int nparts, float* __restrict__ carry,
+                                              int carried, int more, int B, float* __restrict__ grad,
+                                              float* __restrict__ p, float* __restrict__ mom, float lr,
+                                              float momentum, __hip_bfloat16* __restrict__ wb,
+                                              float* __restrict__ loss, int start)
 {
     const int q = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (q > kParams) return;
-    float g = 0.0f;
-    if (q < kB1) {
-        const int u = q / kIn, k = q % kIn;
-        for (int s = 0; s < B; ++s) g += d1[s * kHid + u] * xn[s * kIn + k];
-    } else if (q < kW2) {
-        const int u = q - kB1;
-        for (int s = 0; s < B; ++s) g += d1[s * kHid + u];
-    } else if (q < kB2) {
-        const int u = (q - kW2) / kHid, v = (q - kW2) % kHid;
-        for (int s = 0; s < B; ++s) g += d2[s * kHid + u] * h1[s * kHid + v];
-    } else if (q < kW3) {
-        const int u = q - kB2;
-        for (int s = 0; s < B; ++s) g += d2[s * kHid + u];
-    } else if (q < kB3) {
-        const int u = q - kW3;
-        for (int s = 0; s < B; ++s) g += dy[s] * h2[s * kHid + u];
-    } else if (q == kB3) {
-        for (int s = 0; s < B; ++s) g += dy[s];
-    } else {
-        float l = 0.0f;
-        for (int s = 0; s < B; ++s) {
-            const float d = y[s] - tn[s];
-            l += d * d;
-        }
-        if (loss_acc) *loss_acc += l / (float)B;
+    const bool update = !grad && !more && q < kParams;
+    const float m0 = update ? mom[q] : 0.0f, p0 = update ? p[q] : 0.0f;
+    float g = carried ? carry[q] : 0.0f;
+#pragma unroll 8
+    for (int k = 0; k < nparts; ++k) g += parts[(size_t)k * kPartStride + q];
+    if (more) {
+        carry[q] = g;
         return;
     }
-    grad[q] = g;
-}
-
-// SGD with momentum on the FP32 master weights; refreshes the BF16 copy.
-__global__ void k_sgd(float* __restrict__ p, const float* __restrict__ grad, float* __restrict__ mom, float lr,
-                      float momentum, __hip_bfloat16* __restrict__ wb)
-{
-    const int q = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (q >= kParams) return;
-    const float m = momentum * mom[q] + grad[q];
+    if (q == kParams) {
+        const float l = g / (float)B;
+        *loss = start ? l : *loss + l;
+        return;
+    }
+    if (grad) {
+        grad[q] = g;
+        return;
+    }
+    const float m = momentum * m0 + g;
     mom[q] = m;
-    const float w = p[q] - lr * m;
-    p[q] = w;
-    wb[q] = __float2bfloat16(w);
+    const float v = p0 - lr * m;
+    p[q] = v;
+    wb[q] = __float2bfloat16(v);
 }
 
 __global__ void k_to_bf16(const float* __restrict__ p, __hip_bfloat16* __restrict__ wb)
@@ -168,21 +275,36 @@ __global__ __launch_bounds__(64) void k_infer(const float* __restrict__ x, const
     }
 }
 
-// Mean and standard deviation of each feature and of the target (FP64,
-// sequential over samples): one thread per variable.
-__global__ void k_fit_norm(const float* __restrict__ x, const float* __restrict__ t, int n, float* __restrict__ norm)
+// Mean and standard deviation of each feature and of the target (FP64): one
+// block per variable, its threads' strided sums added in a fixed tree.  (One
+// thread per variable over all samples took 0.34-0.66 ms at n = 4096.)
+constexpr int kNormThreads = 512;
+
+__global__ __launch_bounds__(kNormThreads) void k_fit_norm(const float* __restrict__ x, const float* __restrict__ t,
+                                                           int n, float* __restrict__ norm)
 {
-    const int v = (int)threadIdx.x;
-    if (v > kIn) return;
+    __shared__ double sh[2][kNormThreads];
+    const int v = (int)blockIdx.x, th = (int)threadIdx.x;
     double s = 0.0, s2 = 0.0;
-    for (int i = 0; i < n; ++i) {
-        const double z = (v < kIn) ? (double)x[i * kIn + v] : (double)t[i];
+    for (int i = th; i < n; i += kNormThreads) {
+        const double z = (v < kIn) ? (double)x[(size_t)i * kIn + v] : (double)t[i];
         s += z;
         s2 += z * z;
     }
-    const double mean = s / n;
-    double var = s2 / n - mean * mean;
-    double sd = var > 1e-24 ? sqrt(var) : 1.0;
+    sh[0][th] = s;
+    sh[1][th] = s2;
+    __syncthreads();
+    for (int off = kNormThreads / 2; off >= 1; off >>= 1) {
+        if (th < off) {
+            sh[0][th] += sh[0][th + off];
+            sh[1][th] += sh[1][th + off];
+        }
+        __syncthreads();
+    }
+    if (th != 0) return;
+    const double mean = sh[0][0] / n;
+    const double var = sh[1][0] / n - mean * mean;
+    const double sd = var > 1e-24 ? sqrt(var) : 1.0;
     if (v < kIn) {
         norm[v] = (float)mean;
         norm[kIn + v] = (float)sd;
@@ -195,8 +317,13 @@ __global__ void k_fit_norm(const float* __restrict__ x, const float* __restrict_
 constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
+// Workspace.  `work` holds the partial gradients of as many blocks as fit and,
+// behind them, the sample order of the coming minibatches (its size is that of
+// the activations and deltas of max_batch samples).  `grad` carries the sum
+// over blocks that did not fit at once, and holds the partials of a single one.
 struct Layout {
-    size_t params, grad, mom, wb, norm, xn, tn, h1, h2, d1, d2, dy, y, loss, idx, total;
+    size_t params, grad, mom, wb, norm, work, loss, idx, total;
+    size_t work_floats;
 };
 
 Layout layout(int max_batch)
@@ -214,19 +341,18 @@ Layout layout(int max_batch)
     l.mom = take(kParams * 4);
     l.wb = take(kParams * 2);
     l.norm = take(kNorm * 4);
-    l.xn = take(B * kIn * 4);
-    l.tn = take(B * 4);
-    l.h1 = take(B * kHid * 4);
-    l.h2 = take(B * kHid * 4);
-    l.d1 = take(B * kHid * 4);
-    l.d2 = take(B * kHid * 4);
-    l.dy = take(B * 4);
-    l.y = take(B * 4);
+    l.work = take(B * kIn * 4);
+    take(B * 4);
+    for (int k = 0; k < 4; ++k) take(B * kHid * 4);
+    take(B * 4);
+    take(B * 4);
+    l.work_floats = (o - l.work) / 4;
     l.loss = take(16);
     l.idx = take(B * 4);
     l.total = o;
     return l;
 }
+static_assert((kParams * 4 + kAlign - 1) / kAlign * kAlign >= kPartStride * sizeof(float), "grad holds one block");
 
 }  // namespace
 }  // namespace mlp
@@ -239,9 +365,16 @@ struct pa_mlp {
     hipStream_t stream;
     Layout lo;
     uint8_t* ws;
-    float *p, *grad, *mom, *norm, *xn, *tn, *h1, *h2, *d1, *d2, *dy, *y, *loss;
+    float *p, *grad, *mom, *norm, *work, *loss;
     __hip_bfloat16* wb;
     int32_t* idx;
+    float* h_out = nullptr;         // pinned: gradient and loss, written by k_apply
+    void* h_out_dev = nullptr;      // device view of h_out
+    int32_t* h_order[2] = {nullptr, nullptr};  // pinned: sample orders of two epochs in turn
+    size_t order_cap = 0;           // samples each of them holds
+    hipEvent_t order_read[2] = {nullptr, nullptr};  // the last upload from each
+    float* h_loss = nullptr;        // pinned: epoch losses
+    size_t loss_cap = 0;
     bool broken;
     std::string last_error;
 };
@@ -261,17 +394,63 @@ pa_status mfail(pa_mlp* m, hipError_t e, const char* what)
         if (e_ != hipSuccess) return mfail(m, e_, #expr);    \
     } while (0)
 
-// forward + backward + gradient for the B samples already normalised in xn/tn
-pa_status grad_pass(pa_mlp* m, int B, float* loss_acc)
+// Blocks that B samples are split over: a function of B alone, and with it the
+// order of every sum.  Up to two tiles stay in one block, whose partials need
+// no room in `work`; from 33 samples on `work` holds at least one block
+// (267 floats per sample of max_batch >= B).
+int blocks_of(int B) { return B <= 2 * kTile ? 1 : std::min((B + kTile - 1) / kTile, kMaxParts); }
+static_assert((2 * kTile + 1) * (4 * kHid + kIn + 3) > kPartStride, "work holds a block");
+
+// Blocks whose partials fit `work` at once.
+int blocks_at_once(const pa_mlp* m, int blocks)
 {
-    const hipStream_t s = m->stream;
-    hipLaunchKernelGGL(k_forward, dim3(B), dim3(64), 0, s, m->xn, m->p, m->h1, m->h2, m->y);
-    MCHK(hipGetLastError());
-    hipLaunchKernelGGL(k_backward, dim3(B), dim3(64), 0, s, m->p, m->h1, m->h2, m->y, m->tn, B, m->dy, m->d1, m->d2);
-    MCHK(hipGetLastError());
-    hipLaunchKernelGGL(k_gradient, dim3((kParams + 1 + 255) / 256), dim3(256), 0, s, m->xn, m->h1, m->h2, m->d1,
-                       m->d2, m->dy, m->y, m->tn, B, m->grad, loss_acc);
-    MCHK(hipGetLastError());
+    return blocks == 1 ? 1 : (int)std::min<size_t>((size_t)blocks, m->lo.work_floats / kPartStride);
+}
+
+// Gradient of the B samples idx[0..B) (0..B without idx) of d_x, d_t, and the
+// update or, with `grad`, the gradient itself.  Two launches where the
+// partials of all blocks fit the workspace (max_batch of about 1.13 B on, and
+// B <= 32), else two for every set that fits.
+pa_status grad_pass(pa_mlp* m, const float* d_x, const float* d_t, const int32_t* idx, int B, float* grad, float lr,
+                    float momentum, float* loss, bool start)
+{
+    const int blocks = blocks_of(B), set = blocks_at_once(m, blocks);
+    float* parts = blocks == 1 ? m->grad : m->work;
+    for (int b0 = 0; b0 < blocks; b0 += set) {
+        const int nb = std::min(set, blocks - b0);
+        hipLaunchKernelGGL(k_backprop, dim3(nb), dim3(256), 0, m->stream, d_x, d_t, idx, B, m->norm, m->p, b0, blocks,
+                           parts);
+        MCHK(hipGetLastError());
+        hipLaunchKernelGGL(k_apply, dim3((kParams + 1 + 63) / 64), dim3(64), 0, m->stream, parts, nb, m->grad,
+                           b0 > 0 ? 1 : 0, b0 + nb < blocks ? 1 : 0, B, grad, m->p, m->mom, lr, momentum, m->wb, loss,
+                           start ? 1 : 0);
+        MCHK(hipGetLastError());
+    }
+    return PA_OK;
+}
+
+// Pinned host memory for the sample orders of two epochs and the epoch losses.
+pa_status reserve(pa_mlp* m, size_t n, size_t epochs)
+{
+    if (n > m->order_cap) {
+        for (int k = 0; k < 2; ++k) {
+            if (m->h_order[k]) (void)hipHostFree(m->h_order[k]);
+            m->h_order[k] = nullptr;
+        }
+        m->order_cap = 0;
+        for (int k = 0; k < 2; ++k) {
+            if (hipHostMalloc((void**)&m->h_order[k], n * 4, hipHostMallocDefault) != hipSuccess) return PA_ENOMEM;
+            if (!m->order_read[k]) MCHK(hipEventCreateWithFlags(&m->order_read[k], hipEventDisableTiming));
+        }
+        m->order_cap = n;
+    }
+    if (epochs > m->loss_cap) {
+        if (m->h_loss) (void)hipHostFree(m->h_loss);
+        m->h_loss = nullptr;
+        m->loss_cap = 0;
+        if (hipHostMalloc((void**)&m->h_loss, epochs * 4, hipHostMallocDefault) != hipSuccess) return PA_ENOMEM;
+        m->loss_cap = epochs;
+    }
     return PA_OK;
 }
 
@@ -305,16 +484,18 @@ pa_status pa_mlp_create(int32_t max_batch, uint64_t seed, void* d_workspace, siz
     m->mom = (float*)(w + lo.mom);
     m->wb = (__hip_bfloat16*)(w + lo.wb);
     m->norm = (float*)(w + lo.norm);
-    m->xn = (float*)(w + lo.xn);
-    m->tn = (float*)(w + lo.tn);
-    m->h1 = (float*)(w + lo.h1);
-    m->h2 = (float*)(w + lo.h2);
-    m->d1 = (float*)(w + lo.d1);
-    m->d2 = (float*)(w + lo.d2);
-    m->dy = (float*)(w + lo.dy);
-    m->y = (float*)(w + lo.y);
+    m->work = (float*)(w + lo.work);
     m->loss = (float*)(w + lo.loss);
     m->idx = (int32_t*)(w + lo.idx);
+    if (hipHostMalloc((void**)&m->h_out, kPartStride * 4, hipHostMallocMapped) != hipSuccess) {
+        delete m;
+        return PA_ENOMEM;
+    }
+    if (hipHostGetDevicePointer(&m->h_out_dev, m->h_out, 0) != hipSuccess) {
+        (void)hipHostFree(m->h_out);
+        delete m;
+        return PA_EHIP;
+    }
     // He initialisation from the seed; biases zero; identity normalisation.
     std::vector<float> p(kParams, 0.0f), zero(kParams, 0.0f), norm(kNorm, 0.0f);
     std::mt19937_64 rng(seed);
@@ -362,7 +543,7 @@ pa_status pa_mlp_fit_norm(pa_mlp* m, const float* d_x, const float* d_t, int32_t
 {
     if (!m || !d_x || !d_t || n < 2) return PA_EINVAL;
     if (m->broken) return PA_ESTATE;
-    hipLaunchKernelGGL(k_fit_norm, dim3(1), dim3(64), 0, m->stream, d_x, d_t, n, m->norm);
+    hipLaunchKernelGGL(k_fit_norm, dim3(kIn + 1), dim3(kNormThreads), 0, m->stream, d_x, d_t, n, m->norm);
     MCHK(hipGetLastError());
     MCHK(hipStreamSynchronize(m->stream));
     return PA_OK;
@@ -383,15 +564,12 @@ pa_status pa_mlp_gradient(pa_mlp* m, const float* d_x, const float* d_t, int32_t
 {
     if (!m || !d_x || !d_t || n < 1 || n > m->max_batch) return PA_EINVAL;
     if (m->broken) return PA_ESTATE;
-    hipLaunchKernelGGL(k_gather_norm, dim3((n + 255) / 256), dim3(256), 0, m->stream, d_x, d_t, (const int32_t*)nullptr,
-                       n, m->norm, m->xn, m->tn);
-    MCHK(hipGetLastError());
-    MCHK(hipMemsetAsync(m->loss, 0, 4, m->stream));
-    const pa_status st = grad_pass(m, n, m->loss);
+    float* out = (float*)m->h_out_dev;
+    const pa_status st = grad_pass(m, d_x, d_t, nullptr, n, out, 0.0f, 0.0f, out + kParams, true);
     if (st != PA_OK) return st;
-    if (grad) MCHK(hipMemcpyAsync(grad, m->grad, kParams * 4, hipMemcpyDeviceToHost, m->stream));
-    if (loss) MCHK(hipMemcpyAsync(loss, m->loss, 4, hipMemcpyDeviceToHost, m->stream));
     MCHK(hipStreamSynchronize(m->stream));
+    if (grad) std::memcpy(grad, m->h_out, kParams * 4);
+    if (loss) *loss = m->h_out[kParams];
     return PA_OK;
 }
 
@@ -401,32 +579,45 @@ pa_status pa_mlp_train(pa_mlp* m, const float* d_x, const float* d_t, int32_t n,
     if (!m || !d_x || !d_t || n < 1 || batch < 1 || batch > m->max_batch || epochs < 0 || !(lr > 0.0f)) return PA_EINVAL;
     if (m->broken) return PA_ESTATE;
     std::mt19937_64 rng(seed);
-    std::vector<int32_t> perm((size_t)n);
     const int nb = n / batch;  // full minibatches only
     if (nb < 1) return PA_EINVAL;
-    for (int e = 0; e < epochs; ++e) {
-        for (int i = 0; i < n; ++i) perm[(size_t)i] = i;
-        std::shuffle(perm.begin(), perm.end(), rng);
-        MCHK(hipMemsetAsync(m->loss, 0, 4, m->stream));
-        for (int k = 0; k < nb; ++k) {
-            MCHK(hipMemcpyAsync(m->idx, perm.data() + (size_t)k * batch, (size_t)batch * 4, hipMemcpyHostToDevice,
-                                m->stream));
-            hipLaunchKernelGGL(k_gather_norm, dim3((batch + 255) / 256), dim3(256), 0, m->stream, d_x, d_t, m->idx,
-                               batch, m->norm, m->xn, m->tn);
-            MCHK(hipGetLastError());
-            const pa_status st = grad_pass(m, batch, m->loss);
-            if (st != PA_OK) return st;
-            hipLaunchKernelGGL(k_sgd, dim3((kParams + 255) / 256), dim3(256), 0, m->stream, m->p, m->grad, m->mom, lr,
-                               momentum, m->wb);
-            MCHK(hipGetLastError());
-            // the index buffer is reused by the next minibatch: wait for this one
-            MCHK(hipStreamSynchronize(m->stream));
-        }
-        float l = 0.0f;
-        MCHK(hipMemcpyAsync(&l, m->loss, 4, hipMemcpyDeviceToHost, m->stream));
-        MCHK(hipStreamSynchronize(m->stream));
-        if (epoch_loss) epoch_loss[e] = l / (float)nb;
+    const pa_status rs = reserve(m, (size_t)n, (size_t)epochs);
+    if (rs != PA_OK) return rs;
+    // device room for the sample order: behind the partial sums, or the index
+    // buffer of one minibatch
+    int32_t* order = m->idx;
+    size_t room = (size_t)m->max_batch;
+    const int blocks = blocks_of(batch);
+    const size_t used = blocks == 1 ? 0 : (size_t)blocks_at_once(m, blocks) * kPartStride;
+    if (m->lo.work_floats - used > room) {
+        order = (int32_t*)(m->work + used);
+        room = m->lo.work_floats - used;
     }
+    const int per_upload = (int)std::min<size_t>((size_t)nb, room / (size_t)batch);
+    // Everything of an epoch is queued without a wait: the order of epoch e
+    // comes from pinned buffer e mod 2, which is rewritten only after its
+    // last upload has been read (two epochs earlier).
+    for (int e = 0; e < epochs; ++e) {
+        int32_t* perm = m->h_order[e & 1];
+        if (e >= 2) MCHK(hipEventSynchronize(m->order_read[e & 1]));
+        for (int i = 0; i < n; ++i) perm[i] = i;
+        std::shuffle(perm, perm + n, rng);
+        for (int k = 0; k < nb; ++k) {
+            const int at = k % per_upload;
+            if (at == 0) {
+                const size_t count = (size_t)std::min(per_upload, nb - k) * (size_t)batch;
+                MCHK(hipMemcpyAsync(order, perm + (size_t)k * batch, count * 4, hipMemcpyHostToDevice, m->stream));
+            }
+            const pa_status st = grad_pass(m, d_x, d_t, order + (size_t)at * batch, batch, nullptr, lr, momentum,
+                                           m->loss, k == 0);
+            if (st != PA_OK) return st;
+        }
+        MCHK(hipEventRecord(m->order_read[e & 1], m->stream));
+        MCHK(hipMemcpyAsync(&m->h_loss[e], m->loss, 4, hipMemcpyDeviceToHost, m->stream));
+    }
+    MCHK(hipStreamSynchronize(m->stream));
+    if (epoch_loss)
+        for (int e = 0; e < epochs; ++e) epoch_loss[e] = m->h_loss[e] / (float)nb;
     return PA_OK;
 }
 
@@ -434,6 +625,13 @@ const char* pa_mlp_last_error(const pa_mlp* m) { return m ? m->last_error.c_str(
 
 pa_status pa_mlp_free(pa_mlp* m)
 {
+    if (!m) return PA_OK;
+    for (int k = 0; k < 2; ++k) {
+        if (m->h_order[k]) (void)hipHostFree(m->h_order[k]);
+        if (m->order_read[k]) (void)hipEventDestroy(m->order_read[k]);
+    }
+    if (m->h_loss) (void)hipHostFree(m->h_loss);
+    if (m->h_out) (void)hipHostFree(m->h_out);
     delete m;
     return PA_OK;
 }
