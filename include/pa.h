@@ -341,7 +341,8 @@ size_t pa_batch_workspace_bytes(const pa_params* runs, int32_t nruns);
 /* Start nruns runs at beta_0 = 0 (Sec. 2.1 step 1) and measure them once.
  * `hip_stream` may be NULL: the batch then creates its own stream (graph
  * capture needs a non-null stream).  The sweep's work-group shape (waves per
- * block, one per lattice size, store and update) is chosen by timing the
+ * block, one per launch: L <= 64 together, 128, 256, each with its store and
+ * update) is chosen by timing the
  * candidates 1, 2, 4 and 8 on the batch's spare buffers.  Errors: PA_EINVAL
  * (invalid run parameters or schedule, nruns < 1), PA_ENOMEM, PA_EHIP. */
 pa_status pa_batch_init(const pa_params* runs, const pa_schedule* sched, int32_t nruns, void* d_workspace,

@@ -7,8 +7,9 @@
 //           Eq. (resampling factors), Metropolis thresholds
 //   copy    one upload of every run's step descriptor and tables
 //   graph   counts -> per-run scan -> parent scatter -> replica copy -> sweep
-//           (one launch per lattice size and store) -> statistics -> one
-//           download of every run's statistics block and energy histogram
+//           (one launch for all register-path lattice sizes of a store, one per
+//           larger size) -> statistics, written to host memory by the last
+//           block of every run
 //   host    commit each run (ln Z += ln Q, observables of Eq. (observables))
 // The device part is captured once in a HIP graph and replayed every step.
 // Kernels read each run's step descriptor and its device-side population
@@ -16,8 +17,8 @@
 // would exceed its capacity or die out is flagged on the device; its copy and
 // sweep are skipped and its state stays at the last good step.
 //
-// Launch shapes of the sweep (waves per block) are chosen per (lattice size,
-// store) by timing the candidates on the batch's own spare buffers at start-up.
+// Launch shapes of the sweep (waves per block) are chosen per launch by timing
+// the candidates on the batch's own spare buffers at start-up.
 #include <algorithm>
 #include <atomic>
 #include <chrono>
@@ -62,6 +63,7 @@ struct RunDev {
     uint32_t key0, key1;  // Philox key: the run's seed
     uint32_t tag;         // 16 * run_id: counter word 3 without the stream number
     uint32_t qcap;        // tie-queue limit of the LDS-path sweeps (SweepArgs::qcap)
+    uint64_t host_off;    // the run's statistics block and histogram in the host's download area
 };
 
 struct StepDev {
@@ -153,13 +155,27 @@ __global__ __launch_bounds__(kBlock) void b_counts(const Item* __restrict__ item
     if (threadIdx.x == 0) rd.bsum[it.blk] = total;
 }
 
-// One block per run: exclusive scan of its block sums, total and status.
+// One block per run: its statistics cleared for this step's population, and the
+// exclusive scan of its block sums, total and status.
 __global__ __launch_bounds__(1024) void b_scan(const RunDev* __restrict__ runs, const StepDev* __restrict__ steps,
                                                ResultDev* __restrict__ res)
 {
     __shared__ uint32_t part[1024];
     const StepDev st = steps[blockIdx.x];
-    if (!st.active || !st.resample) return;
+    if (!st.active) return;
+    {
+        const RunDev& rd = runs[blockIdx.x];
+        if (threadIdx.x == 0) {
+            DevStats* s = rd.stats;
+            s->emin = 0x7FFFFFFF;
+            s->emax = (int32_t)0x80000000;
+            s->r_new = 0;
+            s->done = 0;
+            s->sumE = s->sumE2 = s->sumAbsM = s->sumM2 = s->sumM4_lo = s->sumM4_hi = 0;
+        }
+        for (int b = (int)threadIdx.x; b < rd.nbins; b += 1024) rd.hist[b] = 0;
+    }
+    if (!st.resample) return;
     uint32_t* bsum = runs[blockIdx.x].bsum;
     const int nblk = (st.n_parent + kBlock - 1) / kBlock;
     const int t = (int)threadIdx.x;
@@ -228,9 +244,18 @@ __global__ __launch_bounds__(kBlock) void b_copy(const Item* __restrict__ items,
 }
 
 // Item blk covers waves [blk * wpb, (blk + 1) * wpb) of the run (wpb = blockDim.x / 64).
+// L = kSmall: the register-path lattice sizes together, each block that of its
+// run, so that the short launches of small lattices fill the GPU beside the
+// larger ones instead of following them (12 runs of L = 16, 32 and 64: 47 us of
+// separate launches per step beside 137 for L = 64 alone; as branches of the
+// graph they overlap too, but every node of a branching graph starts 10 us
+// after the one before).
+constexpr int kSmall = 0;
+
 template <int L, bool INT8, int U>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sweep_min_waves<L>(), 8))) void b_sweep(const Item* __restrict__ items, const RunDev* __restrict__ runs,
-                                               const StepDev* __restrict__ steps, const ResultDev* __restrict__ res)
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sweep_min_waves<L>(), 8))) void b_sweep(
+    const Item* __restrict__ items, const RunDev* __restrict__ runs, const StepDev* __restrict__ steps,
+    const ResultDev* __restrict__ res)
 {
     extern __shared__ __align__(16) uint32_t lds_dyn[];
     const Item it = items[blockIdx.x];
@@ -265,86 +290,48 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sweep_min_w
     a.t4l = st.t4l;
     a.init = st.init;
     const int wpb = (int)(blockDim.x >> 6);
-    sweep_waves<L, INT8, U == pa::kHeatbath, U == pa::kLcg>(a, it.blk * wpb, wpb, lds_dyn);
-}
-
-__global__ __launch_bounds__(kBlock) void b_stats_reset(const RunDev* __restrict__ runs,
-                                                        const StepDev* __restrict__ steps)
-{
-    const StepDev st = steps[blockIdx.x];
-    if (!st.active) return;
-    const RunDev& rd = runs[blockIdx.x];
-    if (threadIdx.x == 0) {
-        DevStats* s = rd.stats;
-        s->emin = 0x7FFFFFFF;
-        s->emax = (int32_t)0x80000000;
-        s->r_new = 0;
-        s->done = 0;
-        s->sumE = s->sumE2 = s->sumAbsM = s->sumM2 = s->sumM4_lo = s->sumM4_hi = 0;
+    constexpr bool HB = U == pa::kHeatbath, LCG = U == pa::kLcg;
+    if constexpr (L == kSmall) {
+        switch (rd.L) {  // uniform
+        case 16: sweep_waves<16, INT8, HB, LCG>(a, it.blk * wpb, wpb, lds_dyn); break;
+        case 32: sweep_waves<32, INT8, HB, LCG>(a, it.blk * wpb, wpb, lds_dyn); break;
+        default: sweep_waves<64, INT8, HB, LCG>(a, it.blk * wpb, wpb, lds_dyn); break;
+        }
+    } else {
+        sweep_waves<L, INT8, HB, LCG>(a, it.blk * wpb, wpb, lds_dyn);
     }
-    for (int b = (int)threadIdx.x; b < rd.nbins; b += kBlock) rd.hist[b] = 0;
 }
 
-__global__ __launch_bounds__(kBlock) void b_stats(const Item* __restrict__ items, const RunDev* __restrict__ runs,
-                                                  const StepDev* __restrict__ steps, const ResultDev* __restrict__ res)
-{
-    const Item it = items[blockIdx.x];
-    const StepDev st = steps[it.run];
-    if (!st.active) return;
-    int buf, n;
-    const bool ok = post_resample(st, res[it.run], &buf, &n);
-    if (it.blk * kBlock >= n) return;
-    const RunDev& rd = runs[it.run];
-    stats_block(rd.E[buf], rd.M[buf], n, rd.N, it.blk * kBlock, rd.hist, rd.nbins, st.record && ok, rd.mhr,
-                &rd.parts[it.blk]);
-}
-
-// One block per run: sums the partials of b_stats.
-__global__ __launch_bounds__(kBlock) void b_stats_final(const RunDev* __restrict__ runs,
-                                                        const StepDev* __restrict__ steps,
-                                                        const ResultDev* __restrict__ res)
-{
-    const StepDev st = steps[blockIdx.x];
-    if (!st.active) return;
-    int buf, n;
-    post_resample(st, res[blockIdx.x], &buf, &n);
-    const RunDev& rd = runs[blockIdx.x];
-    stats_final(rd.parts, (n + kBlock - 1) / kBlock, rd.stats);
-}
-
-// One block of 64 threads per run: energy moments of the measured population
-// from its histogram (FP64, fixed-order reduction), the proposer's features,
-// and -- when a model is loaded -- the BF16 proposal for the next step:
+// Energy moments of a measured population from its histogram (FP64, fixed-order
+// reduction over the first 64 threads), the proposer's features, and -- when a
+// model is loaded -- the BF16 proposal for the next step:
 //   x = (e/N, ln sigma_E, skew, excess kurtosis, beta, ln L, ln R, ln last step).
-__global__ __launch_bounds__(64) void b_features(const RunDev* __restrict__ runs, const StepDev* __restrict__ steps,
-                                                 const ResultDev* __restrict__ res, const ModelDev* __restrict__ model,
-                                                 FeatDev* __restrict__ feats)
+// Called by every thread of the block.
+__device__ __forceinline__ void run_features(const RunDev& rd, const StepDev& st, int n, bool ok,
+                                             const ModelDev* __restrict__ model, FeatDev* __restrict__ out)
 {
     __shared__ double red[3][64];
     __shared__ float h[pa::mlp::kHid];
     __shared__ float xs[8];
-    const StepDev st = steps[blockIdx.x];
-    if (!st.active) return;
-    int buf, n;
-    const bool ok = post_resample(st, res[blockIdx.x], &buf, &n);
-    const RunDev& rd = runs[blockIdx.x];
     const DevStats* sp = rd.stats;
     const int t = (int)threadIdx.x;
     const double mean = (double)(int64_t)sp->sumE / (double)n;
-    const int bmin = (sp->emin + 2 * rd.N) / 4, bmax = (sp->emax + 2 * rd.N) / 4;
-    double a2 = 0.0, a3 = 0.0, a4 = 0.0;
-    for (int b = bmin + t; b <= bmax; b += 64) {
-        const uint32_t c = rd.hist[b];
-        if (c == 0) continue;
-        const double d = (double)(4 * b - 2 * rd.N) - mean;
-        const double d2 = d * d;
-        a2 += c * d2;
-        a3 += c * d2 * d;
-        a4 += c * d2 * d2;
+    if (t < 64) {
+        const int bmin = (sp->emin + 2 * rd.N) / 4, bmax = (sp->emax + 2 * rd.N) / 4;
+        double a2 = 0.0, a3 = 0.0, a4 = 0.0;
+        for (int b = bmin + t; b <= bmax; b += 64) {
+            const uint32_t c = rd.hist[b];
+            if (c == 0) continue;
+            const double d = (double)(4 * b - 2 * rd.N) - mean;
+            const double d2 = d * d;
+            a2 += c * d2;
+            a3 += c * d2 * d;
+            a4 += c * d2 * d2;
+        }
+        red[0][t] = a2;
+        red[1][t] = a3;
+        red[2][t] = a4;
     }
-    red[0][t] = a2;
-    red[1][t] = a3;
-    red[2][t] = a4;
     __syncthreads();
     for (int off = 32; off >= 1; off >>= 1) {
         if (t < off) {
@@ -357,7 +344,6 @@ __global__ __launch_bounds__(64) void b_features(const RunDev* __restrict__ runs
     const double var = red[0][0] / n;
     const bool valid = ok && var > 0.0 && st.last_dbeta > 0.0;
     if (t == 0) {
-        FeatDev& f = feats[blockIdx.x];
         const double sd = var > 0.0 ? sqrt(var) : 1.0;
         xs[0] = (float)(mean / rd.N);
         xs[1] = (float)log(sd);
@@ -367,15 +353,57 @@ __global__ __launch_bounds__(64) void b_features(const RunDev* __restrict__ runs
         xs[5] = (float)log((double)rd.L);
         xs[6] = (float)log((double)rd.R);
         xs[7] = st.last_dbeta > 0.0 ? (float)log(st.last_dbeta) : 0.0f;
-        for (int k = 0; k < 8; ++k) f.x[k] = xs[k];
-        f.valid = valid ? 1 : 0;
-        f.prop = 0.0f;
+        for (int k = 0; k < 8; ++k) out->x[k] = xs[k];
+        out->valid = valid ? 1 : 0;
+        out->prop = 0.0f;
     }
     __syncthreads();
-    if (valid && model->set) {
+    if (valid && model->set) {  // uniform
         const float y = pa::mlp::forward_bf16(xs, model->wb, model->norm, h, t);
-        if (t == 0) feats[blockIdx.x].prop = y;
+        if (t == 0) out->prop = y;
     }
+}
+
+// Statistics of every run's population, one block per chunk of kBlock replicas.
+// The block of a run that finishes last (counted in its statistics block) sums
+// the partials, computes the features, and writes the run's results, features,
+// statistics block and the occupied window of its histogram to the host's
+// download area, so that no further kernel and no copy follows.  (Separate
+// kernels for the clearing, the sum and the features, and the copy of every
+// histogram, took 24 us per step of 12 small runs; this one takes 15.)
+__global__ __launch_bounds__(kBlock) void b_stats(const Item* __restrict__ items, const RunDev* __restrict__ runs,
+                                                  const StepDev* __restrict__ steps, const ResultDev* __restrict__ res,
+                                                  const ModelDev* __restrict__ model, uint8_t* host, size_t feats_off)
+{
+    __shared__ uint32_t last;
+    const Item it = items[blockIdx.x];
+    const StepDev st = steps[it.run];
+    if (!st.active) return;
+    const ResultDev rs = res[it.run];
+    int buf, n;
+    const bool ok = post_resample(st, rs, &buf, &n);
+    if (it.blk * kBlock >= n) return;
+    const RunDev& rd = runs[it.run];
+    stats_block(rd.E[buf], rd.M[buf], n, rd.N, it.blk * kBlock, rd.hist, rd.nbins, st.record && ok, rd.mhr,
+                &rd.parts[it.blk]);
+    const int nparts = (n + kBlock - 1) / kBlock;
+    __threadfence();  // this block's partials and histogram updates, device-wide
+    __syncthreads();
+    if (threadIdx.x == 0) last = (atomicAdd(&rd.stats->done, 1u) == (uint32_t)(nparts - 1)) ? 1u : 0u;
+    __syncthreads();
+    if (!last) return;  // uniform per block
+    __threadfence();    // every other block's updates are visible to this one
+    stats_final(rd.parts, nparts, rd.stats);
+    __syncthreads();  // *rd.stats written by thread 0 is visible to the block
+    const uint32_t* sw = reinterpret_cast<const uint32_t*>(rd.stats);
+    uint32_t* hs = reinterpret_cast<uint32_t*>(host + rd.host_off);
+    if (threadIdx.x < sizeof(DevStats) / 4) hs[threadIdx.x] = sw[threadIdx.x];
+    if (threadIdx.x == 0) reinterpret_cast<ResultDev*>(host)[it.run] = rs;
+    const int32_t emin = rd.stats->emin, emax = rd.stats->emax;
+    if (emin >= -2 * rd.N && emax <= 2 * rd.N)
+        for (int b = (emin + 2 * rd.N) / 4 + (int)threadIdx.x; b <= (emax + 2 * rd.N) / 4; b += kBlock)
+            hs[sizeof(DevStats) / 4 + b] = rd.hist[b];
+    run_features(rd, st, n, ok, model, reinterpret_cast<FeatDev*>(host + feats_off) + it.run);
 }
 
 __global__ void b_fill_u32(uint32_t* p, uint32_t value, size_t n)
@@ -436,7 +464,7 @@ struct BatchLayout {
 };
 
 struct Group {
-    int L, layout;
+    int L, layout;  // L: kSmall for the register-path sizes together
     int upd;  // update rule of its runs (pa::Update)
     int wpb;
     size_t item_off, n_items;
@@ -449,6 +477,14 @@ int update_of(const pa_params& p)
     if (p.flags & PA_FLAG_HEATBATH) return pa::kHeatbath;
     if (p.flags & PA_FLAG_LCG) return pa::kLcg;
     return pa::kMetropolis;
+}
+
+// Sweep group of a lattice size, and whether a run belongs to a group.
+int group_size(int L) { return L <= 64 ? kSmall : L; }
+
+bool in_group(const pa_params& p, const Group& g)
+{
+    return group_size(p.L) == g.L && p.layout == g.layout && update_of(p) == g.upd;
 }
 
 bool make_batch_layout(const pa_params* runs, int nruns, BatchLayout* bl)
@@ -640,7 +676,8 @@ struct pa_batch {
     size_t parent_off = 0, n_parent_items = 0, copy_off = 0, n_copy_items = 0;
     std::vector<Group> groups;
     uint8_t* h_steps = nullptr;     // pinned: step descriptors + tables
-    uint8_t* h_download = nullptr;  // pinned: results + statistics
+    uint8_t* h_download = nullptr;  // pinned: results, features and statistics, written by b_stats
+    void* h_download_dev = nullptr; // device view of h_download
     hipGraph_t graph = nullptr;        // one step, with the separate replica copy (b_copy)
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph_nocopy = nullptr; // the same step without it: every resampled run sweeps and
@@ -670,8 +707,8 @@ template <int L, bool INT8, int U>
 hipError_t launch_group_t(const Item* items, size_t n, int wpb, const RunDev* rd, const StepDev* st,
                           const ResultDev* rs, hipStream_t s)
 {
-    using Gm = pa::dev::Geo<L>;
-    const size_t lds = (size_t)Gm::lds_words(wpb) * 4;
+    size_t lds = 0;
+    if constexpr (L != kSmall) lds = (size_t)pa::dev::Geo<L>::lds_words(wpb) * 4;
     if (n == 0) return hipSuccess;
     hipLaunchKernelGGL((b_sweep<L, INT8, U>), dim3((unsigned)n), dim3(64 * wpb), lds, s, items, rd, st, rs);
     return hipGetLastError();
@@ -702,9 +739,7 @@ hipError_t launch_group(const Group& g, const Item* items, size_t n, int wpb, co
 {
     const bool i8 = g.layout == PA_SPIN_INT8;
     switch (g.L) {
-    case 16: return launch_group_l<16>(i8, g.upd, items, n, wpb, rd, st, rs, s);
-    case 32: return launch_group_l<32>(i8, g.upd, items, n, wpb, rd, st, rs, s);
-    case 64: return launch_group_l<64>(i8, g.upd, items, n, wpb, rd, st, rs, s);
+    case kSmall: return launch_group_l<kSmall>(i8, g.upd, items, n, wpb, rd, st, rs, s);
     case 128: return launch_group_l<128>(i8, g.upd, items, n, wpb, rd, st, rs, s);
     case 256: return launch_group_l<256>(i8, g.upd, items, n, wpb, rd, st, rs, s);
     default: return hipErrorInvalidValue;
@@ -726,26 +761,26 @@ int reps_per_wave(int L)
 size_t sweep_lds_bytes(int L, int wpb)
 {
     switch (L) {
-    case 16: return (size_t)pa::dev::Geo<16>::lds_words(wpb) * 4;
-    case 32: return (size_t)pa::dev::Geo<32>::lds_words(wpb) * 4;
-    case 64: return (size_t)pa::dev::Geo<64>::lds_words(wpb) * 4;
+    case kSmall: return 0;
     case 128: return (size_t)pa::dev::Geo<128>::lds_words(wpb) * 4;
     default: return (size_t)pa::dev::Geo<256>::lds_words(wpb) * 4;
     }
 }
 
 // Sweep items of one group for a given number of waves per block.
+// The group's blocks, those of the larger lattices (the longer ones) first.
 std::vector<Item> sweep_items(const pa_batch* b, const Group& g, int wpb)
 {
     std::vector<Item> it;
-    const int per_block = reps_per_wave(g.L) * wpb;
-    for (int r = 0; r < b->nruns; ++r) {
-        const pa_params& p = b->runs[(size_t)r].p;
-        if (p.L != g.L || p.layout != g.layout || update_of(p) != g.upd) continue;
-        const int cap = b->lo.runs[(size_t)r].capacity;
-        const int nb = (cap + per_block - 1) / per_block;
-        for (int k = 0; k < nb; ++k) it.push_back(Item{r, k});
-    }
+    for (int L = 256; L >= 16; L >>= 1)
+        for (int r = 0; r < b->nruns; ++r) {
+            const pa_params& p = b->runs[(size_t)r].p;
+            if (p.L != L || !in_group(p, g)) continue;
+            const int per_block = reps_per_wave(L) * wpb;
+            const int cap = b->lo.runs[(size_t)r].capacity;
+            const int nb = (cap + per_block - 1) / per_block;
+            for (int k = 0; k < nb; ++k) it.push_back(Item{r, k});
+        }
     return it;
 }
 
@@ -772,18 +807,10 @@ pa_status enqueue_step(pa_batch* b, bool with_copy)
     }
     for (const Group& g : b->groups)
         BCHK(launch_group(g, items + g.item_off, g.n_items, g.wpb, b->d_rundev, b->d_steps, b->d_results, s));
-    hipLaunchKernelGGL(b_stats_reset, dim3((unsigned)b->nruns), dim3(kBlock), 0, s, b->d_rundev, b->d_steps);
-    BCHK(hipGetLastError());
     hipLaunchKernelGGL(b_stats, dim3((unsigned)b->n_parent_items), dim3(kBlock), 0, s, items + b->parent_off,
-                       b->d_rundev, b->d_steps, b->d_results);
+                       b->d_rundev, b->d_steps, b->d_results, b->d_model, (uint8_t*)b->h_download_dev,
+                       (size_t)(b->lo.feats - b->lo.download));
     BCHK(hipGetLastError());
-    hipLaunchKernelGGL(b_stats_final, dim3((unsigned)b->nruns), dim3(kBlock), 0, s, b->d_rundev, b->d_steps,
-                       b->d_results);
-    BCHK(hipGetLastError());
-    hipLaunchKernelGGL(b_features, dim3((unsigned)b->nruns), dim3(64), 0, s, b->d_rundev, b->d_steps, b->d_results,
-                       b->d_model, b->d_feats);
-    BCHK(hipGetLastError());
-    BCHK(hipMemcpyAsync(b->h_download, b->d_download, b->lo.download_bytes, hipMemcpyDeviceToHost, s));
     return PA_OK;
 }
 
@@ -991,11 +1018,14 @@ static pa_status batch_init(const pa_params* runs, const pa_schedule* sched, int
         d.key1 = (uint32_t)(h.p.seed >> 32);
         d.tag = h.p.run_id << 4;
         d.qcap = 0xFFFFFFFFu;
+        d.host_off = rl.stats_off;
     }
     if (hipHostMalloc((void**)&b->h_steps, bl.steps_bytes, hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void**)&b->h_download, bl.download_bytes, hipHostMallocDefault) != hipSuccess)
+        hipHostMalloc((void**)&b->h_download, bl.download_bytes, hipHostMallocMapped) != hipSuccess)
         return PA_ENOMEM;
+    BCHK(hipHostGetDevicePointer(&b->h_download_dev, b->h_download, 0));
     std::memset(b->h_steps, 0, bl.steps_bytes);
+    std::memset(b->h_download, 0, bl.download_bytes);
     {
         ModelDev md;
         std::memset(&md, 0, sizeof(md));
@@ -1025,13 +1055,13 @@ static pa_status batch_init(const pa_params* runs, const pa_schedule* sched, int
         for (size_t k = 0; k < n; ++k) items.push_back(Item{r, (int32_t)k});
     }
     b->n_copy_items = items.size() - b->copy_off;
-    // sweep groups, one per (L, store, update)
+    // sweep groups, one per (lattice sizes of one launch, store, update)
     std::map<std::tuple<int, int, int>, int> seen;
     for (int r = 0; r < nruns; ++r) {
-        const auto key = std::make_tuple(runs[r].L, runs[r].layout, update_of(runs[r]));
+        const auto key = std::make_tuple(group_size(runs[r].L), runs[r].layout, update_of(runs[r]));
         if (!seen.count(key)) {
             seen[key] = (int)b->groups.size();
-            b->groups.push_back(Group{runs[r].L, runs[r].layout, update_of(runs[r]), 1, 0, 0});
+            b->groups.push_back(Group{group_size(runs[r].L), runs[r].layout, update_of(runs[r]), 1, 0, 0});
         }
     }
     b->pool = new (std::nothrow) Pool((int)std::min<unsigned>(16u, std::max(1u, std::thread::hardware_concurrency())));
@@ -1332,7 +1362,7 @@ pa_status pa_batch_waves_per_block(const pa_batch* b, int32_t run, int32_t* wpb)
     if (!b || !wpb || run < 0 || run >= b->nruns) return PA_EINVAL;
     const pa_params& p = b->runs[(size_t)run].p;
     for (const Group& g : b->groups)
-        if (g.L == p.L && g.layout == p.layout && g.upd == update_of(p)) {
+        if (in_group(p, g)) {
             *wpb = g.wpb;
             return PA_OK;
         }
@@ -1374,25 +1404,26 @@ pa_status pa_batch_free(pa_batch* b)
 
 namespace {
 
-// Picks waves per block for every (L, store) group by timing the sweep on the
+// Picks waves per block for every sweep group by timing the sweep on the
 // spare half of each run's ping-pong store: the spare buffers are overwritten
 // by the first resampling, so tuning leaves no trace in the runs.  The timed
 // launches draw a fresh state and do a few sweeps at beta = 0.44.
 // Waves per block chosen by autotune, kept for the life of the process per
-// (device architecture, L, store, total replicas of the group rounded up to a
-// power of two): later batches of the same shape skip the timed search.
+// (device architecture, lattice sizes, store, update, waves of the group's
+// populations rounded up to a power of two): later batches of the same shape
+// skip the timed search.
 struct TuneKey {
     std::string arch;
     int L, layout;
     int upd;
-    int64_t reps;
+    int64_t waves;
     bool operator<(const TuneKey& o) const
     {
         if (arch != o.arch) return arch < o.arch;
         if (L != o.L) return L < o.L;
         if (layout != o.layout) return layout < o.layout;
         if (upd != o.upd) return upd < o.upd;
-        return reps < o.reps;
+        return waves < o.waves;
     }
 };
 std::mutex g_tune_mu;
@@ -1419,13 +1450,13 @@ pa_status autotune(pa_batch* b)
             g.wpb = w;
             continue;
         }
-        int64_t reps = 0;
+        int64_t waves = 0;
         for (int r = 0; r < b->nruns; ++r) {
             const RunHost& h = b->runs[(size_t)r];
-            if (h.p.L == g.L && h.p.layout == g.layout && update_of(h.p) == g.upd) reps += h.p.R;
+            if (in_group(h.p, g)) waves += (h.p.R + reps_per_wave(h.p.L) - 1) / reps_per_wave(h.p.L);
         }
         int64_t bucket = 1;
-        while (bucket < reps) bucket <<= 1;
+        while (bucket < waves) bucket <<= 1;
         const TuneKey key{arch, g.L, g.layout, g.upd, bucket};
         {
             std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -1439,7 +1470,7 @@ pa_status autotune(pa_batch* b)
             StepDev& d = sd[r];
             std::memset(&d, 0, sizeof(d));
             const RunHost& h = b->runs[(size_t)r];
-            if (h.p.L != g.L || h.p.layout != g.layout || update_of(h.p) != g.upd) continue;
+            if (!in_group(h.p, g)) continue;
             d.active = 1;
             d.init = 1;
             d.cur = 1;  // spare buffer

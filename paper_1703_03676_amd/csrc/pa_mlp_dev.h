@@ -28,27 +28,33 @@ static_assert(kParams == 4801, "parameter count");
 // weights and activations in BF16 and accumulates in FP32.
 __device__ __forceinline__ float bf16r(float x) { return __bfloat162float(__float2bfloat16(x)); }
 
-// Forward pass of one sample by the 64 threads t = 0..63 of a block (t is the
-// hidden unit).  x: raw features (normalised here); wb: BF16 parameters;
-// norm: normalisation constants; h: 64 floats of shared scratch.  Returns the
-// de-normalised output in thread 0.
+// Forward pass of one sample by the threads t = 0..63 of a block (t is the
+// hidden unit); further threads only take part in the barriers.  x: raw
+// features (normalised here); wb: BF16 parameters; norm: normalisation
+// constants; h: 64 floats of shared scratch.  Returns the de-normalised output
+// in thread 0.
 __device__ __forceinline__ float forward_bf16(const float* x, const __hip_bfloat16* wb, const float* norm, float* h,
                                               int t)
 {
-    float xn[kIn];
+    const bool unit = t < kHid;
+    if (unit) {
+        float xn[kIn];
 #pragma unroll
-    for (int k = 0; k < kIn; ++k) xn[k] = bf16r((x[k] - norm[k]) / norm[kIn + k]);
-    float a = __bfloat162float(wb[kB1 + t]);
+        for (int k = 0; k < kIn; ++k) xn[k] = bf16r((x[k] - norm[k]) / norm[kIn + k]);
+        float a = __bfloat162float(wb[kB1 + t]);
 #pragma unroll
-    for (int k = 0; k < kIn; ++k) a += __bfloat162float(wb[kW1 + t * kIn + k]) * xn[k];
-    const float h1 = bf16r(a > 0.0f ? a : 0.0f);
-    h[t] = h1;
+        for (int k = 0; k < kIn; ++k) a += __bfloat162float(wb[kW1 + t * kIn + k]) * xn[k];
+        h[t] = bf16r(a > 0.0f ? a : 0.0f);
+    }
     __syncthreads();
-    float a2 = __bfloat162float(wb[kB2 + t]);
-    for (int v = 0; v < kHid; ++v) a2 += __bfloat162float(wb[kW2 + t * kHid + v]) * h[v];
-    const float h2 = bf16r(a2 > 0.0f ? a2 : 0.0f);
+    float h2 = 0.0f;
+    if (unit) {
+        float a2 = __bfloat162float(wb[kB2 + t]);
+        for (int v = 0; v < kHid; ++v) a2 += __bfloat162float(wb[kW2 + t * kHid + v]) * h[v];
+        h2 = bf16r(a2 > 0.0f ? a2 : 0.0f);
+    }
     __syncthreads();
-    h[t] = __bfloat162float(wb[kW3 + t]) * h2;
+    if (unit) h[t] = __bfloat162float(wb[kW3 + t]) * h2;
     __syncthreads();
     float y = 0.0f;
     if (t == 0) {
