@@ -1127,46 +1127,20 @@ pa_status pa_batch_step(pa_batch* b, int32_t* n_active)
     if (b->broken) return PA_ESTATE;
     StepDev* sd = host_steps(b);
     uint32_t* tb = host_tables(b);
-    // phase 1 (per run): next beta
-    b->pool->parallel_for(b->nruns, [&](int r) {
-        RunHost& h = b->runs[(size_t)r];
-        h.stepping = false;
-        if (h.finished || h.status != PA_OK || h.sched.mode == PA_STEP_FOLLOW) return;
-        const host::Hist hw = host::hist_window(h.h_hist, h.h_stats, h.p.L * h.p.L);
-        double bn = 0.0;
-        const auto t0 = std::chrono::steady_clock::now();
-        const bool ok = choose_beta(h, hw, b->model_set, &bn);
-        h.choose_s += std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
-        if (!ok) return;
-        h.beta_next = bn;
-        h.stepping = true;
-    });
-    // followers take their leader's temperature of this step
-    for (int r = 0; r < b->nruns; ++r) {
-        RunHost& h = b->runs[(size_t)r];
-        if (h.sched.mode != PA_STEP_FOLLOW || h.finished || h.status != PA_OK) continue;
-        const RunHost& l = b->runs[(size_t)h.sched.leader];
-        if (l.stepping && l.step == h.step) {
-            h.beta_next = l.beta_next;
-            h.stepping = true;
-        } else if (l.status != PA_OK || l.step != h.step) {
-            h.status = PA_ESTATE;  // the leader has stopped (or fell behind on an error)
-        }
-    }
-    // phase 2: pack the table windows
+    // place of every run's tables: its occupied energy window, known before its
+    // temperature
     std::vector<uint32_t> toff((size_t)b->nruns, 0u);
     uint32_t o = 0;
-    int any = 0;
     for (int r = 0; r < b->nruns; ++r) {
-        const RunHost& h = b->runs[(size_t)r];
-        if (!h.stepping) continue;
-        ++any;
+        RunHost& h = b->runs[(size_t)r];
+        h.stepping = false;
+        if (h.finished || h.status != PA_OK) continue;
         toff[(size_t)r] = o;
         const int bmin = (h.h_stats.emin + 2 * h.p.L * h.p.L) / 4, bmax = (h.h_stats.emax + 2 * h.p.L * h.p.L) / 4;
         o += 2u * (uint32_t)(bmax - bmin + 1);
     }
-    // phase 3 (per run): tables of Eq. (resampling factors) and the step descriptor
-    b->pool->parallel_for(b->nruns, [&](int r) {
+    // tables of Eq. (resampling factors) and the step descriptor of a run
+    const auto fill_step = [&](int r) {
         RunHost& h = b->runs[(size_t)r];
         StepDev& d = sd[r];
         std::memset(&d, 0, sizeof(d));
@@ -1188,7 +1162,48 @@ pa_status pa_batch_step(pa_batch* b, int32_t* n_active)
         d.tbl_off = toff[(size_t)r];
         d.beta = bn;
         d.last_dbeta = bn - h.beta;
+    };
+    // per run: next beta, then its tables.  One pass of the thread pool, whose
+    // wake-up and join cost about 40 us each: the temperatures, the tables and
+    // the commit in passes of their own took 147 us per step of 12 runs.
+    b->pool->parallel_for(b->nruns, [&](int r) {
+        RunHost& h = b->runs[(size_t)r];
+        if (h.sched.mode == PA_STEP_FOLLOW) return;
+        if (!h.finished && h.status == PA_OK) {
+            const host::Hist hw = host::hist_window(h.h_hist, h.h_stats, h.p.L * h.p.L);
+            double bn = 0.0;
+            const auto t0 = std::chrono::steady_clock::now();
+            const bool ok = choose_beta(h, hw, b->model_set, &bn);
+            h.choose_s += std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+            if (ok) {
+                h.beta_next = bn;
+                h.stepping = true;
+            }
+        }
+        fill_step(r);
     });
+    // followers take their leader's temperature of this step
+    int any = 0, followers = 0;
+    for (int r = 0; r < b->nruns; ++r) {
+        RunHost& h = b->runs[(size_t)r];
+        if (h.sched.mode == PA_STEP_FOLLOW) {
+            ++followers;
+            if (!h.finished && h.status == PA_OK) {
+                const RunHost& l = b->runs[(size_t)h.sched.leader];
+                if (l.stepping && l.step == h.step) {
+                    h.beta_next = l.beta_next;
+                    h.stepping = true;
+                } else if (l.status != PA_OK || l.step != h.step) {
+                    h.status = PA_ESTATE;  // the leader has stopped (or fell behind on an error)
+                }
+            }
+        }
+        any += h.stepping ? 1 : 0;
+    }
+    if (followers)
+        b->pool->parallel_for(b->nruns, [&](int r) {
+            if (b->runs[(size_t)r].sched.mode == PA_STEP_FOLLOW) fill_step(r);
+        });
     if (any) {
         bool need_copy = false;
         for (int r = 0; r < b->nruns; ++r)
@@ -1196,14 +1211,14 @@ pa_status pa_batch_step(pa_batch* b, int32_t* n_active)
         const pa_status st = replay(b, (b->lo.tables - b->lo.steps) + (size_t)o * 4, need_copy);
         if (st != PA_OK) return st;
         const ResultDev* res = reinterpret_cast<const ResultDev*>(b->h_download);
-        b->pool->parallel_for(b->nruns, [&](int r) {
+        for (int r = 0; r < b->nruns; ++r) {
             RunHost& h = b->runs[(size_t)r];
-            if (!h.stepping) return;
+            if (!h.stepping) continue;
             h.stepping = false;
             if (res[r].err) {
                 h.status = (res[r].err == 1) ? PA_ECAPACITY : PA_EEXTINCT;
                 read_stats(b, r);  // statistics of the unchanged population
-                return;
+                continue;
             }
             h.cur ^= 1;
             h.R_cur = res[r].r_new;
@@ -1216,7 +1231,7 @@ pa_status pa_batch_step(pa_batch* b, int32_t* n_active)
             read_stats(b, r);
             record_measurement(h);
             if (h.beta >= h.sched.beta_f) h.finished = true;
-        });
+        }
     }
     if (n_active) {
         int n = 0;

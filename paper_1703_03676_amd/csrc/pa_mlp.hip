@@ -368,7 +368,7 @@ struct pa_mlp {
     float *p, *grad, *mom, *norm, *work, *loss;
     __hip_bfloat16* wb;
     int32_t* idx;
-    float* h_out = nullptr;         // pinned: gradient and loss, written by k_apply
+    float* h_out = nullptr;         // pinned: gradient and loss, written by k_apply (from the first call on)
     void* h_out_dev = nullptr;      // device view of h_out
     int32_t* h_order[2] = {nullptr, nullptr};  // pinned: sample orders of two epochs in turn
     size_t order_cap = 0;           // samples each of them holds
@@ -487,15 +487,6 @@ pa_status pa_mlp_create(int32_t max_batch, uint64_t seed, void* d_workspace, siz
     m->work = (float*)(w + lo.work);
     m->loss = (float*)(w + lo.loss);
     m->idx = (int32_t*)(w + lo.idx);
-    if (hipHostMalloc((void**)&m->h_out, kPartStride * 4, hipHostMallocMapped) != hipSuccess) {
-        delete m;
-        return PA_ENOMEM;
-    }
-    if (hipHostGetDevicePointer(&m->h_out_dev, m->h_out, 0) != hipSuccess) {
-        (void)hipHostFree(m->h_out);
-        delete m;
-        return PA_EHIP;
-    }
     // He initialisation from the seed; biases zero; identity normalisation.
     std::vector<float> p(kParams, 0.0f), zero(kParams, 0.0f), norm(kNorm, 0.0f);
     std::mt19937_64 rng(seed);
@@ -564,6 +555,10 @@ pa_status pa_mlp_gradient(pa_mlp* m, const float* d_x, const float* d_t, int32_t
 {
     if (!m || !d_x || !d_t || n < 1 || n > m->max_batch) return PA_EINVAL;
     if (m->broken) return PA_ESTATE;
+    if (!m->h_out) {
+        if (hipHostMalloc((void**)&m->h_out, kPartStride * 4, hipHostMallocMapped) != hipSuccess) return PA_ENOMEM;
+        MCHK(hipHostGetDevicePointer(&m->h_out_dev, m->h_out, 0));
+    }
     float* out = (float*)m->h_out_dev;
     const pa_status st = grad_pass(m, d_x, d_t, nullptr, n, out, 0.0f, 0.0f, out + kParams, true);
     if (st != PA_OK) return st;
