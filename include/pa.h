@@ -215,9 +215,8 @@ pa_status pa_weighted_average(int32_t N, int32_t nruns, int32_t nb, const pa_obs
  * pa_observables does.  *out (host) receives the same values pa_observables
  * gives for that population: the averages of Eq. (observables), -beta F/N of
  * Eq. (free energy), S/N of Eq. (entropy) and the exact integer sums.
- * The statistics kernel's partial sums, statistics block and energy
- * histogram live in a statically allocated device array of
- * pa_static_scratch_bytes() bytes (about 0.5 MiB), one per GPU, held until
+ * The partial sums and the statistics block live in a statically allocated
+ * device array of pa_static_scratch_bytes() bytes, one per GPU, held until
  * the process ends: the call allocates nothing.  It runs on hip_stream (NULL:
  * the null stream) of the current device and synchronises that stream.
  * Every call on a GPU uses that GPU's one array, so calls that overlap on one
@@ -272,8 +271,8 @@ pa_status pa_set_tie_queue_cap(pa_run* r, int32_t cap);
  * in the epilogue of the sweep that makes the population (every wave adds its
  * replicas with device atomics, then one block sums them) or in a separate
  * pass over E and M.  PA_STATS_AUTO (the
- * default) takes the epilogue where it measured faster: one replica per wave
- * (L >= 64) and R <= 32768, or L = 256.  PA_STATS_EPILOGUE and PA_STATS_PASS
+ * default) takes the epilogue where it measured faster: L >= 32 and
+ * R <= 32768, or L = 256.  PA_STATS_EPILOGUE and PA_STATS_PASS
  * force one of them.  Results do not depend on the choice.
  * Errors: PA_EINVAL (unknown mode), PA_ESTATE. */
 typedef enum { PA_STATS_AUTO = 0, PA_STATS_EPILOGUE = 1, PA_STATS_PASS = 2 } pa_stats_path;

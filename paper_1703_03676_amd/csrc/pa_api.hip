@@ -123,7 +123,8 @@ struct pa_run {
     uint64_t gathered_version = 0;  // population whose statistics the last sweep's epilogue publishes to hstats
     DevStats h_stats;
     std::vector<uint32_t> h_hist;
-    uint8_t* pinned;
+    uint8_t* pinned;            // copy-count tables of the next step, then the resampling total
+    void* pinned_dev = nullptr; // device view of pinned
     size_t pinned_bytes;
     uint32_t* hstats = nullptr;  // pinned: statistics block + histogram window, written by the statistics kernel or gather
     void* hstats_dev = nullptr;  // device view of hstats
@@ -177,16 +178,17 @@ void key_of(const pa_run* r, uint32_t* k0, uint32_t* k1, uint32_t* tag)
 // Whether the sweeps of this run take the statistics of the population they
 // make in their epilogue (else a separate pass, stats_kernel, takes them).
 // Measured per temperature step at theta = 1 (where the difference shows most),
-// against the separate pass: faster with one replica per wave up to about
-// 32768 replicas (L = 64: 1.6 us less at R = 20000; L = 128 within 1 us up to
-// R = 30000) and at L = 256 at every R (15-100 us less); slower beyond (L =
-// 128, R = 100000: 13 us more) and when a wave holds several replicas (L = 16,
-// 32: 2-13 us more), where the epilogue's reductions cost as much as a short
-// sweep.
+// against the separate pass: faster for L >= 32 up to about 32768 replicas
+// (L = 32: 1.6 us less at R = 4000 and 1.8 at 32000; L = 64: 5 us less at R =
+// 30000; L = 128: 3 us less there) and at L = 256 at every R (15-100 us less);
+// slower beyond (L = 32, R = 60000: 3 us more; L = 128, R = 100000: 6 us more)
+// and at L = 16 (R = 1000: 1.8 us more; R = 30000: 2.7 us more), where the
+// epilogue's reductions cost as much as a short sweep.  Up to 4096 replicas
+// both take the same within 0.5 us at L >= 32.
 bool stats_in_epilogue(const pa_run* r)
 {
     if (r->stats_path != PA_STATS_AUTO) return r->stats_path == PA_STATS_EPILOGUE;
-    return r->L == 256 || (r->L >= 64 && r->p.R <= 32768);
+    return r->L == 256 || (r->L >= 32 && r->p.R <= 32768);
 }
 
 // The two ping-pong stores the sweeps and the replica copy of a call work on
@@ -326,15 +328,23 @@ pa_status queue_resample(pa_run* r, const SpinView& view, double beta_next, bool
     *Emin = h.energy(bmin);
     uint32_t* tab = (uint32_t*)r->pinned;
     *lnQ = host::resample_tables(h, r->p.R, r->R_cur, beta_next - r->beta, tab, r->w, &r->wpre);
-    HIPCHK(hipMemcpyAsync(sc.tbl, tab, (size_t)nwin * 8, hipMemcpyHostToDevice, r->stream));
     uint32_t k0, k1, tag;
     key_of(r, &k0, &k1, &tag);
     const int32_t n = (int32_t)r->R_cur;
     const int nxt = r->cur ^ 1;
-    HIPCHK(pa::launch_counts(r->E[r->cur], n, r->N, bmin, nwin, sc.tbl, (uint32_t)(r->step + 1), k0, k1, tag,
-                             sc.counts, sc.bsum, r->stream));
-    HIPCHK(pa::launch_scatter(sc.counts, sc.bsum, n, r->lo.capacity, sc.parent, r->stats, r->hist, r->nbins,
-                              r->stream));
+    uint32_t* total = (uint32_t*)((uint8_t*)r->pinned_dev + r->pinned_bytes - 8);
+    if (pa::resample_small(n, nwin)) {
+        HIPCHK(pa::launch_resample_small(r->E[r->cur], n, r->N, bmin, nwin, r->pinned_dev, (uint32_t)(r->step + 1),
+                                         k0, k1, tag, sc.counts, r->lo.capacity, sc.parent, r->stats, r->hist,
+                                         r->nbins, total, r->stream));
+    } else {
+        HIPCHK(hipMemcpyAsync(sc.tbl, tab, (size_t)nwin * 8, hipMemcpyHostToDevice, r->stream));
+        HIPCHK(pa::launch_counts(r->E[r->cur], n, r->N, bmin, nwin, sc.tbl, (uint32_t)(r->step + 1), k0, k1, tag,
+                                 sc.counts, sc.bsum, r->stream));
+        HIPCHK(pa::launch_scatter(sc.counts, sc.bsum, n, r->lo.capacity, sc.parent, r->stats, r->hist, r->nbins,
+                                  total, r->stream));
+    }
+    if (copy) HIPCHK(hipEventRecord(r->ev_rnew, r->stream));  // the total is in host memory once this has passed
     if (copy && view.layout == PA_SPIN_INTERLEAVED)
         HIPCHK(pa::launch_copy_interleaved(view.spin[r->cur], r->E[r->cur], r->M[r->cur], sc.parent,
                                            &r->stats->r_new, r->lo.capacity, r->N, r->lo.stride, view.spin[nxt],
@@ -428,7 +438,7 @@ pa_status pa_init(const pa_params* p, void* d_workspace, size_t bytes, void* hip
     }
     r->h_hist.assign((size_t)r->nbins, 0u);
     r->pinned_bytes = sizeof(DevStats) + (size_t)r->nbins * 8;
-    if (hipHostMalloc((void**)&r->pinned, r->pinned_bytes, hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc((void**)&r->pinned, r->pinned_bytes, hipHostMallocMapped) != hipSuccess) {
         delete r;
         return PA_ENOMEM;
     }
@@ -439,6 +449,7 @@ pa_status pa_init(const pa_params* p, void* d_workspace, size_t bytes, void* hip
         return PA_ENOMEM;
     }
     if (hipHostGetDevicePointer(&r->hstats_dev, r->hstats, 0) != hipSuccess ||
+        hipHostGetDevicePointer(&r->pinned_dev, r->pinned, 0) != hipSuccess ||
         hipEventCreateWithFlags(&r->ev_rnew, hipEventDisableTiming) != hipSuccess) {
         (void)hipHostFree(r->hstats);
         (void)hipHostFree(r->pinned);
@@ -497,11 +508,8 @@ static pa_status resample_with(pa_run* r, double beta_next, pa_resample_info* ou
     st = queue_resample(r, own_view(r), beta_next, true, &lnQ, &Emin, sc);
     if (st != PA_OK) return st;
     // the host waits only for the total; the copy runs on meanwhile
-    uint32_t* rn = (uint32_t*)(r->pinned + r->pinned_bytes - 8);
-    HIPCHK(hipMemcpyAsync(rn, &r->stats->r_new, 4, hipMemcpyDeviceToHost, r->stream));
-    HIPCHK(hipEventRecord(r->ev_rnew, r->stream));
     HIPCHK(hipEventSynchronize(r->ev_rnew));
-    const int64_t R_new = *rn;
+    const int64_t R_new = *(const volatile uint32_t*)(r->pinned + r->pinned_bytes - 8);
     r->stats_version = 0;  // the stats block now holds the resampling total
     if (R_new > r->lo.capacity) return PA_ECAPACITY;
     if (R_new == 0) return PA_EEXTINCT;

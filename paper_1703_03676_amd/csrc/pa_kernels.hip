@@ -74,6 +74,122 @@ __global__ __launch_bounds__(kBlock) void stats_kernel(const int32_t* __restrict
     stats_publish(parts, nparts, st, hist, N, host);
 }
 
+// The statistics of a small population by one block of kSmallStatsThreads threads:
+// sums and energy range, then (HIST) the histogram over the occupied window in
+// LDS, written to hist and, with `host`, published there as by stats_kernel.
+// hist has been cleared before; r_new is kept.  Bound by latency: one block
+// needs no device-wide fence, counter or second reading of partials.  L = 16,
+// R = 1000: 7.4 us by stats_kernel, 5.2 us so (7.1 us with 1024 threads, see
+// stats_block_total); beyond kSmallStats replicas one CU reads E and M too
+// slowly (R = 8000 with 1024 threads: 4 us more than stats_kernel).
+constexpr int kSmallThreads = 1024;
+static_assert(kSmallResample <= 4 * kSmallThreads, "resample_small_kernel: four parents per thread");
+constexpr int kSmallWin = 4096;  // LDS histogram bins; a wider window counts in hist itself
+
+constexpr int kSmallStatsThreads = 256;
+
+template <bool HIST>
+__global__ __launch_bounds__(kSmallStatsThreads) void stats_small_kernel(const int32_t* __restrict__ E,
+                                                                    const int32_t* __restrict__ M, int32_t n,
+                                                                    const uint32_t* n_dev, int32_t N, DevStats* st,
+                                                                    uint32_t* hist, uint32_t* __restrict__ host)
+{
+    __shared__ DevStats sh;
+    __shared__ uint32_t win[HIST ? kSmallWin : 1];
+    const int t = (int)threadIdx.x;
+    const uint32_t r_new = st->r_new;
+    if (n_dev) n = min(n, (int32_t)*n_dev);
+    uint64_t sE = 0, sE2 = 0, sA = 0, sM2 = 0, m4lo = 0, m4hi = 0;
+    int32_t emin = 0x7FFFFFFF, emax = (int32_t)0x80000000;
+#pragma unroll 4
+    for (int i = t; i < n; i += kSmallStatsThreads) {
+        const int64_t e = E[i], m = M[i];
+        const uint64_t am = (uint64_t)(m < 0 ? -m : m), m2 = am * am;
+        sE += (uint64_t)e;
+        sE2 += (uint64_t)(e * e);
+        sA += am;
+        sM2 += m2;
+        add_u128(m4lo, m4hi, m2 * m2, __umul64hi(m2, m2));
+        emin = min(emin, (int32_t)e);
+        emax = max(emax, (int32_t)e);
+    }
+    if constexpr (HIST)
+        for (int b = t; b < kSmallWin; b += kSmallStatsThreads) win[b] = 0u;
+    stats_block_total<kSmallStatsThreads>(sE, sE2, sA, sM2, m4lo, m4hi, emin, emax, st, &sh);
+    __syncthreads();  // the totals in sh, written by thread 0, are visible to the block
+    if (host && t < (int)(sizeof(DevStats) / 4)) {
+        const uint32_t* sw = reinterpret_cast<const uint32_t*>(&sh);
+        host[t] = (t == 2) ? r_new : (t == 3) ? 0u : sw[t];
+    }
+    if constexpr (HIST) {
+        const int32_t lo = sh.emin, hi = sh.emax;
+        if (lo > hi || lo < -2 * N || hi > 2 * N) return;  // empty or invalid: the host uses no bins
+        const int b0 = (lo + 2 * N) / 4, nwin = (hi - lo) / 4 + 1;
+        uint32_t* hh = host ? host + sizeof(DevStats) / 4 : nullptr;
+        const bool lds = nwin <= kSmallWin;  // uniform
+        for (int i = t; i < n; i += kSmallStatsThreads) {
+            const int b = ((E[i] + 2 * N) >> 2) - b0;
+            atomicAdd(lds ? &win[b] : &hist[b0 + b], 1u);
+        }
+        if (!lds) __threadfence();
+        __syncthreads();
+        for (int b = t; b < nwin; b += kSmallStatsThreads) {
+            // (counts made in hist by this block's atomics are read past the L1)
+            const uint32_t c = lds ? win[b] : __hip_atomic_load(&hist[b0 + b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (lds) hist[b0 + b] = c;
+            if (hh) hh[b0 + b] = c;
+        }
+    }
+}
+
+// Sums and energy range alone of a larger population, for callers that use no
+// histogram: kMomentThreads replicas per block and turn, the block that finishes
+// last (counted in st->done) adds the partials.
+constexpr int kMomentThreads = 256;
+
+__global__ __launch_bounds__(kMomentThreads) void moments_kernel(const int32_t* __restrict__ E,
+                                                                const int32_t* __restrict__ M, int32_t n,
+                                                                DevStats* parts, DevStats* st)
+{
+    __shared__ uint32_t last;
+    const int t = (int)threadIdx.x;
+    uint64_t sE = 0, sE2 = 0, sA = 0, sM2 = 0, m4lo = 0, m4hi = 0;
+    int32_t emin = 0x7FFFFFFF, emax = (int32_t)0x80000000;
+    for (int i = (int)blockIdx.x * kMomentThreads + t; i < n; i += (int)gridDim.x * kMomentThreads) {
+        const int64_t e = E[i], m = M[i];
+        const uint64_t am = (uint64_t)(m < 0 ? -m : m), m2 = am * am;
+        sE += (uint64_t)e;
+        sE2 += (uint64_t)(e * e);
+        sA += am;
+        sM2 += m2;
+        add_u128(m4lo, m4hi, m2 * m2, __umul64hi(m2, m2));
+        emin = min(emin, (int32_t)e);
+        emax = max(emax, (int32_t)e);
+    }
+    stats_block_total<kMomentThreads>(sE, sE2, sA, sM2, m4lo, m4hi, emin, emax, parts + blockIdx.x);
+    if (t == 0) {
+        __threadfence();  // this block's partials, device-wide
+        last = (atomicAdd(&st->done, 1u) == gridDim.x - 1u) ? 1u : 0u;
+    }
+    __syncthreads();
+    if (!last) return;  // uniform per block
+    __threadfence();    // every other block's partials are visible to this one
+    sE = sE2 = sA = sM2 = m4lo = m4hi = 0;
+    emin = 0x7FFFFFFF;
+    emax = (int32_t)0x80000000;
+    for (int p = t; p < (int)gridDim.x; p += kMomentThreads) {
+        const DevStats q = parts[p];
+        sE += q.sumE;
+        sE2 += q.sumE2;
+        sA += q.sumAbsM;
+        sM2 += q.sumM2;
+        add_u128(m4lo, m4hi, q.sumM4_lo, q.sumM4_hi);
+        emin = min(emin, q.emin);
+        emax = max(emax, q.emax);
+    }
+    stats_block_total<kMomentThreads>(sE, sE2, sA, sM2, m4lo, m4hi, emin, emax, st);
+}
+
 __global__ void stats_reset_kernel(DevStats* st, uint32_t* hist, int32_t nbins)
 {
     const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
@@ -130,7 +246,7 @@ __global__ __launch_bounds__(kGatherThreads) void stats_gather_kernel(AccSlot* _
         emax = s->emax;
         reset_slot(s);
     }
-    stats_block_total<kGatherThreads>(sE, sE2, sA, sM2, m4lo, m4hi, emin, emax, st, &sh);
+    stats_block_total<kAccSlots>(sE, sE2, sA, sM2, m4lo, m4hi, emin, emax, st, &sh);
     __syncthreads();  // the totals in sh, written by thread 0, are visible to the block
     const int32_t lo = sh.emin, hi = sh.emax;
     if (host && t < (int)(sizeof(DevStats) / 4)) {
@@ -224,7 +340,7 @@ __global__ __launch_bounds__(1024) void scan_blocks_kernel(uint32_t* bsum, int32
 // caller rejects such a population).  Without `scanned`, the offset of the
 // block's first child is the sum of the totals of the blocks before it (bsum,
 // from counts_kernel), so no separate scan pass is needed, and the last block
-// writes the grand total to st->r_new; with `scanned`, bsum already holds the
+// writes the grand total to st->r_new (and to host memory); with `scanned`, bsum already holds the
 // exclusive prefix (scan_blocks_kernel, for many blocks, where summing would
 // grow with the square of their number).  The kernel also clears the rest of
 // the statistics block and the histogram, ready for the statistics of the
@@ -232,7 +348,8 @@ __global__ __launch_bounds__(1024) void scan_blocks_kernel(uint32_t* bsum, int32
 __global__ __launch_bounds__(kBlock) void scatter_kernel(const uint32_t* __restrict__ counts,
                                                          const uint32_t* __restrict__ bsum, int32_t n, uint32_t cap,
                                                          uint32_t* __restrict__ parent, DevStats* st,
-                                                         uint32_t* __restrict__ hist, int32_t nbins, int scanned)
+                                                         uint32_t* __restrict__ hist, int32_t nbins, int scanned,
+                                                         uint32_t* __restrict__ host_total)
 {
     __shared__ uint32_t wpart[kBlock / 64];
     const int lane = (int)(threadIdx.x & 63u), wid = (int)(threadIdx.x >> 6);
@@ -255,7 +372,10 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(const uint32_t* __restr
     const uint32_t off = base + block_exclusive_scan(c, &total);
     fill_parents(parent, off, c, (uint32_t)(j - lane), cap);
     if (threadIdx.x == 0) {
-        if (!scanned && blockIdx.x == gridDim.x - 1) st->r_new = base + total;
+        if (blockIdx.x == gridDim.x - 1) {
+            if (!scanned) st->r_new = base + total;
+            *host_total = base + total;
+        }
         if (blockIdx.x == 0) {
             st->emin = 0x7FFFFFFF;
             st->emax = (int32_t)0x80000000;
@@ -264,6 +384,96 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(const uint32_t* __restr
         }
     }
     for (int b = j; b < nbins; b += (int)(gridDim.x * kBlock)) hist[b] = 0;
+}
+
+// Copy counts, their prefix sum and the parent indices of a small population in
+// one block: what counts_kernel and scatter_kernel do, with the tables read
+// from host memory into LDS by the kernel itself.  A thread takes four
+// consecutive parents, which share one Philox block, so n <= 4 * kSmallThreads.  It replaces an
+// upload (2.6 us), counts_kernel (2.3 us) and scatter_kernel (3 us), of which
+// most is starting and ending, by 5.9 us, and the gaps between them: with
+// stats_small_kernel a step of L = 16, R = 1000, theta = 1 takes 29.2 us
+// instead of 34.2.  With four times the parents in turns it lost (R = 10000:
+// 16 us against 9.2), so it ends at kSmallResample.
+constexpr int kSmallTable = 4096;  // table entries that LDS takes
+
+__global__ __launch_bounds__(kSmallThreads) void resample_small_kernel(
+    const int32_t* __restrict__ E, int32_t n, int32_t N, int32_t bmin, int32_t nwin, const uint2* __restrict__ tbl,
+    uint32_t step, uint32_t key0, uint32_t key1, uint32_t tag, uint32_t* __restrict__ counts, uint32_t cap,
+    uint32_t* __restrict__ parent, DevStats* st, uint32_t* __restrict__ hist, int32_t nbins,
+    uint32_t* __restrict__ host_total)
+{
+    constexpr int WAVES = kSmallThreads / 64;
+    __shared__ uint2 tab[kSmallTable];
+    __shared__ uint32_t wsum[WAVES];
+    const int t = (int)threadIdx.x, lane = t & 63, wid = t >> 6;
+    const int j = 4 * t;
+    int32_t e4[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (j + k < n) e4[k] = E[j + k];
+    for (int i = t; i < nwin; i += kSmallThreads) tab[i] = tbl[i];
+    const U4 P = philox10((uint32_t)t, step, 0u, tag | kStreamResample, key0, key1);
+    for (int b = t; b < nbins; b += kSmallThreads) hist[b] = 0u;
+    if (t == 0) {
+        st->emin = 0x7FFFFFFF;
+        st->emax = (int32_t)0x80000000;
+        st->done = 0u;
+        st->sumE = st->sumE2 = st->sumAbsM = st->sumM2 = st->sumM4_lo = st->sumM4_hi = 0;
+    }
+    __syncthreads();
+    uint32_t c[4] = {0u, 0u, 0u, 0u};
+    if (j < n) {
+        const uint32_t x[4] = {P.x, P.y, P.z, P.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (j + k >= n) break;
+            const int b = ((e4[k] + 2 * N) >> 2) - bmin;
+            if (b >= 0 && b < nwin) {  // always true for the population the tables were built from
+                const uint2 e = tab[b];
+                c[k] = e.x + (x[k] <= e.y ? 1u : 0u);
+            }
+            counts[j + k] = c[k];
+        }
+    }
+    const uint32_t sum = c[0] + c[1] + c[2] + c[3];
+    uint32_t incl = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)incl, off);
+        if (lane >= off) incl += y;
+    }
+    if (lane == 63) wsum[wid] = incl;
+    __syncthreads();
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        if (w < wid) before += wsum[w];
+        total += wsum[w];
+    }
+    if (t == 0) {
+        st->r_new = total;
+        *host_total = total;
+    }
+    // the wave's children, 64 at a time: the owner lane by binary search over
+    // the lanes' range ends (as in fill_parents), then its parent among four
+    const uint32_t wave_total = wsum[wid];
+    for (uint32_t p0 = 0; p0 < wave_total; p0 += 64u) {
+        const uint32_t p = p0 + (uint32_t)lane;
+        int owner = 0;
+#pragma unroll
+        for (int s = 32; s >= 1; s >>= 1) {
+            const uint32_t e = (uint32_t)__shfl((int)incl, owner + s - 1);
+            if (e <= p) owner += s;
+        }
+        const uint32_t r = p - (uint32_t)__shfl((int)(incl - sum), owner);
+        const uint32_t e0 = (uint32_t)__shfl((int)c[0], owner);
+        const uint32_t e1 = e0 + (uint32_t)__shfl((int)c[1], owner);
+        const uint32_t e2 = e1 + (uint32_t)__shfl((int)c[2], owner);
+        const uint32_t k = (r >= e0 ? 1u : 0u) + (r >= e1 ? 1u : 0u) + (r >= e2 ? 1u : 0u);
+        const uint32_t child = before + p;
+        if (p < wave_total && child < cap) parent[child] = (uint32_t)(4 * (wid * 64 + owner)) + k;
+    }
 }
 
 // Replica copy child <- parent[child] for child < min(*n_new, cap); the size
@@ -317,6 +527,11 @@ hipError_t launch_stats(const int32_t* E, const int32_t* M, int32_t n, const uin
                         DevStats* st, uint32_t* hist, int32_t nbins, int record, DevMhr mhr, StatsPart* parts,
                         void* host, hipStream_t s)
 {
+    if (!record && n > 0 && n <= kSmallStats) {
+        hipLaunchKernelGGL((stats_small_kernel<true>), dim3(1), dim3(kSmallStatsThreads), 0, s, E, M, n, n_dev, N, st, hist,
+                           (uint32_t*)host);
+        return hipGetLastError();
+    }
     // at most kStatsBlocks blocks: each block's device-wide fence before it is
     // counted costs more than the chunks it saves beyond that
     const int blocks = std::min((n + kBlock - 1) / kBlock, kStatsBlocks);
@@ -325,6 +540,34 @@ hipError_t launch_stats(const int32_t* E, const int32_t* M, int32_t n, const uin
                        parts, st, (uint32_t*)host);
     return hipGetLastError();
 }
+
+hipError_t launch_moments(const int32_t* E, const int32_t* M, int32_t n, DevStats* parts, DevStats* st,
+                          hipStream_t s)
+{
+    if (n <= kSmallStats) {
+        hipLaunchKernelGGL((stats_small_kernel<false>), dim3(1), dim3(kSmallStatsThreads), 0, s, E, M, n,
+                           (const uint32_t*)nullptr, 0, st, (uint32_t*)nullptr, (uint32_t*)nullptr);
+    } else {
+        // (its counter starts from zero whatever an earlier call left)
+        hipLaunchKernelGGL(stats_reset_kernel, dim3(1), dim3(64), 0, s, st, (uint32_t*)nullptr, 0);
+        const int blocks = std::min((n + kMomentThreads - 1) / kMomentThreads, kMomentBlocks);
+        hipLaunchKernelGGL(moments_kernel, dim3(blocks), dim3(kMomentThreads), 0, s, E, M, n, parts, st);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_resample_small(const int32_t* E, int32_t n, int32_t N, int32_t bmin, int32_t nwin, const void* tbl,
+                                 uint32_t step, uint32_t key0, uint32_t key1, uint32_t tag, uint32_t* counts,
+                                 int32_t cap, uint32_t* parent, DevStats* st, uint32_t* hist, int32_t nbins,
+                                 uint32_t* host_total, hipStream_t s)
+{
+    hipLaunchKernelGGL(resample_small_kernel, dim3(1), dim3(kSmallThreads), 0, s, E, n, N, bmin, nwin,
+                       (const uint2*)tbl, step, key0, key1, tag, counts, (uint32_t)cap, parent, st, hist, nbins,
+                       host_total);
+    return hipGetLastError();
+}
+
+bool resample_small(int32_t n, int32_t nwin) { return n <= kSmallResample && nwin <= kSmallTable; }
 
 hipError_t launch_stats_reset(DevStats* st, uint32_t* hist, int32_t nbins, hipStream_t s)
 {
@@ -370,13 +613,13 @@ hipError_t launch_counts(const int32_t* E, int32_t n, int32_t N, int32_t bmin, i
 }
 
 hipError_t launch_scatter(const uint32_t* counts, uint32_t* bsum, int32_t n, int32_t cap, uint32_t* parent,
-                          DevStats* st, uint32_t* hist, int32_t nbins, hipStream_t s)
+                          DevStats* st, uint32_t* hist, int32_t nbins, uint32_t* host_total, hipStream_t s)
 {
     const int blocks = std::max((n + kBlock - 1) / kBlock, 1);
     const int scanned = blocks > kScanFreeBlocks ? 1 : 0;
     if (scanned) hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(1024), 0, s, bsum, blocks, st);
     hipLaunchKernelGGL(scatter_kernel, dim3(blocks), dim3(kBlock), 0, s, counts, (const uint32_t*)bsum, n,
-                       (uint32_t)cap, parent, st, hist, nbins, scanned);
+                       (uint32_t)cap, parent, st, hist, nbins, scanned, host_total);
     return hipGetLastError();
 }
 

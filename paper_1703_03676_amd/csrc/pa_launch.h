@@ -14,7 +14,9 @@ hipError_t launch_sweep(int L, int layout, int update, const SweepArgs& a, hipSt
 // range, moment sums; parts holds ceil(n / kBlock) partials.  With n_dev the
 // size is min(*n_dev, n), read on the device.  At most kStatsBlocks blocks,
 // each taking chunks of kBlock replicas in turn.
+// Populations up to kSmallStats replicas take one block (not with `record`).
 constexpr int kStatsBlocks = 128;
+constexpr int kSmallStats = 4096;
 hipError_t launch_stats(const int32_t* E, const int32_t* M, int32_t n, const uint32_t* n_dev, int32_t N,
                         DevStats* st, uint32_t* hist, int32_t nbins, int record, DevMhr mhr, StatsPart* parts,
                         void* host, hipStream_t s);
@@ -28,11 +30,20 @@ hipError_t launch_counts(const int32_t* E, int32_t n, int32_t N, int32_t bmin, i
 // st->r_new, and the statistics block and histogram cleared for the next
 // statistics; then the replica copy of min(*n_new, cap) children, n_new read
 // on the device.
+// The total also goes to *host_total (device view of pinned host memory).
 // Up to kScanFreeBlocks blocks of counts, each scatter block sums the totals
 // before it; beyond, a single-block scan of the totals runs first.
 constexpr int kScanFreeBlocks = 1024;
 hipError_t launch_scatter(const uint32_t* counts, uint32_t* bsum, int32_t n, int32_t cap, uint32_t* parent,
-                          DevStats* st, uint32_t* hist, int32_t nbins, hipStream_t s);
+                          DevStats* st, uint32_t* hist, int32_t nbins, uint32_t* host_total, hipStream_t s);
+// Both of these and the reading of the tables (tbl: device view of pinned host
+// memory) in one block, where resample_small says so.
+constexpr int kSmallResample = 4096;
+bool resample_small(int32_t n, int32_t nwin);
+hipError_t launch_resample_small(const int32_t* E, int32_t n, int32_t N, int32_t bmin, int32_t nwin, const void* tbl,
+                                 uint32_t step, uint32_t key0, uint32_t key1, uint32_t tag, uint32_t* counts,
+                                 int32_t cap, uint32_t* parent, DevStats* st, uint32_t* hist, int32_t nbins,
+                                 uint32_t* host_total, hipStream_t s);
 hipError_t launch_copy(const uint8_t* src, const int32_t* Esrc, const int32_t* Msrc, const uint32_t* parent,
                        const uint32_t* n_new, int32_t cap, size_t rep_bytes, uint8_t* dst, int32_t* Edst,
                        int32_t* Mdst, hipStream_t s);
@@ -51,6 +62,11 @@ hipError_t launch_copy_interleaved(const uint8_t* src, const int32_t* Esrc, cons
 hipError_t launch_stats_gather(AccSlot* acc, uint32_t* acc_hist, int32_t nbins, int32_t N, DevStats* st,
                                uint32_t* hist, void* host, hipStream_t s);
 hipError_t launch_acc_reset(AccSlot* acc, uint32_t* acc_hist, int32_t nbins, hipStream_t s);
+// Energy range and sums of a population alone into *st; parts holds
+// kMomentBlocks partials.
+constexpr int kMomentBlocks = 128;
+hipError_t launch_moments(const int32_t* E, const int32_t* M, int32_t n, DevStats* parts, DevStats* st,
+                          hipStream_t s);
 // Clears the range, the sums and the histogram (not r_new).
 hipError_t launch_stats_reset(DevStats* st, uint32_t* hist, int32_t nbins, hipStream_t s);
 
