@@ -23,7 +23,7 @@
  *   - The HIP stream passed to pa_init is borrowed; all device work of the run
  *     is enqueued on it.  Calls that return host values (pa_resample's info,
  *     pa_adapt_beta, pa_observables, pa_reweight, the download hooks)
- *     synchronise that stream before returning.
+ *     return when the work queued on it that they depend on has been done.
  *   - Spin convention: +1 / -1; J = 1, h = 0; E = -sum over the 2N bonds;
  *     M = sum of spins.  Energies are multiples of 4 in [-2N, 2N].
  *   - Random numbers: Philox4x32-10 keyed by the 64-bit seed, with counters

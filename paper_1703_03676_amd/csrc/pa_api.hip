@@ -9,6 +9,7 @@
 // and without contraction (-ffp-contract=off), so a run is reproducible bit for
 // bit from its seed and schedule.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -126,6 +127,7 @@ struct pa_run {
     uint8_t* pinned;            // copy-count tables of the next step, then the resampling total
     void* pinned_dev = nullptr; // device view of pinned
     size_t pinned_bytes;
+    uint32_t seq = 0;            // number of the last publication queued to hstats
     uint32_t* hstats = nullptr;  // pinned: statistics block + histogram window, written by the statistics kernel or gather
     void* hstats_dev = nullptr;  // device view of hstats
     hipEvent_t ev_rnew = nullptr;  // marks the resampling total in host memory
@@ -230,6 +232,41 @@ hipError_t leave_view(const pa_run* r, const SpinView& v)
     return pa::launch_unpack(r->L, v.spin[r->cur], r->lo.stride, (int32_t)r->R_cur, r->spin[r->cur], r->stream);
 }
 
+// Polls `there` for at most kSpinUs, which covers a short step; the caller
+// falls back to a wait on the stream or on an event, which also reports an
+// error of the device.
+constexpr int kSpinUs = 200;
+
+template <class F>
+bool spin_for(F there)
+{
+    const auto t0 = std::chrono::steady_clock::now();
+    for (;;) {
+        for (int i = 0; i < 64; ++i) {
+            if (there()) return true;
+            __builtin_ia32_pause();
+        }
+        if (std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(kSpinUs)) return false;
+    }
+}
+
+// Number of the next publication to hstats (never zero, the value at the start).
+uint32_t next_seq(pa_run* r)
+{
+    if (++r->seq == 0u) r->seq = 1u;
+    return r->seq;
+}
+
+// Waits for the publication that was queued last: everything of the step
+// before it on the stream has then been done.
+hipError_t wait_published(pa_run* r)
+{
+    const uint32_t want = r->seq;
+    uint32_t* at = r->hstats + 3;
+    if (spin_for([=] { return __atomic_load_n(at, __ATOMIC_ACQUIRE) == want; })) return hipSuccess;
+    return hipStreamSynchronize(r->stream);
+}
+
 // Queues nsweeps sweeps of the current population (or, with `init`, the
 // initial state; with neither, the recount of E and M).  Where the run takes
 // statistics in the epilogue (stats_in_epilogue), the gather publishes those
@@ -263,7 +300,7 @@ pa_status launch_sweeps(pa_run* r, int32_t nsweeps, bool init, uint64_t ver)
     if (init || nsweeps > 0) HIPCHK(leave_view(r, view));
     if (epilogue) {
         HIPCHK(pa::launch_stats_gather(r->acc, r->acc_hist, r->nbins, r->N, r->stats, r->hist, r->hstats_dev,
-                                       r->stream));
+                                       next_seq(r), r->stream));
         r->gathered_version = ver;
     }
     return PA_OK;
@@ -276,6 +313,7 @@ pa_status launch_sweeps(pa_run* r, int32_t nsweeps, bool init, uint64_t ver)
 pa_status read_host_stats(pa_run* r, DevStats* out)
 {
     std::memcpy(out, r->hstats, sizeof(DevStats));
+    out->done = 0u;  // (the publication's number there)
     if (out->emin < -2 * r->N || out->emax > 2 * r->N || out->emin > out->emax) {
         r->broken = true;
         r->last_error = "population energies out of range";
@@ -299,9 +337,9 @@ pa_status refresh_stats(pa_run* r, bool record, pa::StatsPart* parts)
     if (record || r->gathered_version != r->version) {
         HIPCHK(pa::launch_stats_reset(r->stats, r->hist, r->nbins, r->stream));
         HIPCHK(pa::launch_stats(r->E[r->cur], r->M[r->cur], (int32_t)r->R_cur, nullptr, r->N, r->stats, r->hist,
-                                r->nbins, record ? 1 : 0, r->mhr, parts, r->hstats_dev, r->stream));
+                                r->nbins, record ? 1 : 0, r->mhr, parts, r->hstats_dev, next_seq(r), r->stream));
     }  // else the epilogue of the sweep that made this population has queued them
-    HIPCHK(hipStreamSynchronize(r->stream));
+    HIPCHK(wait_published(r));
     const pa_status st = read_host_stats(r, &r->h_stats);
     if (st != PA_OK) return st;
     r->stats_version = r->version;
@@ -309,6 +347,11 @@ pa_status refresh_stats(pa_run* r, bool record, pa::StatsPart* parts)
 }
 
 host::Hist window(const pa_run* r) { return host::hist_window(r->h_hist.data(), r->h_stats, r->N); }
+
+// The resampling total in host memory, and its value until the kernels have
+// written it (at that total, were it to occur, the host waits for the event).
+constexpr uint32_t kNoTotal = 0xFFFFFFFFu;
+uint32_t* resample_total(pa_run* r) { return (uint32_t*)(r->pinned + r->pinned_bytes - 8); }
 
 // Queues the resampling of the current population to beta_next into the
 // other ping-pong buffer: Eq. (Q) with the E_min shift and the tables of Eq.
@@ -333,6 +376,7 @@ pa_status queue_resample(pa_run* r, const SpinView& view, double beta_next, bool
     const int32_t n = (int32_t)r->R_cur;
     const int nxt = r->cur ^ 1;
     uint32_t* total = (uint32_t*)((uint8_t*)r->pinned_dev + r->pinned_bytes - 8);
+    *resample_total(r) = kNoTotal;
     if (pa::resample_small(n, nwin)) {
         HIPCHK(pa::launch_resample_small(r->E[r->cur], n, r->N, bmin, nwin, r->pinned_dev, (uint32_t)(r->step + 1),
                                          k0, k1, tag, sc.counts, r->lo.capacity, sc.parent, r->stats, r->hist,
@@ -456,6 +500,7 @@ pa_status pa_init(const pa_params* p, void* d_workspace, size_t bytes, void* hip
         delete r;
         return PA_EHIP;
     }
+    r->hstats[3] = 0u;
     r->cur = 0;
     r->R_cur = p->R;
     r->step = 0;
@@ -508,8 +553,10 @@ static pa_status resample_with(pa_run* r, double beta_next, pa_resample_info* ou
     st = queue_resample(r, own_view(r), beta_next, true, &lnQ, &Emin, sc);
     if (st != PA_OK) return st;
     // the host waits only for the total; the copy runs on meanwhile
-    HIPCHK(hipEventSynchronize(r->ev_rnew));
-    const int64_t R_new = *(const volatile uint32_t*)(r->pinned + r->pinned_bytes - 8);
+    const uint32_t* total = resample_total(r);
+    if (!spin_for([=] { return __atomic_load_n(total, __ATOMIC_ACQUIRE) != kNoTotal; }))
+        HIPCHK(hipEventSynchronize(r->ev_rnew));
+    const int64_t R_new = *total;
     r->stats_version = 0;  // the stats block now holds the resampling total
     if (R_new > r->lo.capacity) return PA_ECAPACITY;
     if (R_new == 0) return PA_EEXTINCT;
@@ -603,10 +650,10 @@ static pa_status anneal_steps(pa_run* r, const SpinView& view, const pa_schedule
         r->gathered_version = 0;
         if (epilogue)
             HIPCHK(pa::launch_stats_gather(r->acc, r->acc_hist, r->nbins, r->N, r->stats, r->hist, r->hstats_dev,
-                                           r->stream));
+                                           next_seq(r), r->stream));
         else
             HIPCHK(pa::launch_stats(r->E[nxt], r->M[nxt], r->lo.capacity, n_dev, r->N, r->stats, r->hist, r->nbins,
-                                    0, r->mhr, r->parts, r->hstats_dev, r->stream));
+                                    0, r->mhr, r->parts, r->hstats_dev, next_seq(r), r->stream));
         if (sc->mode == PA_STEP_FIXED && bn < sc->beta_f) {
             // while the GPU sweeps: the weights of the next step (its dbeta is
             // known in advance), over the current window plus a margin
@@ -614,7 +661,8 @@ static pa_status anneal_steps(pa_run* r, const SpinView& view, const pa_schedule
             const size_t want = (size_t)(h.bmax - h.bmin + 1) * 5 / 4 + 16;
             if (!r->wpre.covers(db, (int)want)) r->wpre.fill(db, want);
         }
-        HIPCHK(hipStreamSynchronize(r->stream));
+        // (an elapsed time is read only from completed events)
+        HIPCHK(sweep_ms && done < cap ? hipStreamSynchronize(r->stream) : wait_published(r));
         const int64_t R_new = reinterpret_cast<const DevStats*>(r->hstats)->r_new;
         if (R_new > r->lo.capacity || R_new == 0) {
             r->stats_version = 0;  // the statistics block holds the refused population
@@ -631,7 +679,7 @@ static pa_status anneal_steps(pa_run* r, const SpinView& view, const pa_schedule
         if (record) {
             HIPCHK(pa::launch_stats_reset(r->stats, r->hist, r->nbins, r->stream));
             HIPCHK(pa::launch_stats(r->E[r->cur], r->M[r->cur], (int32_t)r->R_cur, nullptr, r->N, r->stats, r->hist,
-                                    r->nbins, 1, r->mhr, r->parts, nullptr, r->stream));
+                                    r->nbins, 1, r->mhr, r->parts, nullptr, 0u, r->stream));
             r->m_beta.push_back(r->beta);
             r->m_lnZ.push_back(r->lnZ);
             r->m_R.push_back(r->R_cur);
@@ -678,6 +726,7 @@ pa_status pa_anneal(pa_run* r, const pa_schedule* sc, int32_t max_steps, pa_obs*
     const int cur0 = r->cur;
     HIPCHK(enter_view(r, view));
     st = anneal_steps(r, view, sc, max_steps, out, sweep_ms, cap, nsteps);
+    if (!r->broken) HIPCHK(hipStreamSynchronize(r->stream));
     if (r->p.layout == PA_SPIN_INTERLEAVED && !r->broken) {
         if (r->cur != cur0) std::swap(r->spin[0], r->spin[1]);
         HIPCHK(leave_view(r, view));

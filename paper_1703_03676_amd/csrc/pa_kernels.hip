@@ -27,34 +27,50 @@ using namespace pa::dev;
 // (bin b at byte 64 + 4 b), so the host reads them after the kernel without a
 // separate copy.
 // ---------------------------------------------------------------------------
+// Marks a publication as complete: `seq` in the place of the block counter
+// (host[3]), after every host write of the block.  The host polls it instead of
+// waiting for the kernel's end, the marker packet behind it and its signal:
+// a step of L = 128, R = 10000, theta = 1 takes 60.8 us instead of 63.1, one of
+// L = 16, R = 1000 27.4 instead of 29.2.  (With the system-wide fence in every
+// wave the 16 waves of the gather took 5 us longer.)
+__device__ __forceinline__ void publish_seq(uint32_t* host, uint32_t seq)
+{
+    // each wave waits for its own writes (they are uncached); only the first
+    // pays for the release, which writes its L2 back
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(host + 3, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Sums the partials into *st, clears the block counter and, with `host`,
 // publishes the statistics block and the histogram window there.  Called by
 // every thread of the one block that finalises.
 __device__ __forceinline__ void stats_publish(const StatsPart* parts, int nparts, DevStats* st, const uint32_t* hist,
-                                              int32_t N, uint32_t* host)
+                                              int32_t N, uint32_t* host, uint32_t seq)
 {
     stats_final(parts, nparts, st);
     __syncthreads();  // *st written by thread 0 is visible to the block
     if (threadIdx.x == 0) st->done = 0u;
     if (!host) return;
     const uint32_t* sw = reinterpret_cast<const uint32_t*>(st);
-    if (threadIdx.x < sizeof(DevStats) / 4) host[threadIdx.x] = (threadIdx.x == 3) ? 0u : sw[threadIdx.x];
+    if (threadIdx.x < sizeof(DevStats) / 4 && threadIdx.x != 3) host[threadIdx.x] = sw[threadIdx.x];
     const int32_t emin = st->emin, emax = st->emax;
-    if (emin > emax || emin < -2 * N || emax > 2 * N) return;  // empty or invalid: the host uses no bins
     uint32_t* h = host + sizeof(DevStats) / 4;
-    for (int b = (emin + 2 * N) / 4 + (int)threadIdx.x; b <= (emax + 2 * N) / 4; b += kBlock) h[b] = hist[b];
+    if (emin <= emax && emin >= -2 * N && emax <= 2 * N)  // else empty or invalid: the host uses no bins
+        for (int b = (emin + 2 * N) / 4 + (int)threadIdx.x; b <= (emax + 2 * N) / 4; b += kBlock) h[b] = hist[b];
+    publish_seq(host, seq);
 }
 
 __global__ __launch_bounds__(kBlock) void stats_kernel(const int32_t* __restrict__ E, const int32_t* __restrict__ M,
                                                        int32_t n, const uint32_t* n_dev, int32_t N, uint32_t* hist,
                                                        int32_t nbins, int record, DevMhr mhr, StatsPart* parts,
-                                                       DevStats* st, uint32_t* __restrict__ host)
+                                                       DevStats* st, uint32_t* __restrict__ host, uint32_t seq)
 {
     __shared__ uint32_t last;
     if (n_dev) n = min(n, (int32_t)*n_dev);
     const int nparts = (n + kBlock - 1) / kBlock;
     if (nparts == 0) {  // empty population (a refused step): block 0 publishes the empty statistics
-        if (blockIdx.x == 0) stats_publish(parts, 0, st, hist, N, host);
+        if (blockIdx.x == 0) stats_publish(parts, 0, st, hist, N, host, seq);
         return;
     }
     // chunks of kBlock replicas, strided over the grid; the blocks that hold
@@ -71,7 +87,7 @@ __global__ __launch_bounds__(kBlock) void stats_kernel(const int32_t* __restrict
     __syncthreads();
     if (!last) return;  // uniform per block
     __threadfence();    // every other block's updates are visible to this one
-    stats_publish(parts, nparts, st, hist, N, host);
+    stats_publish(parts, nparts, st, hist, N, host, seq);
 }
 
 // The statistics of a small population by one block of kSmallStatsThreads threads:
@@ -92,7 +108,8 @@ template <bool HIST>
 __global__ __launch_bounds__(kSmallStatsThreads) void stats_small_kernel(const int32_t* __restrict__ E,
                                                                     const int32_t* __restrict__ M, int32_t n,
                                                                     const uint32_t* n_dev, int32_t N, DevStats* st,
-                                                                    uint32_t* hist, uint32_t* __restrict__ host)
+                                                                    uint32_t* hist, uint32_t* __restrict__ host,
+                                                                    uint32_t seq)
 {
     __shared__ DevStats sh;
     __shared__ uint32_t win[HIST ? kSmallWin : 1];
@@ -117,17 +134,18 @@ __global__ __launch_bounds__(kSmallStatsThreads) void stats_small_kernel(const i
         for (int b = t; b < kSmallWin; b += kSmallStatsThreads) win[b] = 0u;
     stats_block_total<kSmallStatsThreads>(sE, sE2, sA, sM2, m4lo, m4hi, emin, emax, st, &sh);
     __syncthreads();  // the totals in sh, written by thread 0, are visible to the block
-    if (host && t < (int)(sizeof(DevStats) / 4)) {
+    if (host && t < (int)(sizeof(DevStats) / 4) && t != 3) {
         const uint32_t* sw = reinterpret_cast<const uint32_t*>(&sh);
-        host[t] = (t == 2) ? r_new : (t == 3) ? 0u : sw[t];
+        host[t] = (t == 2) ? r_new : sw[t];
     }
     if constexpr (HIST) {
         const int32_t lo = sh.emin, hi = sh.emax;
-        if (lo > hi || lo < -2 * N || hi > 2 * N) return;  // empty or invalid: the host uses no bins
-        const int b0 = (lo + 2 * N) / 4, nwin = (hi - lo) / 4 + 1;
+        // empty or invalid: the host uses no bins
+        const bool valid = lo <= hi && lo >= -2 * N && hi <= 2 * N;
+        const int b0 = valid ? (lo + 2 * N) / 4 : 0, nwin = valid ? (hi - lo) / 4 + 1 : 0;
         uint32_t* hh = host ? host + sizeof(DevStats) / 4 : nullptr;
         const bool lds = nwin <= kSmallWin;  // uniform
-        for (int i = t; i < n; i += kSmallStatsThreads) {
+        for (int i = t; valid && i < n; i += kSmallStatsThreads) {
             const int b = ((E[i] + 2 * N) >> 2) - b0;
             atomicAdd(lds ? &win[b] : &hist[b0 + b], 1u);
         }
@@ -139,6 +157,7 @@ __global__ __launch_bounds__(kSmallStatsThreads) void stats_small_kernel(const i
             if (lds) hist[b0 + b] = c;
             if (hh) hh[b0 + b] = c;
         }
+        if (host) publish_seq(host, seq);
     }
 }
 
@@ -225,7 +244,7 @@ __global__ __launch_bounds__(kGatherThreads) void stats_gather_kernel(AccSlot* _
                                                                       uint32_t* __restrict__ acc_hist, int32_t nbins,
                                                                       int32_t N, DevStats* st,
                                                                       uint32_t* __restrict__ hist,
-                                                                      uint32_t* __restrict__ host)
+                                                                      uint32_t* __restrict__ host, uint32_t seq)
 {
     __shared__ DevStats sh;
     const int t = (int)threadIdx.x;
@@ -249,13 +268,13 @@ __global__ __launch_bounds__(kGatherThreads) void stats_gather_kernel(AccSlot* _
     stats_block_total<kAccSlots>(sE, sE2, sA, sM2, m4lo, m4hi, emin, emax, st, &sh);
     __syncthreads();  // the totals in sh, written by thread 0, are visible to the block
     const int32_t lo = sh.emin, hi = sh.emax;
-    if (host && t < (int)(sizeof(DevStats) / 4)) {
+    if (host && t < (int)(sizeof(DevStats) / 4) && t != 3) {
         const uint32_t* sw = reinterpret_cast<const uint32_t*>(&sh);
-        host[t] = (t == 2) ? r_new : (t == 3) ? 0u : sw[t];
+        host[t] = (t == 2) ? r_new : sw[t];
     }
-    if (lo > hi || lo < -2 * N || hi > 2 * N) return;  // empty: no bins were added
+    const bool valid = lo <= hi && lo >= -2 * N && hi <= 2 * N;  // else empty: no bins were added
     uint32_t* hh = host ? host + sizeof(DevStats) / 4 : nullptr;
-    for (int b = (lo + 2 * N) / 4 + t; b <= (hi + 2 * N) / 4; b += kGatherThreads) {
+    for (int b = (lo + 2 * N) / 4 + t; valid && b <= (hi + 2 * N) / 4; b += kGatherThreads) {
         uint32_t c[kAccHists];
 #pragma unroll
         for (int k = 0; k < kAccHists; ++k) c[k] = acc_hist[(size_t)k * nbins + b];
@@ -268,6 +287,7 @@ __global__ __launch_bounds__(kGatherThreads) void stats_gather_kernel(AccSlot* _
         hist[b] = v;
         if (hh) hh[b] = v;
     }
+    if (host) publish_seq(host, seq);
 }
 
 // Every slot to the empty state and every histogram copy to zero.
@@ -525,11 +545,11 @@ __global__ __launch_bounds__(kBlock) void copy_kernel(const uint4* __restrict__ 
 
 hipError_t launch_stats(const int32_t* E, const int32_t* M, int32_t n, const uint32_t* n_dev, int32_t N,
                         DevStats* st, uint32_t* hist, int32_t nbins, int record, DevMhr mhr, StatsPart* parts,
-                        void* host, hipStream_t s)
+                        void* host, uint32_t seq, hipStream_t s)
 {
     if (!record && n > 0 && n <= kSmallStats) {
         hipLaunchKernelGGL((stats_small_kernel<true>), dim3(1), dim3(kSmallStatsThreads), 0, s, E, M, n, n_dev, N, st, hist,
-                           (uint32_t*)host);
+                           (uint32_t*)host, seq);
         return hipGetLastError();
     }
     // at most kStatsBlocks blocks: each block's device-wide fence before it is
@@ -537,7 +557,7 @@ hipError_t launch_stats(const int32_t* E, const int32_t* M, int32_t n, const uin
     const int blocks = std::min((n + kBlock - 1) / kBlock, kStatsBlocks);
     if (blocks == 0) return hipSuccess;
     hipLaunchKernelGGL(stats_kernel, dim3(blocks), dim3(kBlock), 0, s, E, M, n, n_dev, N, hist, nbins, record, mhr,
-                       parts, st, (uint32_t*)host);
+                       parts, st, (uint32_t*)host, seq);
     return hipGetLastError();
 }
 
@@ -546,7 +566,7 @@ hipError_t launch_moments(const int32_t* E, const int32_t* M, int32_t n, DevStat
 {
     if (n <= kSmallStats) {
         hipLaunchKernelGGL((stats_small_kernel<false>), dim3(1), dim3(kSmallStatsThreads), 0, s, E, M, n,
-                           (const uint32_t*)nullptr, 0, st, (uint32_t*)nullptr, (uint32_t*)nullptr);
+                           (const uint32_t*)nullptr, 0, st, (uint32_t*)nullptr, (uint32_t*)nullptr, 0u);
     } else {
         // (its counter starts from zero whatever an earlier call left)
         hipLaunchKernelGGL(stats_reset_kernel, dim3(1), dim3(64), 0, s, st, (uint32_t*)nullptr, 0);
@@ -577,10 +597,10 @@ hipError_t launch_stats_reset(DevStats* st, uint32_t* hist, int32_t nbins, hipSt
 }
 
 hipError_t launch_stats_gather(AccSlot* acc, uint32_t* acc_hist, int32_t nbins, int32_t N, DevStats* st,
-                               uint32_t* hist, void* host, hipStream_t s)
+                               uint32_t* hist, void* host, uint32_t seq, hipStream_t s)
 {
     hipLaunchKernelGGL(stats_gather_kernel, dim3(1), dim3(kGatherThreads), 0, s, acc, acc_hist, nbins, N, st, hist,
-                       (uint32_t*)host);
+                       (uint32_t*)host, seq);
     return hipGetLastError();
 }
 

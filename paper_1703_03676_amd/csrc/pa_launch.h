@@ -19,7 +19,7 @@ constexpr int kStatsBlocks = 128;
 constexpr int kSmallStats = 4096;
 hipError_t launch_stats(const int32_t* E, const int32_t* M, int32_t n, const uint32_t* n_dev, int32_t N,
                         DevStats* st, uint32_t* hist, int32_t nbins, int record, DevMhr mhr, StatsPart* parts,
-                        void* host, hipStream_t s);
+                        void* host, uint32_t seq, hipStream_t s);
 // With `host` (device view of pinned host memory of at least 64 + 4 nbins
 // bytes) the statistics block and the histogram window [emin, emax] are also
 // written there (bin b at byte 64 + 4 b).
@@ -60,7 +60,7 @@ hipError_t launch_copy_interleaved(const uint8_t* src, const int32_t* Esrc, cons
 // (hist cleared before, r_new kept), published to `host` as by launch_stats,
 // and the accumulators left cleared.  launch_acc_reset clears them once.
 hipError_t launch_stats_gather(AccSlot* acc, uint32_t* acc_hist, int32_t nbins, int32_t N, DevStats* st,
-                               uint32_t* hist, void* host, hipStream_t s);
+                               uint32_t* hist, void* host, uint32_t seq, hipStream_t s);
 hipError_t launch_acc_reset(AccSlot* acc, uint32_t* acc_hist, int32_t nbins, hipStream_t s);
 // Energy range and sums of a population alone into *st; parts holds
 // kMomentBlocks partials.
