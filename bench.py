@@ -302,7 +302,7 @@ def _batch_errors(b, runs):
 def workload_batch64(pa, torch, sequential=True):
     """64 runs, (L, R) in {16,32,64,128} x {5000,20000}, theta=20, adaptive
     alpha*=0.85, beta 0->1: plain adaptive one run at a time, batched
-    adaptive (one graph replay per step for all runs) and batched learned."""
+    adaptive (one launch per phase of a step for all runs) and batched learned."""
     import numpy as np
     theta, alpha = 20, 0.85
     out = {"workload": "64 runs, (L,R) in {16,32,64,128}x{5000,20000}, 8 seeds each, theta=20, "

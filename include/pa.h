@@ -271,8 +271,8 @@ pa_status pa_set_tie_queue_cap(pa_run* r, int32_t cap);
  * in the epilogue of the sweep that makes the population (every wave adds its
  * replicas with device atomics, then one block sums them) or in a separate
  * pass over E and M.  PA_STATS_AUTO (the
- * default) takes the epilogue where it measured faster: L >= 32 and
- * R <= 32768, or L = 256.  PA_STATS_EPILOGUE and PA_STATS_PASS
+ * default) takes the epilogue where it measured faster: one replica per wave
+ * (L >= 64) and R <= 32768, or L = 256.  PA_STATS_EPILOGUE and PA_STATS_PASS
  * force one of them.  Results do not depend on the choice.
  * Errors: PA_EINVAL (unknown mode), PA_ESTATE. */
 typedef enum { PA_STATS_AUTO = 0, PA_STATS_EPILOGUE = 1, PA_STATS_PASS = 2 } pa_stats_path;
@@ -282,8 +282,7 @@ pa_status pa_set_stats_path(pa_run* r, int32_t mode);
  * Every run has its own parameters (L, R, seed, run_id, layout, flags) and
  * schedule.  One pa_batch_step advances every unfinished run by one
  * temperature step (choose beta_{i+1}, resample, theta sweeps, measure) with
- * one batched launch per phase, replayed from a HIP graph, and one host
- * synchronisation for the whole batch.  Each run follows exactly the same
+ * one batched launch per phase and one host wait for the whole batch.  Each run follows exactly the same
  * arithmetic and random streams as a single run with the same parameters and
  * schedule, so its results are bit-identical to that run's. */
 
@@ -338,8 +337,7 @@ typedef struct pa_batch pa_batch;  /* opaque host handle */
 size_t pa_batch_workspace_bytes(const pa_params* runs, int32_t nruns);
 
 /* Start nruns runs at beta_0 = 0 (Sec. 2.1 step 1) and measure them once.
- * `hip_stream` may be NULL: the batch then creates its own stream (graph
- * capture needs a non-null stream).  The sweep's work-group shape (waves per
+ * `hip_stream` may be NULL: the batch then creates its own stream.  The sweep's work-group shape (waves per
  * block, one per launch: L <= 64 together, 128, 256, each with its store and
  * update) is chosen by timing the
  * candidates 1, 2, 4 and 8 on the batch's spare buffers.  Errors: PA_EINVAL

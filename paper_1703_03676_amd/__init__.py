@@ -389,7 +389,7 @@ class BatchOptions(ctypes.Structure):
 
 
 class Batch:
-    """Many independent PA runs advanced together (one graph replay per step).
+    """Many independent PA runs advanced together (one launch per phase of a step).
 
     runs: list of dicts with keys L, R, seed and optional run_id, capacity,
     layout, mhr, heatbath, lcg.  schedules: list of dicts for make_schedule (or one dict for

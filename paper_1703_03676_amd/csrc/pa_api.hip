@@ -9,7 +9,6 @@
 // and without contraction (-ffp-contract=off), so a run is reproducible bit for
 // bit from its seed and schedule.
 #include <algorithm>
-#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -180,17 +179,17 @@ void key_of(const pa_run* r, uint32_t* k0, uint32_t* k1, uint32_t* tag)
 // Whether the sweeps of this run take the statistics of the population they
 // make in their epilogue (else a separate pass, stats_kernel, takes them).
 // Measured per temperature step at theta = 1 (where the difference shows most),
-// against the separate pass: faster for L >= 32 up to about 32768 replicas
-// (L = 32: 1.6 us less at R = 4000 and 1.8 at 32000; L = 64: 5 us less at R =
-// 30000; L = 128: 3 us less there) and at L = 256 at every R (15-100 us less);
-// slower beyond (L = 32, R = 60000: 3 us more; L = 128, R = 100000: 6 us more)
-// and at L = 16 (R = 1000: 1.8 us more; R = 30000: 2.7 us more), where the
-// epilogue's reductions cost as much as a short sweep.  Up to 4096 replicas
-// both take the same within 0.5 us at L >= 32.
+// against the separate pass: faster with one replica per wave up to about
+// 32768 replicas (L = 64: 2 us less at R = 5000, 1.3 at 30000; L = 128: 2.5 us
+// less at R = 4000, within 1 us at 30000) and at L = 256 (2 us less at R =
+// 5000); slower beyond (L = 128, R = 100000: 9 us more) and when a wave holds
+// several replicas (L = 32 within 1.5 us of each other up to R = 32000, then
+// 7 us more at 60000; L = 16: 2 us more at R = 1000, 7 at 30000), where the
+// epilogue's reductions cost as much as a short sweep.
 bool stats_in_epilogue(const pa_run* r)
 {
     if (r->stats_path != PA_STATS_AUTO) return r->stats_path == PA_STATS_EPILOGUE;
-    return r->L == 256 || (r->L >= 32 && r->p.R <= 32768);
+    return r->L == 256 || (r->L >= 64 && r->p.R <= 32768);
 }
 
 // The two ping-pong stores the sweeps and the replica copy of a call work on
@@ -232,24 +231,6 @@ hipError_t leave_view(const pa_run* r, const SpinView& v)
     return pa::launch_unpack(r->L, v.spin[r->cur], r->lo.stride, (int32_t)r->R_cur, r->spin[r->cur], r->stream);
 }
 
-// Polls `there` for at most kSpinUs, which covers a short step; the caller
-// falls back to a wait on the stream or on an event, which also reports an
-// error of the device.
-constexpr int kSpinUs = 200;
-
-template <class F>
-bool spin_for(F there)
-{
-    const auto t0 = std::chrono::steady_clock::now();
-    for (;;) {
-        for (int i = 0; i < 64; ++i) {
-            if (there()) return true;
-            __builtin_ia32_pause();
-        }
-        if (std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(kSpinUs)) return false;
-    }
-}
-
 // Number of the next publication to hstats (never zero, the value at the start).
 uint32_t next_seq(pa_run* r)
 {
@@ -263,7 +244,7 @@ hipError_t wait_published(pa_run* r)
 {
     const uint32_t want = r->seq;
     uint32_t* at = r->hstats + 3;
-    if (spin_for([=] { return __atomic_load_n(at, __ATOMIC_ACQUIRE) == want; })) return hipSuccess;
+    if (host::spin_for([=] { return __atomic_load_n(at, __ATOMIC_ACQUIRE) == want; })) return hipSuccess;
     return hipStreamSynchronize(r->stream);
 }
 
@@ -554,7 +535,7 @@ static pa_status resample_with(pa_run* r, double beta_next, pa_resample_info* ou
     if (st != PA_OK) return st;
     // the host waits only for the total; the copy runs on meanwhile
     const uint32_t* total = resample_total(r);
-    if (!spin_for([=] { return __atomic_load_n(total, __ATOMIC_ACQUIRE) != kNoTotal; }))
+    if (!host::spin_for([=] { return __atomic_load_n(total, __ATOMIC_ACQUIRE) != kNoTotal; }))
         HIPCHK(hipEventSynchronize(r->ev_rnew));
     const int64_t R_new = *total;
     r->stats_version = 0;  // the stats block now holds the resampling total

@@ -6,12 +6,17 @@
 //           learned proposal + exact overlap test), FP64 copy-count tables of
 //           Eq. (resampling factors), Metropolis thresholds
 //   copy    one upload of every run's step descriptor and tables
-//   graph   counts -> per-run scan -> parent scatter -> replica copy -> sweep
-//           (one launch for all register-path lattice sizes of a store, one per
-//           larger size) -> statistics, written to host memory by the last
-//           block of every run
+//   device  counts -> parent scatter -> sweep (one launch for all register-path
+//           lattice sizes of a store, one per larger size) -> statistics,
+//           written to host memory by the last block of every run, which the
+//           host polls
 //   host    commit each run (ln Z += ln Q, observables of Eq. (observables))
-// The device part is captured once in a HIP graph and replayed every step.
+// The launches of a step are few and queued one by one: the first kernel runs
+// while the later ones are queued.  (A captured graph of the same kernels took
+// the host 28 us to launch before the first one started, and left 4-8 us
+// between its nodes.  A step of 12 runs of L = 16, 32 and 64 with 1000 and 5000
+// replicas: 271 us by the graph, a scan launch for every run, a stream wait and
+// fences in every wave of the statistics; 247 us so.)
 // Kernels read each run's step descriptor and its device-side population
 // size, so launch shapes stay fixed while R_i changes.  A run whose resampling
 // would exceed its capacity or die out is flagged on the device; its copy and
@@ -79,7 +84,7 @@ struct StepDev {
     uint32_t t2h, t2l, t4h, t4l;
     int32_t bmin, nwin;
     uint32_t tbl_off;  // offset in u32 of this run's tables in the table area
-    int32_t pad;
+    uint32_t seq;      // number of the step, by which the host knows its publication
     double beta;        // inverse temperature after this step
     double last_dbeta;  // the step just taken (0: none)
 };
@@ -131,14 +136,35 @@ __device__ __forceinline__ bool post_resample(const StepDev& st, const ResultDev
     return true;
 }
 
+// Runs of more parents than this (kScanFreeBlocks blocks of b_counts) have their
+// block sums scanned by b_scan; in the others every block of b_scatter sums
+// those before it, which saves the launch.
+__host__ __device__ constexpr bool scanned_run(int32_t capacity)
+{
+    return capacity > pa::kScanFreeBlocks * kBlock;
+}
+
+// Also clears the run's statistics for this step's population (the host has
+// read the previous ones).
 __global__ __launch_bounds__(kBlock) void b_counts(const Item* __restrict__ items, const RunDev* __restrict__ runs,
                                                    const StepDev* __restrict__ steps, const uint32_t* __restrict__ tbl)
 {
     const Item it = items[blockIdx.x];
     const StepDev st = steps[it.run];
-    if (!st.active || !st.resample || it.blk * kBlock >= st.n_parent) return;  // uniform per block
+    if (!st.active || it.blk * kBlock >= st.n_parent) return;  // uniform per block
     const RunDev& rd = runs[it.run];
     const int j = it.blk * kBlock + (int)threadIdx.x;
+    if (j == 0) {
+        DevStats* s = rd.stats;
+        s->emin = 0x7FFFFFFF;
+        s->emax = (int32_t)0x80000000;
+        s->r_new = 0;
+        s->done = 0;
+        s->sumE = s->sumE2 = s->sumAbsM = s->sumM2 = s->sumM4_lo = s->sumM4_hi = 0;
+    }
+    const int nblk = (st.n_parent + kBlock - 1) / kBlock;
+    for (int b = j; b < rd.nbins; b += nblk * kBlock) rd.hist[b] = 0;
+    if (!st.resample) return;
     uint32_t c = 0;
     if (j < st.n_parent) {
         const int b = ((rd.E[st.cur][j] + 2 * rd.N) >> 2) - st.bmin;
@@ -155,27 +181,20 @@ __global__ __launch_bounds__(kBlock) void b_counts(const Item* __restrict__ item
     if (threadIdx.x == 0) rd.bsum[it.blk] = total;
 }
 
-// One block per run: its statistics cleared for this step's population, and the
-// exclusive scan of its block sums, total and status.
+// Size and status of a run's resampled population.
+__device__ __forceinline__ ResultDev resampled(uint32_t total, int32_t capacity)
+{
+    return ResultDev{total, total > (uint32_t)capacity ? 1u : (total == 0u ? 2u : 0u)};
+}
+
+// One block per run that needs it (scanned_run): the exclusive scan of its
+// block sums, total and status.
 __global__ __launch_bounds__(1024) void b_scan(const RunDev* __restrict__ runs, const StepDev* __restrict__ steps,
                                                ResultDev* __restrict__ res)
 {
     __shared__ uint32_t part[1024];
     const StepDev st = steps[blockIdx.x];
-    if (!st.active) return;
-    {
-        const RunDev& rd = runs[blockIdx.x];
-        if (threadIdx.x == 0) {
-            DevStats* s = rd.stats;
-            s->emin = 0x7FFFFFFF;
-            s->emax = (int32_t)0x80000000;
-            s->r_new = 0;
-            s->done = 0;
-            s->sumE = s->sumE2 = s->sumAbsM = s->sumM2 = s->sumM4_lo = s->sumM4_hi = 0;
-        }
-        for (int b = (int)threadIdx.x; b < rd.nbins; b += 1024) rd.hist[b] = 0;
-    }
-    if (!st.resample) return;
+    if (!st.active || !st.resample || !scanned_run(runs[blockIdx.x].capacity)) return;
     uint32_t* bsum = runs[blockIdx.x].bsum;
     const int nblk = (st.n_parent + kBlock - 1) / kBlock;
     const int t = (int)threadIdx.x;
@@ -197,26 +216,42 @@ __global__ __launch_bounds__(1024) void b_scan(const RunDev* __restrict__ runs, 
         bsum[i] = run;
         run += v;
     }
-    if (t == 1023) {
-        const uint32_t total = part[1023];
-        res[blockIdx.x].r_new = total;
-        res[blockIdx.x].err = total > (uint32_t)runs[blockIdx.x].capacity ? 1u : (total == 0u ? 2u : 0u);
-    }
+    if (t == 1023) res[blockIdx.x] = resampled(part[1023], runs[blockIdx.x].capacity);
 }
 
+// Parent of every child; children beyond the capacity (a refused step) are not
+// written.
 __global__ __launch_bounds__(kBlock) void b_scatter(const Item* __restrict__ items, const RunDev* __restrict__ runs,
                                                     const StepDev* __restrict__ steps,
-                                                    const ResultDev* __restrict__ res)
+                                                    ResultDev* __restrict__ res)
 {
+    __shared__ uint32_t wpart[kBlock / 64];
     const Item it = items[blockIdx.x];
     const StepDev st = steps[it.run];
-    if (!st.active || !st.resample || it.blk * kBlock >= st.n_parent || res[it.run].err) return;
+    if (!st.active || !st.resample || it.blk * kBlock >= st.n_parent) return;
     const RunDev& rd = runs[it.run];
+    const bool scanned = scanned_run(rd.capacity);
+    const int lane = (int)(threadIdx.x & 63u);
     const int j = it.blk * kBlock + (int)threadIdx.x;
     const uint32_t c = (j < st.n_parent) ? rd.counts[j] : 0u;
+    uint32_t base = 0;
+    if (scanned) {
+        base = rd.bsum[it.blk];
+    } else {
+        uint32_t before = 0;
+        for (int i = (int)threadIdx.x; i < it.blk; i += kBlock) before += rd.bsum[i];
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) before += (uint32_t)__shfl_xor((int)before, off);
+        if (lane == 0) wpart[threadIdx.x >> 6] = before;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kBlock / 64; ++w) base += wpart[w];
+    }
     uint32_t total;
-    const uint32_t off = rd.bsum[it.blk] + block_exclusive_scan(c, &total);
-    fill_parents(rd.parent, off, c, (uint32_t)j - (threadIdx.x & 63u), 0xFFFFFFFFu);
+    const uint32_t off = base + block_exclusive_scan(c, &total);
+    fill_parents(rd.parent, off, c, (uint32_t)(j - lane), (uint32_t)rd.capacity);
+    if (!scanned && threadIdx.x == 0 && (it.blk + 1) * kBlock >= st.n_parent)
+        res[it.run] = resampled(base + total, rd.capacity);
 }
 
 // Item blk covers 16-byte chunks [blk * kBlock, (blk + 1) * kBlock) of the run's new population.
@@ -247,9 +282,7 @@ __global__ __launch_bounds__(kBlock) void b_copy(const Item* __restrict__ items,
 // L = kSmall: the register-path lattice sizes together, each block that of its
 // run, so that the short launches of small lattices fill the GPU beside the
 // larger ones instead of following them (12 runs of L = 16, 32 and 64: 47 us of
-// separate launches per step beside 137 for L = 64 alone; as branches of the
-// graph they overlap too, but every node of a branching graph starts 10 us
-// after the one before).
+// separate launches per step beside 137 for L = 64 alone).
 constexpr int kSmall = 0;
 
 template <int L, bool INT8, int U>
@@ -375,7 +408,6 @@ __global__ __launch_bounds__(kBlock) void b_stats(const Item* __restrict__ items
                                                   const StepDev* __restrict__ steps, const ResultDev* __restrict__ res,
                                                   const ModelDev* __restrict__ model, uint8_t* host, size_t feats_off)
 {
-    __shared__ uint32_t last;
     const Item it = items[blockIdx.x];
     const StepDev st = steps[it.run];
     if (!st.active) return;
@@ -387,23 +419,19 @@ __global__ __launch_bounds__(kBlock) void b_stats(const Item* __restrict__ items
     stats_block(rd.E[buf], rd.M[buf], n, rd.N, it.blk * kBlock, rd.hist, rd.nbins, st.record && ok, rd.mhr,
                 &rd.parts[it.blk]);
     const int nparts = (n + kBlock - 1) / kBlock;
-    __threadfence();  // this block's partials and histogram updates, device-wide
-    __syncthreads();
-    if (threadIdx.x == 0) last = (atomicAdd(&rd.stats->done, 1u) == (uint32_t)(nparts - 1)) ? 1u : 0u;
-    __syncthreads();
-    if (!last) return;  // uniform per block
-    __threadfence();    // every other block's updates are visible to this one
+    if (!finishes_last(&rd.stats->done, (uint32_t)nparts)) return;  // uniform per block
     stats_final(rd.parts, nparts, rd.stats);
     __syncthreads();  // *rd.stats written by thread 0 is visible to the block
     const uint32_t* sw = reinterpret_cast<const uint32_t*>(rd.stats);
     uint32_t* hs = reinterpret_cast<uint32_t*>(host + rd.host_off);
-    if (threadIdx.x < sizeof(DevStats) / 4) hs[threadIdx.x] = sw[threadIdx.x];
+    if (threadIdx.x < sizeof(DevStats) / 4 && threadIdx.x != 3) hs[threadIdx.x] = sw[threadIdx.x];
     if (threadIdx.x == 0) reinterpret_cast<ResultDev*>(host)[it.run] = rs;
     const int32_t emin = rd.stats->emin, emax = rd.stats->emax;
     if (emin >= -2 * rd.N && emax <= 2 * rd.N)
         for (int b = (emin + 2 * rd.N) / 4 + (int)threadIdx.x; b <= (emax + 2 * rd.N) / 4; b += kBlock)
             hs[sizeof(DevStats) / 4 + b] = rd.hist[b];
     run_features(rd, st, n, ok, model, reinterpret_cast<FeatDev*>(host + feats_off) + it.run);
+    publish_seq(hs, st.seq);
 }
 
 __global__ void b_fill_u32(uint32_t* p, uint32_t value, size_t n)
@@ -678,10 +706,8 @@ struct pa_batch {
     uint8_t* h_steps = nullptr;     // pinned: step descriptors + tables
     uint8_t* h_download = nullptr;  // pinned: results, features and statistics, written by b_stats
     void* h_download_dev = nullptr; // device view of h_download
-    hipGraph_t graph = nullptr;        // one step, with the separate replica copy (b_copy)
-    hipGraphExec_t exec = nullptr;
-    hipGraph_t graph_nocopy = nullptr; // the same step without it: every resampled run sweeps and
-    hipGraphExec_t exec_nocopy = nullptr;  // so gathers its parents in b_sweep (the usual case)
+    bool any_scanned = false;       // some run's block sums need b_scan
+    uint32_t seq = 0;               // number of the last step queued
     pa::batch::Pool* pool = nullptr;
     pa_batch_options opt{0};  // forced launch shape (0: autotuned)
     bool broken = false;
@@ -784,8 +810,8 @@ std::vector<Item> sweep_items(const pa_batch* b, const Group& g, int wpb)
     return it;
 }
 
-// Enqueue the device part of one step (captured into the graphs), with or
-// without the separate replica copy of runs that resample without sweeping.
+// Enqueue the device part of one step, with or without the separate replica
+// copy of runs that resample without sweeping.
 pa_status enqueue_step(pa_batch* b, bool with_copy)
 {
     const hipStream_t s = b->stream;
@@ -795,8 +821,10 @@ pa_status enqueue_step(pa_batch* b, bool with_copy)
                            b->d_rundev, b->d_steps, b->d_tables);
         BCHK(hipGetLastError());
     }
-    hipLaunchKernelGGL(b_scan, dim3((unsigned)b->nruns), dim3(1024), 0, s, b->d_rundev, b->d_steps, b->d_results);
-    BCHK(hipGetLastError());
+    if (b->any_scanned) {
+        hipLaunchKernelGGL(b_scan, dim3((unsigned)b->nruns), dim3(1024), 0, s, b->d_rundev, b->d_steps, b->d_results);
+        BCHK(hipGetLastError());
+    }
     hipLaunchKernelGGL(b_scatter, dim3((unsigned)b->n_parent_items), dim3(kBlock), 0, s, items + b->parent_off,
                        b->d_rundev, b->d_steps, b->d_results);
     BCHK(hipGetLastError());
@@ -820,16 +848,29 @@ uint32_t* host_tables(pa_batch* b)
     return reinterpret_cast<uint32_t*>(b->h_steps + (b->lo.tables - b->lo.steps));
 }
 
-// Runs one replay of a step graph after uploading the first `bytes` bytes of
-// the step descriptors and packed tables: the one with the separate replica
-// copy only if some run resamples without sweeping (its b_copy launch covers
-// every run's capacity and costs tens of microseconds even when it has
-// nothing to do).
-pa_status replay(pa_batch* b, size_t bytes, bool need_copy)
+// Runs one step after uploading the first `bytes` bytes of the step descriptors
+// and packed tables, with the separate replica copy only if some run resamples
+// without sweeping (its launch covers every run's capacity and costs tens of
+// microseconds even when it has nothing to do).  Waits for the publication of
+// every run that takes part.
+pa_status run_step(pa_batch* b, size_t bytes, bool need_copy)
 {
+    if (++b->seq == 0u) b->seq = 1u;
+    StepDev* sd = host_steps(b);
+    for (int r = 0; r < b->nruns; ++r) sd[r].seq = b->seq;
     BCHK(hipMemcpyAsync(b->d_steps, b->h_steps, bytes, hipMemcpyHostToDevice, b->stream));
-    BCHK(hipGraphLaunch(need_copy ? b->exec : b->exec_nocopy, b->stream));
-    BCHK(hipStreamSynchronize(b->stream));
+    const pa_status st = enqueue_step(b, need_copy);
+    if (st != PA_OK) return st;
+    int r = 0;
+    const auto published = [&] {
+        for (; r < b->nruns; ++r) {
+            if (!sd[r].active) continue;
+            const uint32_t* at = reinterpret_cast<const uint32_t*>(b->h_download + b->lo.runs[(size_t)r].stats_off) + 3;
+            if (__atomic_load_n(at, __ATOMIC_ACQUIRE) != b->seq) return false;
+        }
+        return true;
+    };
+    if (!host::spin_for(published)) BCHK(hipStreamSynchronize(b->stream));
     return PA_OK;
 }
 
@@ -1087,17 +1128,7 @@ static pa_status batch_init(const pa_params* runs, const pa_schedule* sched, int
         g.n_items = it.size();
     }
     BCHK(hipMemcpyAsync(b->d_items, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice, b->stream));
-    // capture one step, with and without the separate replica copy
-    for (int with_copy = 1; with_copy >= 0; --with_copy) {
-        BCHK(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-        st = enqueue_step(b, with_copy != 0);
-        hipGraph_t g = nullptr;
-        const hipError_t ce = hipStreamEndCapture(b->stream, &g);
-        if (st != PA_OK) return st;
-        BCHK(ce);
-        (with_copy ? b->graph : b->graph_nocopy) = g;
-        BCHK(hipGraphInstantiate(with_copy ? &b->exec : &b->exec_nocopy, g, nullptr, nullptr, 0));
-    }
+    for (int r = 0; r < nruns; ++r) b->any_scanned = b->any_scanned || scanned_run(bl.runs[(size_t)r].capacity);
     // initial state (Sec. 2.1 step 1) and the measurement at beta_0 = 0
     StepDev* sd = host_steps(b);
     for (int r = 0; r < nruns; ++r) {
@@ -1112,7 +1143,7 @@ static pa_status batch_init(const pa_params* runs, const pa_schedule* sched, int
         h.R_cur = h.p.R;
         h.lnZ = (double)(h.p.L * h.p.L) * std::log(2.0);
     }
-    st = replay(b, b->lo.tables - b->lo.steps, false);  // initial states: no resampling
+    st = run_step(b, b->lo.tables - b->lo.steps, false);  // initial states: no resampling
     if (st != PA_OK) return st;
     for (int r = 0; r < nruns; ++r) {
         read_stats(b, r);
@@ -1208,7 +1239,7 @@ pa_status pa_batch_step(pa_batch* b, int32_t* n_active)
         bool need_copy = false;
         for (int r = 0; r < b->nruns; ++r)
             need_copy = need_copy || (sd[r].active && sd[r].resample && sd[r].nsweeps == 0);
-        const pa_status st = replay(b, (b->lo.tables - b->lo.steps) + (size_t)o * 4, need_copy);
+        const pa_status st = run_step(b, (b->lo.tables - b->lo.steps) + (size_t)o * 4, need_copy);
         if (st != PA_OK) return st;
         const ResultDev* res = reinterpret_cast<const ResultDev*>(b->h_download);
         for (int r = 0; r < b->nruns; ++r) {
@@ -1249,6 +1280,7 @@ pa_status pa_batch_run(pa_batch* b)
         const pa_status st = pa_batch_step(b, &n);
         if (st != PA_OK) return st;
     }
+    BCHK(hipStreamSynchronize(b->stream));
     return PA_OK;
 }
 
@@ -1403,10 +1435,6 @@ pa_status pa_batch_learned_stats(const pa_batch* b, int32_t run, int32_t* propos
 pa_status pa_batch_free(pa_batch* b)
 {
     if (!b) return PA_OK;
-    if (b->exec) (void)hipGraphExecDestroy(b->exec);
-    if (b->graph) (void)hipGraphDestroy(b->graph);
-    if (b->exec_nocopy) (void)hipGraphExecDestroy(b->exec_nocopy);
-    if (b->graph_nocopy) (void)hipGraphDestroy(b->graph_nocopy);
     if (b->h_steps) (void)hipHostFree(b->h_steps);
     if (b->h_download) (void)hipHostFree(b->h_download);
     if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);

@@ -6,6 +6,7 @@
 // use a fixed operation order over ascending bins and are compiled without
 // contraction, so they are reproducible bit for bit.
 #pragma once
+#include <chrono>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -16,6 +17,24 @@
 
 namespace pa {
 namespace host {
+
+// Polls `there` for at most kSpinUs, which covers a short step; the caller
+// falls back to a wait on the stream or on an event, which also reports an
+// error of the device.
+constexpr int kSpinUs = 1000;
+
+template <class F>
+bool spin_for(F there)
+{
+    const auto t0 = std::chrono::steady_clock::now();
+    for (;;) {
+        for (int i = 0; i < 64; ++i) {
+            if (there()) return true;
+            __builtin_ia32_pause();
+        }
+        if (std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(kSpinUs)) return false;
+    }
+}
 
 // Occupied window [bmin, bmax] of an energy histogram n[0..N].
 struct Hist {

@@ -74,6 +74,7 @@ struct SweepArgs {
 };
 
 constexpr int kBlock = 256;     // threads per block of the population kernels
+constexpr int kScanFreeBlocks = 1024;  // blocks of copy counts up to which the scatter sums their totals itself
 
 // Update rule of the sweep kernels.
 enum Update : int {

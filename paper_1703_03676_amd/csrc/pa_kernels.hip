@@ -27,21 +27,6 @@ using namespace pa::dev;
 // (bin b at byte 64 + 4 b), so the host reads them after the kernel without a
 // separate copy.
 // ---------------------------------------------------------------------------
-// Marks a publication as complete: `seq` in the place of the block counter
-// (host[3]), after every host write of the block.  The host polls it instead of
-// waiting for the kernel's end, the marker packet behind it and its signal:
-// a step of L = 128, R = 10000, theta = 1 takes 60.8 us instead of 63.1, one of
-// L = 16, R = 1000 27.4 instead of 29.2.  (With the system-wide fence in every
-// wave the 16 waves of the gather took 5 us longer.)
-__device__ __forceinline__ void publish_seq(uint32_t* host, uint32_t seq)
-{
-    // each wave waits for its own writes (they are uncached); only the first
-    // pays for the release, which writes its L2 back
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(host + 3, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 // Sums the partials into *st, clears the block counter and, with `host`,
 // publishes the statistics block and the histogram window there.  Called by
 // every thread of the one block that finalises.
@@ -66,7 +51,6 @@ __global__ __launch_bounds__(kBlock) void stats_kernel(const int32_t* __restrict
                                                        int32_t nbins, int record, DevMhr mhr, StatsPart* parts,
                                                        DevStats* st, uint32_t* __restrict__ host, uint32_t seq)
 {
-    __shared__ uint32_t last;
     if (n_dev) n = min(n, (int32_t)*n_dev);
     const int nparts = (n + kBlock - 1) / kBlock;
     if (nparts == 0) {  // empty population (a refused step): block 0 publishes the empty statistics
@@ -81,12 +65,7 @@ __global__ __launch_bounds__(kBlock) void stats_kernel(const int32_t* __restrict
         stats_block(E, M, n, N, c * kBlock, hist, nbins, record != 0, mhr, &parts[c]);
         __syncthreads();  // the LDS tables are reused by the next chunk
     }
-    __threadfence();  // this block's partials and histogram updates, device-wide
-    __syncthreads();
-    if (threadIdx.x == 0) last = (atomicAdd(&st->done, 1u) == (uint32_t)(nblk - 1)) ? 1u : 0u;
-    __syncthreads();
-    if (!last) return;  // uniform per block
-    __threadfence();    // every other block's updates are visible to this one
+    if (!finishes_last(&st->done, (uint32_t)nblk)) return;  // uniform per block
     stats_publish(parts, nparts, st, hist, N, host, seq);
 }
 
@@ -170,7 +149,6 @@ __global__ __launch_bounds__(kMomentThreads) void moments_kernel(const int32_t* 
                                                                 const int32_t* __restrict__ M, int32_t n,
                                                                 DevStats* parts, DevStats* st)
 {
-    __shared__ uint32_t last;
     const int t = (int)threadIdx.x;
     uint64_t sE = 0, sE2 = 0, sA = 0, sM2 = 0, m4lo = 0, m4hi = 0;
     int32_t emin = 0x7FFFFFFF, emax = (int32_t)0x80000000;
@@ -186,13 +164,7 @@ __global__ __launch_bounds__(kMomentThreads) void moments_kernel(const int32_t* 
         emax = max(emax, (int32_t)e);
     }
     stats_block_total<kMomentThreads>(sE, sE2, sA, sM2, m4lo, m4hi, emin, emax, parts + blockIdx.x);
-    if (t == 0) {
-        __threadfence();  // this block's partials, device-wide
-        last = (atomicAdd(&st->done, 1u) == gridDim.x - 1u) ? 1u : 0u;
-    }
-    __syncthreads();
-    if (!last) return;  // uniform per block
-    __threadfence();    // every other block's partials are visible to this one
+    if (!finishes_last(&st->done, gridDim.x)) return;  // uniform per block
     sE = sE2 = sA = sM2 = m4lo = m4hi = 0;
     emin = 0x7FFFFFFF;
     emax = (int32_t)0x80000000;

@@ -33,7 +33,6 @@ hipError_t launch_counts(const int32_t* E, int32_t n, int32_t N, int32_t bmin, i
 // The total also goes to *host_total (device view of pinned host memory).
 // Up to kScanFreeBlocks blocks of counts, each scatter block sums the totals
 // before it; beyond, a single-block scan of the totals runs first.
-constexpr int kScanFreeBlocks = 1024;
 hipError_t launch_scatter(const uint32_t* counts, uint32_t* bsum, int32_t n, int32_t cap, uint32_t* parent,
                           DevStats* st, uint32_t* hist, int32_t nbins, uint32_t* host_total, hipStream_t s);
 // Both of these and the reading of the tables (tbl: device view of pinned host

@@ -210,6 +210,43 @@ __device__ __forceinline__ void stats_block(const int32_t* __restrict__ E, const
     }
 }
 
+// Marks a publication as complete: `seq` in the place of the block counter
+// (host[3]), after every host write of the block.  The host polls it instead of
+// waiting for the kernel's end, the marker packet behind it and its signal:
+// a step of L = 128, R = 10000, theta = 1 takes 60.8 us instead of 63.1, one of
+// L = 16, R = 1000 27.4 instead of 29.2.  (With the system-wide fence in every
+// wave the 16 waves of the gather took 5 us longer.)
+__device__ __forceinline__ void publish_seq(uint32_t* host, uint32_t seq)
+{
+    // each wave waits for its own writes (they are uncached); only the first
+    // pays for the release, which writes its L2 back
+    __threadfence_block();  // no write moves below
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(host + 3, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Whether this block is the last of `blocks` that count themselves in *done; the
+// writes of all of them are then visible to it.  Every thread waits for its own
+// writes; the device-wide fences, each of which writes back or drops the
+// caches, are left to one wave (in all four waves a statistics launch over 12
+// runs took 15.5 us instead of 12.3, and a step of L = 16, R = 30000, theta = 1
+// 41 us instead of 36).
+__device__ __forceinline__ bool finishes_last(uint32_t* done, uint32_t blocks)
+{
+    __shared__ uint32_t last;
+    __threadfence_block();  // no write moves below
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        last = (atomicAdd(done, 1u) == blocks - 1u) ? 1u : 0u;
+        __threadfence();
+    }
+    __syncthreads();
+    return last != 0u;
+}
+
 // Sums the per-thread statistics of the first NT threads of a block into st
 // (energy range and moment sums; r_new and done are left as they are), and into
 // the block's LDS copy `sh` if given.  Called by every thread of the block.
