@@ -323,15 +323,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sweep_min_w
     a.t4l = st.t4l;
     a.init = st.init;
     const int wpb = (int)(blockDim.x >> 6);
+    a.one_round = (int)gridDim.x * wpb <= sweep_resident_waves<(L == kSmall ? 64 : L)>() ? 1 : 0;
     constexpr bool HB = U == pa::kHeatbath, LCG = U == pa::kLcg;
     if constexpr (L == kSmall) {
         switch (rd.L) {  // uniform
-        case 16: sweep_waves<16, INT8, HB, LCG>(a, it.blk * wpb, wpb, lds_dyn); break;
-        case 32: sweep_waves<32, INT8, HB, LCG>(a, it.blk * wpb, wpb, lds_dyn); break;
-        default: sweep_waves<64, INT8, HB, LCG>(a, it.blk * wpb, wpb, lds_dyn); break;
+        case 16: sweep_waves<16, INT8, HB, LCG>(a, it.blk * wpb, lds_dyn); break;
+        case 32: sweep_waves<32, INT8, HB, LCG>(a, it.blk * wpb, lds_dyn); break;
+        default: sweep_waves<64, INT8, HB, LCG>(a, it.blk * wpb, lds_dyn); break;
         }
     } else {
-        sweep_waves<L, INT8, HB, LCG>(a, it.blk * wpb, wpb, lds_dyn);
+        sweep_waves<L, INT8, HB, LCG>(a, it.blk * wpb, lds_dyn);
     }
 }
 

@@ -1031,11 +1031,43 @@ __device__ __forceinline__ void write_EM(const SweepArgs& a, const LaneInfo& li,
     if (a.acc) accumulate_stats<L>(a, li, e, m);
 }
 
+// Priority of a wave among those of its SIMD: lower the further its sweeps have
+// come.  Left to itself the SIMD issues from its oldest waves first, so these
+// finish early and the last ones run with too few others to hide their
+// latency: with every wave resident from the start, 7.8 of them per SIMD, L = 64
+// ran at 0.7 of the rate that a long queue of waves reaches.  Three steps keep the
+// waves of a SIMD together.  Where all waves fit the GPU at once (one_round)
+// the steps lie late, so that what remains after the last is short; where
+// waves queue for a place they lie early, as waves that end together leave
+// their SIMD to a last round that starts together and may be thin.  Launches
+// in ms without the priorities, with steps at 1/2, 1/4 and 1/8 of the sweeps
+// left, and at 3/4, 1/2 and 1/4: L = 16, R = 80000, theta = 100: 0.329, 0.271,
+// 0.283; L = 256, R = 3800, theta = 50: 1.57, 1.34, 1.39; L = 64, theta = 100,
+// R = 8000: 0.475, 0.413, 0.422; queueing: L = 128, R = 50000, theta = 20:
+// 1.61, 1.60, 1.57; R = 10000, theta = 50: 0.897, 0.856, 0.845; L = 64,
+// R = 100000, theta = 40: 1.753, 1.789, 1.749.  (Waves that each took several
+// replicas in turn, as many as fit, lost 22 % there: the oldest wave of each
+// SIMD ran through all of its own first.)
+struct Progress {
+    int l2, l1, l0;  // sweeps left at which it steps down
+    __device__ __forceinline__ Progress(int n, bool one_round)
+        : l2(one_round ? n / 2 : 3 * n / 4), l1(one_round ? n / 4 : n / 2), l0(one_round ? n / 8 : n / 4)
+    {
+        __builtin_amdgcn_s_setprio(3);
+    }
+    __device__ __forceinline__ void left(int n) const
+    {
+        if (n == l2) __builtin_amdgcn_s_setprio(2);
+        if (n == l1) __builtin_amdgcn_s_setprio(1);
+        if (n == l0) __builtin_amdgcn_s_setprio(0);
+    }
+};
+
 // Register-resident sweep: each lane owns one word per colour (L <= 64).
 // LCG: the in-line LCG variant; the word's seeds for both colours of a sweep
 // come from one Philox block (outputs x and y).
 template <int L, bool INT8, bool HB, bool LCG>
-__device__ __forceinline__ void sweep_regs(const SweepArgs& a, const LaneInfo& li)
+__device__ __forceinline__ void sweep_regs(const SweepArgs& a, const LaneInfo& li, const Progress& progress)
 {
     using Gm = Geo<L>;
     static_assert(Gm::K == 1, "one word per lane");
@@ -1052,6 +1084,7 @@ __device__ __forceinline__ void sweep_regs(const SweepArgs& a, const LaneInfo& l
     const PhiloxKeys K = philox_keys(a.key0, a.key1);
     for (int t = 0; t < a.nsweeps; ++t) {
         const uint32_t g = a.g0 + (uint32_t)t;
+        progress.left(a.nsweeps - t);
         if constexpr (LCG) {
             const U4 P = philox10(v, g, li.j, a.tag | kStreamLcgSeed, a.key0, a.key1);
             half_sweep_lcg<L, 0>(s0, s1, li.lane, li.gl, P.x, a);
@@ -1169,7 +1202,7 @@ __device__ __forceinline__ void half_sweep_lds_lcg(const LdsRep<L>& rep, int gl,
 
 // The wave's LDS: replica [2][NW], then the tie queue.
 template <int L, bool INT8, bool HB, bool LCG>
-__device__ __forceinline__ void sweep_lds(const SweepArgs& a, uint32_t j, uint32_t* lds)
+__device__ __forceinline__ void sweep_lds(const SweepArgs& a, uint32_t j, uint32_t* lds, const Progress& progress)
 {
     using Gm = Geo<L>;
     static_assert(Gm::WIDE && Gm::RL % 2 == 0 && Gm::G == 64, "LDS path layout");
@@ -1194,6 +1227,7 @@ __device__ __forceinline__ void sweep_lds(const SweepArgs& a, uint32_t j, uint32
     const PhiloxKeys K = philox_keys(a.key0, a.key1);
     for (int t = 0; t < a.nsweeps; ++t) {
         const uint32_t g = a.g0 + (uint32_t)t;
+        progress.left(a.nsweeps - t);
         if constexpr (LCG) {
             half_sweep_lds_lcg<L, 0>(rep, gl, g, j, a);
             half_sweep_lds_lcg<L, 1>(rep, gl, g, j, a);
@@ -1224,11 +1258,25 @@ __device__ __forceinline__ void sweep_lds(const SweepArgs& a, uint32_t j, uint32
 // more than fit four waves per SIMD; holding the kernel to four (two values go
 // to scratch outside the inner loops) takes 1.59 ms per launch at R = 50000,
 // theta = 20, against 1.78 with three waves (2.10 before the keys, the tail by
-// planes and the plane block).
+// planes and the plane block).  The register path fits eight with at most a few
+// values of the set-up in scratch; at 65 to 68 registers it held seven, so that
+// 7500 waves no longer fitted at once (L = 32, R = 30000, theta = 50: 0.258 ms
+// against 0.221 in the int8 store, 0.269 against 0.236 with the heat bath; L =
+// 64, R = 7777, theta = 20, heat bath: 0.124 against 0.106).  The batch's kernel
+// over several lattice sizes is left to the compiler: held to eight it was no
+// faster.
 template <int L>
 constexpr int sweep_min_waves()
 {
-    return L == 128 ? 4 : 1;
+    return L == 128 ? 4 : (L >= 16 && L <= 64) ? 8 : 1;
+}
+
+// Waves of a sweep that the GPU holds at once: 256 CUs of 4 SIMDs, each with 8
+// waves of the register path or 4 of the LDS path.
+template <int L>
+constexpr int sweep_resident_waves()
+{
+    return 1024 * (Geo<L>::K == 1 ? 8 : 4);
 }
 
 // Threads per block of the single-run sweep kernel.
@@ -1245,12 +1293,13 @@ constexpr int sweep_block()
 // selects the heat-bath update instead of Metropolis; LCG the in-line LCG
 // variant of the Metropolis sweep.
 template <int L, bool INT8, bool HB, bool LCG = false>
-__device__ __forceinline__ void sweep_waves(const SweepArgs& a, int wave0, int wpb, uint32_t* lds)
+__device__ __forceinline__ void sweep_waves(const SweepArgs& a, int wave0, uint32_t* lds)
 {
     using Gm = Geo<L>;
-    const int lane = (int)(threadIdx.x & 63u), wib = (int)(threadIdx.x >> 6);
+    const int lane = (int)(threadIdx.x & 63u), wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wave = wave0 + wib;
     if (wave * Gm::RPWV >= a.n_rep) return;  // uniform per wave
+    const Progress progress(a.nsweeps, a.one_round != 0);
     if constexpr (Gm::K == 1) {
         LaneInfo li;
         li.lane = lane;
@@ -1259,10 +1308,10 @@ __device__ __forceinline__ void sweep_waves(const SweepArgs& a, int wave0, int w
         if constexpr (Gm::REPW == 1) jj = __builtin_amdgcn_readfirstlane(jj);
         li.j = (uint32_t)jj;
         li.valid = jj < a.n_rep;
-        sweep_regs<L, INT8, HB, LCG>(a, li);
+        sweep_regs<L, INT8, HB, LCG>(a, li, progress);
     } else {
         sweep_lds<L, INT8, HB, LCG>(a, (uint32_t)__builtin_amdgcn_readfirstlane(wave),
-                                    lds + wib * Gm::WAVE_LDS_WORDS);
+                                    lds + wib * Gm::WAVE_LDS_WORDS, progress);
     }
 }
 

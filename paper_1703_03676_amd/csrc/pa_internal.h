@@ -71,6 +71,7 @@ struct SweepArgs {
     AccSlot* acc;           // if set: the sweep's epilogue adds the population statistics to these
     uint32_t* acc_hist;     // kAccSlots slots and kAccHists histogram copies of nbins bins each
     int32_t nbins;
+    int32_t one_round;      // 1: every wave of the launch has a place on the GPU from its start (Progress)
 };
 
 constexpr int kBlock = 256;     // threads per block of the population kernels

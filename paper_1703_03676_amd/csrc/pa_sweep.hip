@@ -32,16 +32,17 @@ __attribute__((amdgpu_waves_per_eu(sweep_min_waves<L>(), 8))) void sweep_kernel(
     constexpr int WPB = sweep_block<L>() / 64;
     __shared__ __align__(16) uint32_t lds[Gm::lds_words(WPB) > 0 ? Gm::lds_words(WPB) : 1];
     if (a.n_dev) a.n_rep = min(a.n_rep, (int32_t)*a.n_dev);
-    sweep_waves<L, INT8, U == kHeatbath, U == kLcg>(a, (int)blockIdx.x * WPB, WPB, lds);
+    sweep_waves<L, INT8, U == kHeatbath, U == kLcg>(a, (int)blockIdx.x * WPB, lds);
 }
 
 template <int L, bool INT8, int U>
-hipError_t launch_sweep_t(const SweepArgs& a, hipStream_t s)
+hipError_t launch_sweep_t(SweepArgs a, hipStream_t s)
 {
     using Gm = Geo<L>;
     const int reps_per_block = (sweep_block<L>() / 64) * Gm::RPWV;
     const int blocks = (a.n_rep + reps_per_block - 1) / reps_per_block;
     if (blocks == 0) return hipSuccess;
+    a.one_round = blocks * (sweep_block<L>() / 64) <= sweep_resident_waves<L>() ? 1 : 0;
     hipLaunchKernelGGL((sweep_kernel<L, INT8, U>), dim3(blocks), dim3(sweep_block<L>()), 0, s, a);
     return hipGetLastError();
 }
