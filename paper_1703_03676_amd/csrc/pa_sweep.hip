@@ -36,9 +36,32 @@ __attribute__((amdgpu_waves_per_eu(sweep_min_waves<L>(), 8))) void sweep_kernel(
 }
 
 template <int L, bool INT8, int U>
+__global__ __launch_bounds__(64) void sweep_quads_kernel(SweepArgs a)
+{
+    if (a.n_dev) a.n_rep = min(a.n_rep, (int32_t)*a.n_dev);
+    if ((int)blockIdx.x * quad_replicas<L>() >= a.n_rep) return;
+    sweep_quads<L, INT8, U == kHeatbath>(a, (int)blockIdx.x);
+}
+
+// Waves of sweep_quads up to which it is taken, four per SIMD (without the
+// statistics in the epilogue, which it has none of).  Launches in ms, ordinary
+// path and this one: L = 16, theta = 50: R = 1000 0.088, 0.029; 8000 0.090,
+// 0.044; 16000 (4000 waves) 0.093, 0.078; 30000 0.103, 0.138.  L = 32, theta =
+// 20: R = 100 0.038, 0.014; 2000 0.040, 0.025; 4000 0.041, 0.033; 8000 0.046,
+// 0.057.
+constexpr int kQuadWaves = 4096;
+
+template <int L, bool INT8, int U>
 hipError_t launch_sweep_t(SweepArgs a, hipStream_t s)
 {
     using Gm = Geo<L>;
+    if constexpr (L <= 32 && U != kLcg) {
+        const int waves = (a.n_rep + quad_replicas<L>() - 1) / quad_replicas<L>();
+        if (waves > 0 && waves <= kQuadWaves && !a.acc && !a.init && a.nsweeps > 0) {
+            hipLaunchKernelGGL((sweep_quads_kernel<L, INT8, U>), dim3(waves), dim3(64), 0, s, a);
+            return hipGetLastError();
+        }
+    }
     const int reps_per_block = (sweep_block<L>() / 64) * Gm::RPWV;
     const int blocks = (a.n_rep + reps_per_block - 1) / reps_per_block;
     if (blocks == 0) return hipSuccess;
