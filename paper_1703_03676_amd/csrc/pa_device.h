@@ -1132,14 +1132,11 @@ struct QuadPlanes {
     }
 };
 
-template <int L, int C, bool HB>
-__device__ __forceinline__ void half_sweep_quads(uint32_t (&own)[1], const uint32_t (&oth)[1], int lane, uint32_t v,
-                                                 uint32_t g, uint32_t j, const SweepArgs& a, const PhiloxKeys& K,
-                                                 const QuadPlanes& T)
+// Word w of colour C after its half sweep.
+template <int C, bool HB>
+__device__ __forceinline__ uint32_t quad_word(uint32_t w, const Nb& n, int lane, uint32_t v, uint32_t g, uint32_t j,
+                                              const SweepArgs& a, const PhiloxKeys& K, const QuadPlanes& T)
 {
-    const Neighbours<L, C, 4> nb(oth, lane, 0);
-    const Nb n = nb.get(oth, 0);
-    const uint32_t w = own[0];
     const HalfBlocks blk{philox_half(2u * g + (uint32_t)C, j, a.key0), a.key0, a.key1, K};
     const U4 P = blk(4u * v + (uint32_t)(lane & 3), a.tag | kStreamSweepHigh);
     uint32_t x[4] = {P.x, P.y, P.z, P.w};
@@ -1183,7 +1180,16 @@ __device__ __forceinline__ void half_sweep_quads(uint32_t (&own)[1], const uint3
         const uint32_t tl = ((cls1 >> b) & 1u) ? a.t2l : a.t4l;
         if (lo < tl) acc |= 1u << b;
     }
-    own[0] = w ^ acc ^ neg;
+    return w ^ acc ^ neg;
+}
+
+template <int L, int C, bool HB>
+__device__ __forceinline__ void half_sweep_quads(uint32_t (&own)[1], const uint32_t (&oth)[1], int lane, uint32_t v,
+                                                 uint32_t g, uint32_t j, const SweepArgs& a, const PhiloxKeys& K,
+                                                 const QuadPlanes& T)
+{
+    const Neighbours<L, C, 4> nb(oth, lane, 0);
+    own[0] = quad_word<C, HB>(own[0], nb.get(oth, 0), lane, v, g, j, a, K, T);
 }
 
 // Replicas of a wave of sweep_quads.
@@ -1229,6 +1235,84 @@ __device__ __forceinline__ void sweep_quads(const SweepArgs& a, int wave)
     }
 }
 
+// Adds the per-lane counts of the W waves of a replica in lanes of the first
+// wave, whose lane i < W returns with the sum of wave i; false in the others.
+// red: W pairs of LDS words that nothing else uses any more.
+template <int W>
+__device__ __forceinline__ bool first_wave_sums(uint32_t* red, int lane, int wv, uint32_t& anti, uint32_t& downs)
+{
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        anti += (uint32_t)__shfl_xor((int)anti, off);
+        downs += (uint32_t)__shfl_xor((int)downs, off);
+    }
+    if (lane == 0) {
+        red[2 * wv] = anti;
+        red[2 * wv + 1] = downs;
+    }
+    __syncthreads();
+    anti = (lane < W) ? red[2 * lane] : 0u;
+    downs = (lane < W) ? red[2 * lane + 1] : 0u;
+    return wv == 0;
+}
+
+// The same for L = 64, whose 64 words take the four waves of a block: the words
+// stand in LDS too (lds: [2][64]), where their vertical neighbours are read; the
+// waves meet once per half sweep.
+template <int C>
+__device__ __forceinline__ Nb row_neighbours64(const uint32_t* oth, uint32_t v)
+{
+    Nb n;
+    n.same = oth[v];
+    n.up = oth[(v + 63u) & 63u];
+    n.dn = oth[(v + 1u) & 63u];
+    // (y + C) even: horizontal neighbour at h-1, else at h+1
+    n.side = __builtin_amdgcn_alignbit(n.same, n.same, (((v + (uint32_t)C) & 1u) == 0u) ? 31u : 1u);
+    return n;
+}
+
+template <bool INT8, bool HB>
+__device__ __forceinline__ void sweep_quads64(const SweepArgs& a, uint32_t j, uint32_t* lds)
+{
+    const int lane = (int)(threadIdx.x & 63u), kk = lane & 3;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t v = threadIdx.x >> 2;
+    uint32_t* c0 = lds;
+    uint32_t* c1 = lds + 64;
+    uint32_t w0, w1;
+    load_word<64, INT8>(replica_in<64, INT8>(a, j), v, w0, w1);
+    if (kk == 0) {
+        c0[v] = w0;
+        c1[v] = w1;
+    }
+    const PhiloxKeys K = philox_keys(a.key0, a.key1);
+    const QuadPlanes T(a, kk);
+    __syncthreads();
+    for (int t = 0; t < a.nsweeps; ++t) {
+        const uint32_t g = a.g0 + (uint32_t)t;
+        w0 = quad_word<0, HB>(w0, row_neighbours64<0>(c1, v), lane, v, g, j, a, K, T);
+        if (kk == 0) c0[v] = w0;
+        __syncthreads();
+        w1 = quad_word<1, HB>(w1, row_neighbours64<1>(c0, v), lane, v, g, j, a, K, T);
+        if (kk == 0) c1[v] = w1;
+        __syncthreads();
+    }
+    const Nb n = row_neighbours64<0>(c1, v);
+    uint32_t anti = __popc(w0 ^ n.up) + __popc(w0 ^ n.dn) + __popc(w0 ^ n.same) + __popc(w0 ^ n.side);
+    uint32_t downs = __popc(w0) + __popc(w1);
+    if (kk == 0) {
+        store_word<64, INT8>(a, j, v, w0, w1);
+    } else {
+        anti = downs = 0u;
+    }
+    if (!first_wave_sums<4>(lds + 128, lane, wv, anti, downs)) return;
+    LaneInfo li;
+    li.lane = li.gl = lane;
+    li.j = j;
+    li.valid = true;
+    write_EM<64>(a, li, anti, downs);
+}
+
 // LDS-resident sweep for rows of whole words (L >= 128): one wave owns one
 // replica; word (k, lane) of a colour sits at k * 64 + lane, so the 64 lanes
 // touch 64 consecutive words for every k.
@@ -1259,18 +1343,32 @@ struct LdsRep {
     }
 };
 
+// Orders the LDS accesses of the W waves that share a replica.
+template <int W>
+__device__ __forceinline__ void replica_lds_sync()
+{
+    if constexpr (W == 1)
+        wave_lds_sync();
+    else
+        __syncthreads();
+}
+
 // One colour of a sweep on the LDS path: the lane's K words in chunks of
-// SLOTS, each chunk followed by the wave's tie resolution.
-template <int L, int C, bool HB>
-__device__ __forceinline__ void half_sweep_lds(const LdsRep<L>& rep, int gl, uint32_t g, uint32_t j,
+// SLOTS, each chunk followed by the wave's tie resolution.  With W waves to the
+// replica, wave wv takes words [wv K / W, (wv + 1) K / W) of every lane.
+template <int L, int C, bool HB, int W>
+__device__ __forceinline__ void half_sweep_lds(const LdsRep<L>& rep, int gl, int wv, uint32_t g, uint32_t j,
                                                const SweepArgs& a, const PhiloxKeys& K, uint32_t* queue)
 {
     using Gm = Geo<L>;
-    constexpr int S = Gm::SLOTS, NG = 4;  // groups of four words share the branches of decide8_group
-    static_assert(Gm::K % S == 0 && S % NG == 0, "slots divide the words of a lane");
+    constexpr int KW = Gm::K / W;
+    constexpr int S = KW < Gm::SLOTS ? KW : Gm::SLOTS;
+    constexpr int NG = S < 4 ? S : 4;  // groups of four words share the branches of decide8_group
+    static_assert(Gm::K % W == 0 && KW % S == 0 && S % NG == 0, "slots divide the words of a lane");
     const PhiloxHalf h = philox_half(2u * g + (uint32_t)C, j, a.key0);
+    const int kbase = W == 1 ? 0 : wv * KW;
 #pragma unroll 1
-    for (int k0 = 0; k0 < Gm::K; k0 += S) {
+    for (int k0 = kbase; k0 < kbase + KW; k0 += S) {
         uint32_t nq = 0u;
 #pragma unroll
         for (int s0 = 0; s0 < S; s0 += NG) {
@@ -1293,7 +1391,11 @@ __device__ __forceinline__ void half_sweep_lds(const LdsRep<L>& rep, int gl, uin
                 rep.at(C, k0 + s0 + i, gl) ^=
                     decide_word_tail<HB>((uint32_t)(gl * Gm::K + k0 + s0 + i), t, c, m, h, a, K);
             };
-            queue_ties<NG>(tie, cls1, ng, id, a, queue, nq, own);
+            if constexpr (KW == 1) {
+                if (tie[0]) own(0, tie[0], cls1[0], ng[0]);
+            } else {
+                queue_ties<NG>(tie, cls1, ng, id, a, queue, nq, own);
+            }
         }
         if (nq == 0u) continue;
         const auto half = [&](uint32_t w, uint32_t* v) {
@@ -1305,7 +1407,7 @@ __device__ __forceinline__ void half_sweep_lds(const LdsRep<L>& rep, int gl, uin
         };
         resolve_ties<HB>(nq, a, K, queue, gl, half, apply);
     }
-    wave_lds_sync();
+    replica_lds_sync<W>();
 }
 
 // One colour of an LCG sweep on the LDS path: every word of the lane in turn,
@@ -1326,18 +1428,22 @@ __device__ __forceinline__ void half_sweep_lds_lcg(const LdsRep<L>& rep, int gl,
     wave_lds_sync();
 }
 
-// The wave's LDS: replica [2][NW], then the tie queue.
-template <int L, bool INT8, bool HB, bool LCG>
-__device__ __forceinline__ void sweep_lds(const SweepArgs& a, uint32_t j, uint32_t* lds, const Progress& progress)
+// The LDS of the W waves of a replica: the replica [2][NW], then W tie queues.
+template <int L, bool INT8, bool HB, bool LCG, int W = 1>
+__device__ __forceinline__ void sweep_lds(const SweepArgs& a, uint32_t j, uint32_t* lds, const Progress& progress,
+                                          int wv = 0)
 {
+    static_assert(W == 1 || !LCG, "the LCG variant has one wave per replica");
     using Gm = Geo<L>;
     static_assert(Gm::WIDE && Gm::RL % 2 == 0 && Gm::G == 64, "LDS path layout");
     const LdsRep<L> rep{lds};
-    uint32_t* queue = lds + 2 * Gm::NW;
+    uint32_t* queue = lds + 2 * Gm::NW + wv * kTieQueueWords;
     const int gl = (int)(threadIdx.x & 63u);
     const uint8_t* in = a.init ? nullptr : replica_in<L, INT8>(a, j);
+    constexpr int KW = Gm::K / W;
+    const int kbase = W == 1 ? 0 : wv * KW;
 #pragma unroll 1
-    for (int k = 0; k < Gm::K; ++k) {
+    for (int k = kbase; k < kbase + KW; ++k) {
         const uint32_t v = (uint32_t)(gl * Gm::K + k);
         uint32_t w0, w1;
         if (a.init) {
@@ -1349,7 +1455,7 @@ __device__ __forceinline__ void sweep_lds(const SweepArgs& a, uint32_t j, uint32
         rep.at(0, k, gl) = w0;
         rep.at(1, k, gl) = w1;
     }
-    wave_lds_sync();
+    replica_lds_sync<W>();
     const PhiloxKeys K = philox_keys(a.key0, a.key1);
     for (int t = 0; t < a.nsweeps; ++t) {
         const uint32_t g = a.g0 + (uint32_t)t;
@@ -1358,18 +1464,21 @@ __device__ __forceinline__ void sweep_lds(const SweepArgs& a, uint32_t j, uint32
             half_sweep_lds_lcg<L, 0>(rep, gl, g, j, a);
             half_sweep_lds_lcg<L, 1>(rep, gl, g, j, a);
         } else {
-            half_sweep_lds<L, 0, HB>(rep, gl, g, j, a, K, queue);
-            half_sweep_lds<L, 1, HB>(rep, gl, g, j, a, K, queue);
+            half_sweep_lds<L, 0, HB, W>(rep, gl, wv, g, j, a, K, queue);
+            half_sweep_lds<L, 1, HB, W>(rep, gl, wv, g, j, a, K, queue);
         }
     }
     uint32_t anti = 0, downs = 0;
 #pragma unroll 1
-    for (int k = 0; k < Gm::K; ++k) {
+    for (int k = kbase; k < kbase + KW; ++k) {
         const Nb n = rep.template nb<0>(k, gl);
         const uint32_t w0 = rep.at(0, k, gl), w1 = rep.at(1, k, gl);
         anti += __popc(w0 ^ n.up) + __popc(w0 ^ n.dn) + __popc(w0 ^ n.same) + __popc(w0 ^ n.side);
         downs += __popc(w0) + __popc(w1);
         store_word<L, INT8>(a, j, (uint32_t)(gl * Gm::K + k), w0, w1);
+    }
+    if constexpr (W > 1) {
+        if (!first_wave_sums<W>(lds + 2 * Gm::NW, gl, wv, anti, downs)) return;
     }
     LaneInfo li;
     li.lane = gl;

@@ -7,7 +7,9 @@
 // of word q >> 5; bit set = spin -1).  A wave owns whole replicas and keeps
 // them on chip for all requested sweeps: in VGPRs for L <= 64 (vertical
 // neighbours cross lanes by shuffle, horizontal ones are funnel shifts), in
-// LDS for L >= 128.  The Metropolis decision for all 32 sites of a word is
+// LDS for L >= 128; in small launches four lanes share a word (L <= 64) or four
+// waves a replica (L >= 64).
+// The Metropolis decision for all 32 sites of a word is
 // bit-sliced: the uniform of each site is compared to the integer threshold
 // one bit plane at a time (16 planes from four Philox blocks, high bit first).
 // For L <= 64 the planes stop as soon as no site of the wave is undecided; for
@@ -43,6 +45,39 @@ __global__ __launch_bounds__(64) void sweep_quads_kernel(SweepArgs a)
     sweep_quads<L, INT8, U == kHeatbath>(a, (int)blockIdx.x);
 }
 
+// One replica per block of four waves: L = 64 by sweep_quads64, L >= 128 by the
+// LDS path with the replica shared.  Few replicas leave most SIMDs empty and the
+// others with one wave, whose time is its number of instructions; four waves
+// each have a quarter of them, for a barrier per half sweep.
+constexpr int kReplicaWaves = 4;
+
+template <int L, bool INT8, int U>
+__global__ __launch_bounds__(64 * kReplicaWaves) void sweep_shared_kernel(SweepArgs a)
+{
+    constexpr int W = kReplicaWaves;
+    constexpr bool HB = U == kHeatbath;
+    __shared__ __align__(16) uint32_t lds[L == 64 ? 128 + 2 * W : 2 * Geo<L>::NW + W * kTieQueueWords];
+    if (a.n_dev) a.n_rep = min(a.n_rep, (int32_t)*a.n_dev);
+    if ((int)blockIdx.x >= a.n_rep) return;
+    if constexpr (L == 64) {
+        sweep_quads64<INT8, HB>(a, blockIdx.x, lds);
+    } else {
+        const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        sweep_lds<L, INT8, HB, false, W>(a, blockIdx.x, lds, Progress(a.nsweeps, true), wv);
+    }
+}
+
+// Replicas up to which a launch takes it, five to eight waves per SIMD.  Launches
+// of 20 sweeps in us, one wave per replica and four:
+//   L = 64:  R = 300 46, 27; 1000 47, 39; 1500 49, 49; 2500 54, 69
+//   L = 128: R = 300 93, 62; 1000 94, 71; 1500 108, 82; 2500 126, 137
+//   L = 256: R = 300 303, 121; 1000 311, 225; 1500 376, 266; 2500 456, 464
+template <int L>
+constexpr int shared_replicas()
+{
+    return L == 64 ? 1280 : 2048;
+}
+
 // Waves of sweep_quads up to which it is taken, four per SIMD (without the
 // statistics in the epilogue, which it has none of).  Launches in ms, ordinary
 // path and this one: L = 16, theta = 50: R = 1000 0.088, 0.029; 8000 0.090,
@@ -59,6 +94,12 @@ hipError_t launch_sweep_t(SweepArgs a, hipStream_t s)
         const int waves = (a.n_rep + quad_replicas<L>() - 1) / quad_replicas<L>();
         if (waves > 0 && waves <= kQuadWaves && !a.acc && !a.init && a.nsweeps > 0) {
             hipLaunchKernelGGL((sweep_quads_kernel<L, INT8, U>), dim3(waves), dim3(64), 0, s, a);
+            return hipGetLastError();
+        }
+    }
+    if constexpr (L >= 64 && U != kLcg) {
+        if (a.n_rep > 0 && a.n_rep <= shared_replicas<L>() && !a.init && a.nsweeps > 0) {
+            hipLaunchKernelGGL((sweep_shared_kernel<L, INT8, U>), dim3(a.n_rep), dim3(64 * kReplicaWaves), 0, s, a);
             return hipGetLastError();
         }
     }
