@@ -262,7 +262,10 @@ pa_status pa_download_counts(pa_run* r, uint32_t* counts, int32_t* n);
  * entries), every lane decides its own tied sites instead.  cap >= 0 lowers
  * the number of entries a wave may use before taking that second route (0:
  * always), so that tests reach it; values of 128 and above restore the
- * default.  Results do not depend on cap.
+ * default.  Results do not depend on cap.  (A launch sized for at most 2048
+ * replicas - R_i in pa_sweep, the capacity in pa_anneal - shares each replica
+ * among four waves; at L = 128 these have one word per lane and queue none, so
+ * cap has no effect there.)
  * Errors: PA_EINVAL (cap < 0), PA_ESTATE. */
 pa_status pa_set_tie_queue_cap(pa_run* r, int32_t cap);
 
