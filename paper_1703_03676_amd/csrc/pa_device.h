@@ -286,6 +286,13 @@ __device__ __forceinline__ uint32_t from_lane(uint32_t v, int lane, int delta)
     return (uint32_t)__shfl((int)v, src);
 }
 
+// Value held by lane CTRL of the same four lanes.
+template <int CTRL>
+__device__ __forceinline__ uint32_t quad_lane(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL * 0x55, 0xF, 0xF, true);
+}
+
 // Neighbour words (other colour) of one own word of colour C.
 struct Nb {
     uint32_t up, dn, same, side;
@@ -827,40 +834,55 @@ __device__ __forceinline__ void resolve_ties(uint32_t nq, const SweepArgs& a, co
     wave_lds_sync();
 }
 
-// Sign bits of 64 consecutive int8 spins -> (even-x bits, odd-x bits).
+// Sign bits of 16 consecutive int8 spins: the even-x ones in byte 0, the odd-x
+// ones in byte 1 (the bytes above are not meant).  Dword k puts its four sign
+// bits at bit 2k of the bytes of x; the even sites are then in bytes 0 and 2 and
+// the odd ones in 1 and 3, and the upper pair moves in between the lower one's
+// bits.
+__device__ __forceinline__ uint32_t pack16(const uint4& q)
+{
+    const uint32_t x = ((q.x >> 7) & 0x01010101u) | ((q.y >> 5) & 0x04040404u) | ((q.z >> 3) & 0x10101010u) |
+                       ((q.w >> 1) & 0x40404040u);
+    return x | (x >> 15);
+}
+
+// The reverse (bytes 2 and 3 of z are zero): each dword's four bits picked out
+// of x, one per byte, select the bytes +1 (0x01) or -1 (0xFF).
+__device__ __forceinline__ uint4 unpack16(uint32_t z)
+{
+    const uint32_t x = z | (z << 15);
+    uint32_t w[4];
+#pragma unroll
+    for (uint32_t k = 0; k < 4u; ++k) w[k] = __builtin_amdgcn_perm(0u, 0xFF01u, (x >> (2u * k)) & 0x01010101u);
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// Byte s of ev and od as unpack16 takes them (v_perm_b32: selector bytes 0-3
+// take from the second operand, 4-7 from the first, 12 is zero).
+__device__ __forceinline__ uint32_t byte_pair(uint32_t ev, uint32_t od, uint32_t s)
+{
+    return __builtin_amdgcn_perm(od, ev, 0x0C0C0400u + 0x0101u * s);
+}
+
+// Sign bits of 64 consecutive int8 spins -> (even-x bits, odd-x bits), and back.
+// One running value per 16 bytes: as 64 single bits joined by an or-tree it held
+// up to 30 temporaries, which put other values of the register-path kernels
+// into scratch memory.
 __device__ __forceinline__ void pack64(const uint4* src, uint32_t& ev, uint32_t& od)
 {
-    ev = 0;
-    od = 0;
+    uint32_t z[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint4 q = src[i];
-        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int p = 2 * (4 * i + k);
-            ev |= ((w[k] >> 7) & 1u) << p;
-            ev |= ((w[k] >> 23) & 1u) << (p + 1);
-            od |= ((w[k] >> 15) & 1u) << p;
-            od |= ((w[k] >> 31) & 1u) << (p + 1);
-        }
-    }
+    for (int i = 0; i < 4; ++i) z[i] = pack16(src[i]);
+    const uint32_t lo = __builtin_amdgcn_perm(z[1], z[0], 0x05010400u);  // even 0, even 1, odd 0, odd 1
+    const uint32_t hi = __builtin_amdgcn_perm(z[3], z[2], 0x05010400u);
+    ev = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+    od = __builtin_amdgcn_perm(hi, lo, 0x07060302u);
 }
 
 __device__ __forceinline__ void unpack64(uint32_t ev, uint32_t od, uint4* dst)
 {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        uint32_t w[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int p = 2 * (4 * i + k);
-            const uint32_t m = ((ev >> p) & 1u) * 0xFEu | ((od >> p) & 1u) * 0xFE00u |
-                               ((ev >> (p + 1)) & 1u) * 0xFE0000u | ((od >> (p + 1)) & 1u) * 0xFE000000u;
-            w[k] = 0x01010101u | m;
-        }
-        dst[i] = make_uint4(w[0], w[1], w[2], w[3]);
-    }
+    for (uint32_t i = 0; i < 4u; ++i) dst[i] = unpack16(byte_pair(ev, od, i));
 }
 
 // Row-parity blend between the even-x / odd-x bits of a 64-site chunk and the
@@ -882,6 +904,21 @@ struct LaneInfo {
     uint32_t j;
     bool valid;
 };
+
+// Lane of thread `thread` in the wave `wave` of a run (register path).
+template <int L>
+__device__ __forceinline__ LaneInfo lane_info(const SweepArgs& a, int wave, uint32_t thread)
+{
+    using Gm = Geo<L>;
+    LaneInfo li;
+    li.lane = (int)(thread & 63u);
+    li.gl = li.lane % Gm::G;
+    int j = wave * Gm::REPW + li.lane / Gm::G;
+    if constexpr (Gm::REPW == 1) j = __builtin_amdgcn_readfirstlane(j);
+    li.j = (uint32_t)j;
+    li.valid = j < a.n_rep;
+    return li;
+}
 
 // Initial-state word (stream INIT): the INIT output word p >> 5 with
 // p = c N/2 + q is exactly the 32-site word (c, v) of the bit store.
@@ -941,6 +978,37 @@ __device__ __forceinline__ void store_word(const SweepArgs& a, uint32_t j, uint3
         uint32_t* base = reinterpret_cast<uint32_t*>(a.spin + (size_t)j * Gm::BITS_BYTES);
         base[v] = w0;
         base[Gm::NW + v] = w1;
+    }
+}
+
+// Stores the words of a wave's replicas in the int8 store (register path, G = NW
+// lanes to a replica), 16 bytes per lane and access: access i of lane l covers
+// the l-th 16 sites of the i-th quarter of the wave's 64 words, so that 64 lanes
+// write 1024 consecutive bytes of a replica (of four, for L = 16).  One exchange
+// brings word 16 i + l / 4 to the lane of its quad with l mod 4 = i, and the quad
+// shares it from there.  Bound by memory in launches of few sweeps, where the
+// partial lines of a lane writing the 64 bytes of its own word cost most.  In us,
+// every lane its own word and so: one sweep of L = 32, R = 100000 48.3, 36.3;
+// L = 64, R = 50000 83.3, 64.3; L = 16, R = 400000 47.8, 37.0; 20 sweeps of
+// L = 32, R = 12000 48.1, 48.1.  The load keeps a word per lane: in this order
+// it took 41 us where that took 36 (L = 32, R = 100000), as the words of a launch
+// then arrive all at once, and its waves store all at once.
+template <int L>
+__device__ __forceinline__ void store_wave_int8(const SweepArgs& a, int wave, int lane, uint32_t v, uint32_t w0,
+                                                uint32_t w1)
+{
+    const uint32_t em = even_row_mask<L>(v);
+    const int from = 16 * (lane & 3) + (lane >> 2);  // the word this lane keeps
+    const uint32_t ev = (uint32_t)__shfl((int)((w0 & em) | (w1 & ~em)), from);
+    const uint32_t od = (uint32_t)__shfl((int)((w1 & em) | (w0 & ~em)), from);
+    const uint32_t e[4] = {quad_lane<0>(ev), quad_lane<1>(ev), quad_lane<2>(ev), quad_lane<3>(ev)};
+    const uint32_t o[4] = {quad_lane<0>(od), quad_lane<1>(od), quad_lane<2>(od), quad_lane<3>(od)};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        constexpr int CH = Geo<L>::N / 16;  // 16-byte chunks of a replica
+        const int c = 64 * i + lane, j = wave * Geo<L>::REPW + c / CH;
+        const uint4 q = unpack16(byte_pair(e[i], o[i], (uint32_t)lane & 3u));
+        if (j < a.n_rep) reinterpret_cast<uint4*>(a.spin + (size_t)j * Geo<L>::N)[c % CH] = q;
     }
 }
 
@@ -1068,11 +1136,12 @@ struct Progress {
 // LCG: the in-line LCG variant; the word's seeds for both colours of a sweep
 // come from one Philox block (outputs x and y).
 template <int L, bool INT8, bool HB, bool LCG>
-__device__ __forceinline__ void sweep_regs(const SweepArgs& a, const LaneInfo& li, const Progress& progress)
+__device__ __forceinline__ void sweep_regs(const SweepArgs& a, int wave, const Progress& progress)
 {
     using Gm = Geo<L>;
     static_assert(Gm::K == 1, "one word per lane");
-    const uint32_t v = (uint32_t)li.gl;
+    LaneInfo li = lane_info<L>(a, wave, threadIdx.x);
+    uint32_t v = (uint32_t)li.gl;
     uint32_t s0[1], s1[1];
     if (a.init) {
         s0[0] = init_word<L>(0, v, li.j, a);
@@ -1095,12 +1164,22 @@ __device__ __forceinline__ void sweep_regs(const SweepArgs& a, const LaneInfo& l
             half_sweep<L, 1, HB>(s1, s0, li.lane, li.gl, g, li.j, a, K);
         }
     }
+    // the replica's number and its addresses are taken from the thread's number
+    // again: kept through the sweeps they need more registers than eight waves
+    // leave, and went to scratch memory
+    uint32_t thread = threadIdx.x;
+    __asm__("" : "+v"(thread));
+    li = lane_info<L>(a, wave, thread);
+    v = (uint32_t)li.gl;
     const Neighbours<L, 0> nb(s1, li.lane, li.gl);
     const Nb n = nb.get(s1, 0);
     const uint32_t anti = __popc(s0[0] ^ n.up) + __popc(s0[0] ^ n.dn) + __popc(s0[0] ^ n.same) + __popc(s0[0] ^ n.side);
     const uint32_t downs = __popc(s0[0]) + __popc(s1[0]);
     write_EM<L>(a, li, anti, downs);
-    if (li.valid) store_word<L, INT8>(a, li.j, v, s0[0], s1[0]);
+    if constexpr (INT8)
+        store_wave_int8<L>(a, wave, li.lane, v, s0[0], s1[0]);
+    else if (li.valid)
+        store_word<L, INT8>(a, li.j, v, s0[0], s1[0]);
 }
 
 
@@ -1113,12 +1192,6 @@ __device__ __forceinline__ void sweep_regs(const SweepArgs& a, const LaneInfo& l
 // planes give the sites below (lt) and equal to (eq) the threshold there, which
 // are then joined over the quad, high planes first.  The results are those of
 // sweep_regs.  L = 16, R = 1000, ten sweeps: 19.8 -> 7.9 us.
-template <int CTRL>
-__device__ __forceinline__ uint32_t quad_lane(uint32_t v)
-{
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL * 0x55, 0xF, 0xF, true);
-}
-
 struct QuadPlanes {
     uint32_t m2[4], m4[4];  // the lane's four bits of T_2 and T_4 as masks
     __device__ __forceinline__ QuadPlanes(const SweepArgs& a, int kk)
@@ -1493,13 +1566,13 @@ __device__ __forceinline__ void sweep_lds(const SweepArgs& a, uint32_t j, uint32
 // more than fit four waves per SIMD; holding the kernel to four (two values go
 // to scratch outside the inner loops) takes 1.59 ms per launch at R = 50000,
 // theta = 20, against 1.78 with three waves (2.10 before the keys, the tail by
-// planes and the plane block).  The register path fits eight with at most a few
-// values of the set-up in scratch; at 65 to 68 registers it held seven, so that
-// 7500 waves no longer fitted at once (L = 32, R = 30000, theta = 50: 0.258 ms
-// against 0.221 in the int8 store, 0.269 against 0.236 with the heat bath; L =
-// 64, R = 7777, theta = 20, heat bath: 0.124 against 0.106).  The batch's kernel
-// over several lattice sizes is left to the compiler: held to eight it was no
-// faster.
+// planes and the plane block).  The register path fits eight without
+// scratch memory; at 65 to 68 registers it held seven, so that 7500 waves no
+// longer fitted at once (seven and eight waves, and now: L = 32, R = 30000, theta =
+// 50: 0.258, 0.221, 0.217 ms in the int8 store, 0.269, 0.236, 0.215 with the
+// heat bath; L = 64, R = 7777, theta = 20, heat bath: 0.124, 0.106, 0.092).
+// The batch's kernel over several lattice sizes is left to the compiler: held to
+// eight it was no faster.
 template <int L>
 constexpr int sweep_min_waves()
 {
@@ -1531,19 +1604,12 @@ template <int L, bool INT8, bool HB, bool LCG = false>
 __device__ __forceinline__ void sweep_waves(const SweepArgs& a, int wave0, uint32_t* lds)
 {
     using Gm = Geo<L>;
-    const int lane = (int)(threadIdx.x & 63u), wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wave = wave0 + wib;
     if (wave * Gm::RPWV >= a.n_rep) return;  // uniform per wave
     const Progress progress(a.nsweeps, a.one_round != 0);
     if constexpr (Gm::K == 1) {
-        LaneInfo li;
-        li.lane = lane;
-        li.gl = lane % Gm::G;
-        int jj = wave * Gm::REPW + lane / Gm::G;
-        if constexpr (Gm::REPW == 1) jj = __builtin_amdgcn_readfirstlane(jj);
-        li.j = (uint32_t)jj;
-        li.valid = jj < a.n_rep;
-        sweep_regs<L, INT8, HB, LCG>(a, li, progress);
+        sweep_regs<L, INT8, HB, LCG>(a, wave, progress);
     } else {
         sweep_lds<L, INT8, HB, LCG>(a, (uint32_t)__builtin_amdgcn_readfirstlane(wave),
                                     lds + wib * Gm::WAVE_LDS_WORDS, progress);
