@@ -587,9 +587,34 @@ __device__ __forceinline__ uint32_t shift_in_le(uint32_t acc, uint32_t x, uint32
     return acc;
 }
 
+// The same for two outputs and both thresholds as one block, the comparisons
+// before the adds, so that no add waits for its own.  Between blocks of which one
+// writes a register and the next reads it the compiler puts a wait state: about
+// 50 in the 528 instructions of a sweep with a block per comparison.  They and
+// the waits are lost time where a wave has its SIMD to itself, and free
+// where others fill them; there the shorter blocks mix better with the
+// multiplications (20 sweeps of L = 64, R = 30000: 441 us by these, 459 by pairs).
+__device__ __forceinline__ void shift_in_pair(uint32_t& m2, uint32_t& m4, uint32_t x, uint32_t y, uint32_t t2,
+                                              uint32_t t4)
+{
+    uint64_t x2, x4, y2, y4;
+    __asm__("v_cmp_ge_u32_e64 %[x2], %[t2], %[x]\n\t"
+            "v_cmp_ge_u32_e64 %[x4], %[t4], %[x]\n\t"
+            "v_cmp_ge_u32_e64 %[y2], %[t2], %[y]\n\t"
+            "v_cmp_ge_u32_e64 %[y4], %[t4], %[y]\n\t"
+            "v_addc_co_u32_e64 %[m2], %[x2], %[m2], %[m2], %[x2]\n\t"
+            "v_addc_co_u32_e64 %[m4], %[x4], %[m4], %[m4], %[x4]\n\t"
+            "v_addc_co_u32_e64 %[m2], %[y2], %[m2], %[m2], %[y2]\n\t"
+            "v_addc_co_u32_e64 %[m4], %[y4], %[m4], %[m4], %[y4]"
+            : [m2] "+&v"(m2), [m4] "+&v"(m4), [x2] "=&s"(x2), [x4] "=&s"(x4), [y2] "=&s"(y2), [y4] "=&s"(y4)
+            : [x] "v"(x), [y] "v"(y), [t2] "s"(t2), [t4] "s"(t4));
+}
+
 // Metropolis acceptance mask of one 32-site word whose uniforms are the LCG
 // outputs after `seed`: a site flips if k <= 0, else if its uniform x is below
 // T_2 (one anti-aligned neighbour) or T_4 (none), i.e. x <= T - 1 (T >= 1).
+// PAIRS: by shift_in_pair.
+template <bool PAIRS>
 __device__ __forceinline__ uint32_t lcg_accept_mask(uint32_t w, const Nb& n, uint32_t seed, const SweepArgs& a)
 {
     const uint32_t d1 = w ^ n.up, d2 = w ^ n.dn, d3 = w ^ n.same, d4 = w ^ n.side;
@@ -600,22 +625,28 @@ __device__ __forceinline__ uint32_t lcg_accept_mask(uint32_t w, const Nb& n, uin
     const uint32_t t2m1 = (a.t2h << 16) + a.t2l - 1u;
     const uint32_t t4m1 = (a.t4h << 16) + a.t4l - 1u;
     uint32_t m2 = 0u, m4 = 0u;
+    const auto output = [seed](int i) { return (uint32_t)((uint64_t)lcg_mul(i) * seed + (uint64_t)lcg_add(i)); };
+    if constexpr (PAIRS) {
 #pragma unroll
-    for (int b = 31; b >= 0; --b) {
-        const uint32_t x = (uint32_t)((uint64_t)lcg_mul(b + 1) * seed + (uint64_t)lcg_add(b + 1));
-        m2 = shift_in_le(m2, x, t2m1);
-        m4 = shift_in_le(m4, x, t4m1);
+        for (int b = 32; b > 0; b -= 2) shift_in_pair(m2, m4, output(b), output(b - 1), t2m1, t4m1);
+    } else {
+#pragma unroll
+        for (int b = 32; b > 0; --b) {
+            const uint32_t x = output(b);
+            m2 = shift_in_le(m2, x, t2m1);
+            m4 = shift_in_le(m4, x, t4m1);
+        }
     }
     return ge2 | (any & ~ge2 & m2) | (~any & m4);
 }
 
 // One colour of the LCG sweep for the lane's one word (register path).
-template <int L, int C>
+template <int L, int C, bool PAIRS>
 __device__ __forceinline__ void half_sweep_lcg(uint32_t (&own)[1], const uint32_t (&oth)[1], int lane, int gl,
                                                uint32_t seed, const SweepArgs& a)
 {
     const Neighbours<L, C> nb(oth, lane, gl);
-    own[0] ^= lcg_accept_mask(own[0], nb.get(oth, 0), seed, a);
+    own[0] ^= lcg_accept_mask<PAIRS>(own[0], nb.get(oth, 0), seed, a);
 }
 
 template <int L, int C, bool HB>
@@ -1117,15 +1148,17 @@ __device__ __forceinline__ void write_EM(const SweepArgs& a, const LaneInfo& li,
 // R = 100000, theta = 40: 1.753, 1.789, 1.749.  (Waves that each took several
 // replicas in turn, as many as fit, lost 22 % there: the oldest wave of each
 // SIMD ran through all of its own first.)
+template <bool ON>
 struct Progress {
     int l2, l1, l0;  // sweeps left at which it steps down
     __device__ __forceinline__ Progress(int n, bool one_round)
         : l2(one_round ? n / 2 : 3 * n / 4), l1(one_round ? n / 4 : n / 2), l0(one_round ? n / 8 : n / 4)
     {
-        __builtin_amdgcn_s_setprio(3);
+        if constexpr (ON) __builtin_amdgcn_s_setprio(3);
     }
     __device__ __forceinline__ void left(int n) const
     {
+        if constexpr (!ON) return;
         if (n == l2) __builtin_amdgcn_s_setprio(2);
         if (n == l1) __builtin_amdgcn_s_setprio(1);
         if (n == l0) __builtin_amdgcn_s_setprio(0);
@@ -1135,11 +1168,12 @@ struct Progress {
 // Register-resident sweep: each lane owns one word per colour (L <= 64).
 // LCG: the in-line LCG variant; the word's seeds for both colours of a sweep
 // come from one Philox block (outputs x and y).
-template <int L, bool INT8, bool HB, bool LCG>
-__device__ __forceinline__ void sweep_regs(const SweepArgs& a, int wave, const Progress& progress)
+template <int L, bool INT8, bool HB, bool LCG, bool PRIO>
+__device__ __forceinline__ void sweep_regs(const SweepArgs& a, int wave)
 {
     using Gm = Geo<L>;
     static_assert(Gm::K == 1, "one word per lane");
+    const Progress<PRIO> progress(a.nsweeps, a.one_round != 0);
     LaneInfo li = lane_info<L>(a, wave, threadIdx.x);
     uint32_t v = (uint32_t)li.gl;
     uint32_t s0[1], s1[1];
@@ -1157,8 +1191,8 @@ __device__ __forceinline__ void sweep_regs(const SweepArgs& a, int wave, const P
         progress.left(a.nsweeps - t);
         if constexpr (LCG) {
             const U4 P = philox10(v, g, li.j, a.tag | kStreamLcgSeed, a.key0, a.key1);
-            half_sweep_lcg<L, 0>(s0, s1, li.lane, li.gl, P.x, a);
-            half_sweep_lcg<L, 1>(s1, s0, li.lane, li.gl, P.y, a);
+            half_sweep_lcg<L, 0, !PRIO>(s0, s1, li.lane, li.gl, P.x, a);
+            half_sweep_lcg<L, 1, !PRIO>(s1, s0, li.lane, li.gl, P.y, a);
         } else {
             half_sweep<L, 0, HB>(s0, s1, li.lane, li.gl, g, li.j, a, K);
             half_sweep<L, 1, HB>(s1, s0, li.lane, li.gl, g, li.j, a, K);
@@ -1486,7 +1520,7 @@ __device__ __forceinline__ void half_sweep_lds(const LdsRep<L>& rep, int gl, int
 // One colour of an LCG sweep on the LDS path: every word of the lane in turn,
 // its seed from the word's Philox block of this sweep (x: colour 0, y:
 // colour 1).  The uniforms are whole 32-bit numbers, so there are no ties.
-template <int L, int C>
+template <int L, int C, bool PAIRS>
 __device__ __forceinline__ void half_sweep_lds_lcg(const LdsRep<L>& rep, int gl, uint32_t g, uint32_t j,
                                                    const SweepArgs& a)
 {
@@ -1496,19 +1530,19 @@ __device__ __forceinline__ void half_sweep_lds_lcg(const LdsRep<L>& rep, int gl,
         const Nb n = rep.template nb<C>(k, gl);
         const uint32_t w = rep.at(C, k, gl);
         const U4 P = philox10u((uint32_t)(gl * Gm::K + k), g, j, a.tag | kStreamLcgSeed, a.key0, a.key1);
-        rep.at(C, k, gl) = w ^ lcg_accept_mask(w, n, C == 0 ? P.x : P.y, a);
+        rep.at(C, k, gl) = w ^ lcg_accept_mask<PAIRS>(w, n, C == 0 ? P.x : P.y, a);
     }
     wave_lds_sync();
 }
 
 // The LDS of the W waves of a replica: the replica [2][NW], then W tie queues.
-template <int L, bool INT8, bool HB, bool LCG, int W = 1>
-__device__ __forceinline__ void sweep_lds(const SweepArgs& a, uint32_t j, uint32_t* lds, const Progress& progress,
-                                          int wv = 0)
+template <int L, bool INT8, bool HB, bool LCG, bool PRIO, int W = 1>
+__device__ __forceinline__ void sweep_lds(const SweepArgs& a, uint32_t j, uint32_t* lds, int wv = 0)
 {
     static_assert(W == 1 || !LCG, "the LCG variant has one wave per replica");
     using Gm = Geo<L>;
     static_assert(Gm::WIDE && Gm::RL % 2 == 0 && Gm::G == 64, "LDS path layout");
+    const Progress<PRIO> progress(a.nsweeps, a.one_round != 0);
     const LdsRep<L> rep{lds};
     uint32_t* queue = lds + 2 * Gm::NW + wv * kTieQueueWords;
     const int gl = (int)(threadIdx.x & 63u);
@@ -1534,8 +1568,8 @@ __device__ __forceinline__ void sweep_lds(const SweepArgs& a, uint32_t j, uint32
         const uint32_t g = a.g0 + (uint32_t)t;
         progress.left(a.nsweeps - t);
         if constexpr (LCG) {
-            half_sweep_lds_lcg<L, 0>(rep, gl, g, j, a);
-            half_sweep_lds_lcg<L, 1>(rep, gl, g, j, a);
+            half_sweep_lds_lcg<L, 0, !PRIO>(rep, gl, g, j, a);
+            half_sweep_lds_lcg<L, 1, !PRIO>(rep, gl, g, j, a);
         } else {
             half_sweep_lds<L, 0, HB, W>(rep, gl, wv, g, j, a, K, queue);
             half_sweep_lds<L, 1, HB, W>(rep, gl, wv, g, j, a, K, queue);
@@ -1599,20 +1633,19 @@ constexpr int sweep_block()
 // the block's Geo<L>::lds_words(wpb) words (none on the register path).
 // Waves share no barrier: each returns as soon as it holds no replica.  HB
 // selects the heat-bath update instead of Metropolis; LCG the in-line LCG
-// variant of the Metropolis sweep.
-template <int L, bool INT8, bool HB, bool LCG = false>
+// variant of the Metropolis sweep; PRIO the wave priorities (Progress).
+template <int L, bool INT8, bool HB, bool LCG = false, bool PRIO = true>
 __device__ __forceinline__ void sweep_waves(const SweepArgs& a, int wave0, uint32_t* lds)
 {
     using Gm = Geo<L>;
     const int wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wave = wave0 + wib;
     if (wave * Gm::RPWV >= a.n_rep) return;  // uniform per wave
-    const Progress progress(a.nsweeps, a.one_round != 0);
     if constexpr (Gm::K == 1) {
-        sweep_regs<L, INT8, HB, LCG>(a, wave, progress);
+        sweep_regs<L, INT8, HB, LCG, PRIO>(a, wave);
     } else {
-        sweep_lds<L, INT8, HB, LCG>(a, (uint32_t)__builtin_amdgcn_readfirstlane(wave),
-                                    lds + wib * Gm::WAVE_LDS_WORDS, progress);
+        sweep_lds<L, INT8, HB, LCG, PRIO>(a, (uint32_t)__builtin_amdgcn_readfirstlane(wave),
+                                          lds + wib * Gm::WAVE_LDS_WORDS);
     }
 }
 

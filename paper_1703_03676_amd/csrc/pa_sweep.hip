@@ -26,7 +26,7 @@ namespace {
 
 using namespace pa::dev;
 
-template <int L, bool INT8, int U>
+template <int L, bool INT8, int U, bool PRIO>
 __global__ __launch_bounds__(sweep_block<L>())
 __attribute__((amdgpu_waves_per_eu(sweep_min_waves<L>(), 8))) void sweep_kernel(SweepArgs a)
 {
@@ -34,7 +34,7 @@ __attribute__((amdgpu_waves_per_eu(sweep_min_waves<L>(), 8))) void sweep_kernel(
     constexpr int WPB = sweep_block<L>() / 64;
     __shared__ __align__(16) uint32_t lds[Gm::lds_words(WPB) > 0 ? Gm::lds_words(WPB) : 1];
     if (a.n_dev) a.n_rep = min(a.n_rep, (int32_t)*a.n_dev);
-    sweep_waves<L, INT8, U == kHeatbath, U == kLcg>(a, (int)blockIdx.x * WPB, lds);
+    sweep_waves<L, INT8, U == kHeatbath, U == kLcg, PRIO>(a, (int)blockIdx.x * WPB, lds);
 }
 
 template <int L, bool INT8, int U>
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(64 * kReplicaWaves) void sweep_shared_kernel(SweepA
         sweep_quads64<INT8, HB>(a, blockIdx.x, lds);
     } else {
         const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-        sweep_lds<L, INT8, HB, false, W>(a, blockIdx.x, lds, Progress(a.nsweeps, true), wv);
+        sweep_lds<L, INT8, HB, false, true, W>(a, blockIdx.x, lds, wv);
     }
 }
 
@@ -86,10 +86,28 @@ constexpr int shared_replicas()
 // 0.057.
 constexpr int kQuadWaves = 4096;
 
+// Launches of the LCG update without wave priorities and with its comparisons in
+// pairs (shift_in_pair): up to one wave per SIMD, which priorities cannot help,
+// and, in the bit store of L = 16 and 64, launches whose last round would be a
+// thin one (up to a quarter), since waves kept together leave all of it to the
+// end.  Launches of 20 sweeps in us, with priorities and without.  One wave per
+// SIMD: L = 16, R = 300 23.4, 22.6, int8 24.1, 20.6; L = 64, R = 300 29.5, 25.5;
+// L = 128, R = 300 121, 102; two: L = 64, R = 1400 39.3, 41.0.  A thin last round:
+// L = 64, R = 9000 163, 146, R = 10000 176, 161, in the int8 store 153, 164;
+// L = 16, R = 160000 170, 153; but L = 32, R = 36000 133, 142.  A long queue:
+// L = 64, R = 30000 441, 459.
+template <int L, bool INT8>
+bool lcg_without_priorities(int waves)
+{
+    constexpr int ALL = sweep_resident_waves<L>();
+    return waves <= 1024 || ((L == 16 || L == 64) && !INT8 && waves > ALL && waves <= ALL / 4 * 5);
+}
+
 template <int L, bool INT8, int U>
 hipError_t launch_sweep_t(SweepArgs a, hipStream_t s)
 {
     using Gm = Geo<L>;
+    a.one_round = 1;
     if constexpr (L <= 32 && U != kLcg) {
         const int waves = (a.n_rep + quad_replicas<L>() - 1) / quad_replicas<L>();
         if (waves > 0 && waves <= kQuadWaves && !a.acc && !a.init && a.nsweeps > 0) {
@@ -106,8 +124,15 @@ hipError_t launch_sweep_t(SweepArgs a, hipStream_t s)
     const int reps_per_block = (sweep_block<L>() / 64) * Gm::RPWV;
     const int blocks = (a.n_rep + reps_per_block - 1) / reps_per_block;
     if (blocks == 0) return hipSuccess;
-    a.one_round = blocks * (sweep_block<L>() / 64) <= sweep_resident_waves<L>() ? 1 : 0;
-    hipLaunchKernelGGL((sweep_kernel<L, INT8, U>), dim3(blocks), dim3(sweep_block<L>()), 0, s, a);
+    const int waves = blocks * (sweep_block<L>() / 64);
+    a.one_round = waves <= sweep_resident_waves<L>() ? 1 : 0;
+    if constexpr (U == kLcg) {
+        if (lcg_without_priorities<L, INT8>(waves)) {
+            hipLaunchKernelGGL((sweep_kernel<L, INT8, U, false>), dim3(blocks), dim3(sweep_block<L>()), 0, s, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((sweep_kernel<L, INT8, U, true>), dim3(blocks), dim3(sweep_block<L>()), 0, s, a);
     return hipGetLastError();
 }
 
