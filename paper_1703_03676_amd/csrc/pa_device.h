@@ -369,7 +369,8 @@ struct Neighbours {
 // block of assembly, arithmetic and branches only: written as a switch, the
 // compiler joins the cases with five register moves per plane of four words
 // (L = 128, R = 50000: 144 -> 131 vector instructions per word and half sweep,
-// 1.68 -> 1.63 ms per launch of 20 sweeps).
+// 1.68 -> 1.63 ms per launch of 20 sweeps).  The masks are early
+// clobbers: the cases that select read the class again after writing them.
 #define PA_PLANE_M(i, t) "v_bitop3_b32 %[" t "], %[a" i "], %[o" i "], %[x" i "] bitop3:0xf4\n\t"
 #define PA_PLANE_SEL(d, i, p, q) "v_bitop3_b32 %[" d i "], %[c" i "], %[" p "], %[" q "] bitop3:0xca\n\t"
 #define PA_PLANE_0(i) PA_PLANE_M(i, "o" i)
@@ -399,13 +400,13 @@ __device__ __forceinline__ void open_plane(const uint32_t (&x)[NG], uint32_t tb,
     uint32_t t0;
     if constexpr (NG == 1) {
         __asm__(PA_PLANE_ASM(PA_PLANE_0("0"), PA_PLANE_1("0", "t0"), PA_PLANE_2("0", "t0"), PA_PLANE_3("0"))
-                : [a0] "+v"(acc[0]), [o0] "+v"(open[0]), [t0] "=&v"(t0)
+                : [a0] "+&v"(acc[0]), [o0] "+&v"(open[0]), [t0] "=&v"(t0)
                 : [x0] "v"(x[0]), [c0] "v"(cls1[0]), [tb] "s"(tb)
                 : "scc");
     } else if constexpr (NG == 2) {
         __asm__(PA_PLANE_ASM(PA_PLANE_0("0") PA_PLANE_0("1"), PA_PLANE_1("0", "t0") PA_PLANE_1("1", "t0"),
                              PA_PLANE_2("0", "t0") PA_PLANE_2("1", "t0"), PA_PLANE_3("0") PA_PLANE_3("1"))
-                : [a0] "+v"(acc[0]), [o0] "+v"(open[0]), [a1] "+v"(acc[1]), [o1] "+v"(open[1]), [t0] "=&v"(t0)
+                : [a0] "+&v"(acc[0]), [o0] "+&v"(open[0]), [a1] "+&v"(acc[1]), [o1] "+&v"(open[1]), [t0] "=&v"(t0)
                 : [x0] "v"(x[0]), [c0] "v"(cls1[0]), [x1] "v"(x[1]), [c1] "v"(cls1[1]), [tb] "s"(tb)
                 : "scc");
     } else {
@@ -413,8 +414,8 @@ __device__ __forceinline__ void open_plane(const uint32_t (&x)[NG], uint32_t tb,
                              PA_PLANE_1("0", "t0") PA_PLANE_1("1", "t0") PA_PLANE_1("2", "t0") PA_PLANE_1("3", "t0"),
                              PA_PLANE_2("0", "t0") PA_PLANE_2("1", "t0") PA_PLANE_2("2", "t0") PA_PLANE_2("3", "t0"),
                              PA_PLANE_3("0") PA_PLANE_3("1") PA_PLANE_3("2") PA_PLANE_3("3"))
-                : [a0] "+v"(acc[0]), [o0] "+v"(open[0]), [a1] "+v"(acc[1]), [o1] "+v"(open[1]), [a2] "+v"(acc[2]),
-                  [o2] "+v"(open[2]), [a3] "+v"(acc[3]), [o3] "+v"(open[3]), [t0] "=&v"(t0)
+                : [a0] "+&v"(acc[0]), [o0] "+&v"(open[0]), [a1] "+&v"(acc[1]), [o1] "+&v"(open[1]), [a2] "+&v"(acc[2]),
+                  [o2] "+&v"(open[2]), [a3] "+&v"(acc[3]), [o3] "+&v"(open[3]), [t0] "=&v"(t0)
                 : [x0] "v"(x[0]), [c0] "v"(cls1[0]), [x1] "v"(x[1]), [c1] "v"(cls1[1]), [x2] "v"(x[2]),
                   [c2] "v"(cls1[2]), [x3] "v"(x[3]), [c3] "v"(cls1[3]), [tb] "s"(tb)
                 : "scc");
