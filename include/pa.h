@@ -441,7 +441,10 @@ typedef struct pa_mlp pa_mlp;
 size_t pa_mlp_workspace_bytes(int32_t max_batch);
 
 /* Network with He-initialised weights drawn from `seed` and identity
- * normalisation; max_batch bounds the minibatch and gradient sizes. */
+ * normalisation; max_batch bounds the minibatch and gradient sizes.  Takes the
+ * pinned host memory of all later calls (23 KB and twice the larger of
+ * max_batch and 8192 sample numbers, 4 bytes each).  Errors: PA_EINVAL,
+ * PA_ENOMEM (bytes too small, no host memory), PA_EHIP. */
 pa_status pa_mlp_create(int32_t max_batch, uint64_t seed, void* d_workspace, size_t bytes, void* hip_stream,
                         pa_mlp** out);
 pa_status pa_mlp_set_params(pa_mlp* m, const float* params, const float* norm);  /* host arrays; either may be NULL */
@@ -454,7 +457,9 @@ pa_status pa_mlp_forward(pa_mlp* m, const float* d_x, int32_t n, float* d_y, int
 /* Gradient (host grad[4801]) and loss of the n <= max_batch samples. */
 pa_status pa_mlp_gradient(pa_mlp* m, const float* d_x, const float* d_t, int32_t n, float* grad, float* loss);
 /* `epochs` passes of minibatch SGD (shuffled with `seed`, full minibatches of
- * `batch` samples); epoch_loss[epochs] (may be NULL) receives the mean loss. */
+ * `batch` samples); epoch_loss[epochs] (may be NULL) receives the mean loss.
+ * Errors: PA_EINVAL, PA_ENOMEM (no host memory for the n sample numbers),
+ * PA_ESTATE, PA_EHIP. */
 pa_status pa_mlp_train(pa_mlp* m, const float* d_x, const float* d_t, int32_t n, int32_t batch, int32_t epochs,
                        float lr, float momentum, uint64_t seed, float* epoch_loss);
 const char* pa_mlp_last_error(const pa_mlp* m);

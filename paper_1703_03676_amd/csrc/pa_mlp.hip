@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <random>
 #include <string>
@@ -368,13 +369,13 @@ struct pa_mlp {
     float *p, *grad, *mom, *norm, *work, *loss;
     __hip_bfloat16* wb;
     int32_t* idx;
-    float* h_out = nullptr;         // pinned: gradient and loss, written by k_apply (from the first call on)
+    // one pinned block, from pa_mlp_create on: no later call allocates any
+    float* h_out = nullptr;         // gradient and loss, written by k_apply
     void* h_out_dev = nullptr;      // device view of h_out
-    int32_t* h_order[2] = {nullptr, nullptr};  // pinned: sample orders of two epochs in turn
+    float* h_loss = nullptr;        // losses of kLossRing epochs
+    int32_t* h_order[2] = {nullptr, nullptr};  // sample orders on their way, in turn
     size_t order_cap = 0;           // samples each of them holds
     hipEvent_t order_read[2] = {nullptr, nullptr};  // the last upload from each
-    float* h_loss = nullptr;        // pinned: epoch losses
-    size_t loss_cap = 0;
     bool broken;
     std::string last_error;
 };
@@ -429,30 +430,10 @@ pa_status grad_pass(pa_mlp* m, const float* d_x, const float* d_t, const int32_t
     return PA_OK;
 }
 
-// Pinned host memory for the sample orders of two epochs and the epoch losses.
-pa_status reserve(pa_mlp* m, size_t n, size_t epochs)
-{
-    if (n > m->order_cap) {
-        for (int k = 0; k < 2; ++k) {
-            if (m->h_order[k]) (void)hipHostFree(m->h_order[k]);
-            m->h_order[k] = nullptr;
-        }
-        m->order_cap = 0;
-        for (int k = 0; k < 2; ++k) {
-            if (hipHostMalloc((void**)&m->h_order[k], n * 4, hipHostMallocDefault) != hipSuccess) return PA_ENOMEM;
-            if (!m->order_read[k]) MCHK(hipEventCreateWithFlags(&m->order_read[k], hipEventDisableTiming));
-        }
-        m->order_cap = n;
-    }
-    if (epochs > m->loss_cap) {
-        if (m->h_loss) (void)hipHostFree(m->h_loss);
-        m->h_loss = nullptr;
-        m->loss_cap = 0;
-        if (hipHostMalloc((void**)&m->h_loss, epochs * 4, hipHostMallocDefault) != hipSuccess) return PA_ENOMEM;
-        m->loss_cap = epochs;
-    }
-    return PA_OK;
-}
+// Samples of one upload of the order (at least a minibatch), and epochs whose
+// losses are read back together.
+constexpr int kOrderChunk = 8192;
+constexpr int kLossRing = 1024;
 
 }  // namespace
 
@@ -496,7 +477,18 @@ pa_status pa_mlp_create(int32_t max_batch, uint64_t seed, void* d_workspace, siz
     for (int i = 0; i < kHid; ++i) p[kW3 + i] = (float)(nd(rng) * std::sqrt(1.0 / kHid));
     for (int k = 0; k < kIn; ++k) norm[kIn + k] = 1.0f;
     norm[2 * kIn + 1] = 1.0f;
+    m->order_cap = (size_t)std::max(max_batch, kOrderChunk);
+    const size_t pinned = (size_t)(kPartStride + kLossRing) * 4 + 2 * m->order_cap * 4;
+    if (hipHostMalloc((void**)&m->h_out, pinned, hipHostMallocMapped) != hipSuccess) {
+        delete m;
+        return PA_ENOMEM;
+    }
+    m->h_loss = m->h_out + kPartStride;
+    m->h_order[0] = reinterpret_cast<int32_t*>(m->h_loss + kLossRing);
+    m->h_order[1] = m->h_order[0] + m->order_cap;
     *out = m;
+    MCHK(hipHostGetDevicePointer(&m->h_out_dev, m->h_out, 0));
+    for (int k = 0; k < 2; ++k) MCHK(hipEventCreateWithFlags(&m->order_read[k], hipEventDisableTiming));
     MCHK(hipMemcpyAsync(m->p, p.data(), kParams * 4, hipMemcpyHostToDevice, m->stream));
     MCHK(hipMemcpyAsync(m->mom, zero.data(), kParams * 4, hipMemcpyHostToDevice, m->stream));
     MCHK(hipMemcpyAsync(m->norm, norm.data(), kNorm * 4, hipMemcpyHostToDevice, m->stream));
@@ -555,10 +547,6 @@ pa_status pa_mlp_gradient(pa_mlp* m, const float* d_x, const float* d_t, int32_t
 {
     if (!m || !d_x || !d_t || n < 1 || n > m->max_batch) return PA_EINVAL;
     if (m->broken) return PA_ESTATE;
-    if (!m->h_out) {
-        if (hipHostMalloc((void**)&m->h_out, kPartStride * 4, hipHostMallocMapped) != hipSuccess) return PA_ENOMEM;
-        MCHK(hipHostGetDevicePointer(&m->h_out_dev, m->h_out, 0));
-    }
     float* out = (float*)m->h_out_dev;
     const pa_status st = grad_pass(m, d_x, d_t, nullptr, n, out, 0.0f, 0.0f, out + kParams, true);
     if (st != PA_OK) return st;
@@ -576,8 +564,8 @@ pa_status pa_mlp_train(pa_mlp* m, const float* d_x, const float* d_t, int32_t n,
     std::mt19937_64 rng(seed);
     const int nb = n / batch;  // full minibatches only
     if (nb < 1) return PA_EINVAL;
-    const pa_status rs = reserve(m, (size_t)n, (size_t)epochs);
-    if (rs != PA_OK) return rs;
+    const std::unique_ptr<int32_t[]> perm(new (std::nothrow) int32_t[(size_t)n]);
+    if (!perm) return PA_ENOMEM;
     // device room for the sample order: behind the partial sums, or the index
     // buffer of one minibatch
     int32_t* order = m->idx;
@@ -588,31 +576,36 @@ pa_status pa_mlp_train(pa_mlp* m, const float* d_x, const float* d_t, int32_t n,
         order = (int32_t*)(m->work + used);
         room = m->lo.work_floats - used;
     }
-    const int per_upload = (int)std::min<size_t>((size_t)nb, room / (size_t)batch);
-    // Everything of an epoch is queued without a wait: the order of epoch e
-    // comes from pinned buffer e mod 2, which is rewritten only after its
-    // last upload has been read (two epochs earlier).
+    const int per_upload = (int)std::min<size_t>((size_t)nb, std::min(room, m->order_cap) / (size_t)batch);
+    // Everything is queued without a wait: the order goes through two pinned
+    // buffers in turn, each rewritten only after its last upload has been read.
+    int uploads = 0;
     for (int e = 0; e < epochs; ++e) {
-        int32_t* perm = m->h_order[e & 1];
-        if (e >= 2) MCHK(hipEventSynchronize(m->order_read[e & 1]));
-        for (int i = 0; i < n; ++i) perm[i] = i;
-        std::shuffle(perm, perm + n, rng);
+        for (int i = 0; i < n; ++i) perm[(size_t)i] = i;
+        std::shuffle(perm.get(), perm.get() + n, rng);
         for (int k = 0; k < nb; ++k) {
             const int at = k % per_upload;
             if (at == 0) {
                 const size_t count = (size_t)std::min(per_upload, nb - k) * (size_t)batch;
-                MCHK(hipMemcpyAsync(order, perm + (size_t)k * batch, count * 4, hipMemcpyHostToDevice, m->stream));
+                const int h = uploads & 1;
+                if (uploads >= 2) MCHK(hipEventSynchronize(m->order_read[h]));
+                ++uploads;
+                std::memcpy(m->h_order[h], perm.get() + (size_t)k * batch, count * 4);
+                MCHK(hipMemcpyAsync(order, m->h_order[h], count * 4, hipMemcpyHostToDevice, m->stream));
+                MCHK(hipEventRecord(m->order_read[h], m->stream));
             }
             const pa_status st = grad_pass(m, d_x, d_t, order + (size_t)at * batch, batch, nullptr, lr, momentum,
                                            m->loss, k == 0);
             if (st != PA_OK) return st;
         }
-        MCHK(hipEventRecord(m->order_read[e & 1], m->stream));
-        MCHK(hipMemcpyAsync(&m->h_loss[e], m->loss, 4, hipMemcpyDeviceToHost, m->stream));
+        const int slot = e % kLossRing;
+        MCHK(hipMemcpyAsync(&m->h_loss[slot], m->loss, 4, hipMemcpyDeviceToHost, m->stream));
+        if (slot == kLossRing - 1 || e == epochs - 1) {
+            MCHK(hipStreamSynchronize(m->stream));
+            if (epoch_loss)
+                for (int i = 0; i <= slot; ++i) epoch_loss[e - slot + i] = m->h_loss[i] / (float)nb;
+        }
     }
-    MCHK(hipStreamSynchronize(m->stream));
-    if (epoch_loss)
-        for (int e = 0; e < epochs; ++e) epoch_loss[e] = m->h_loss[e] / (float)nb;
     return PA_OK;
 }
 
@@ -622,10 +615,8 @@ pa_status pa_mlp_free(pa_mlp* m)
 {
     if (!m) return PA_OK;
     for (int k = 0; k < 2; ++k) {
-        if (m->h_order[k]) (void)hipHostFree(m->h_order[k]);
         if (m->order_read[k]) (void)hipEventDestroy(m->order_read[k]);
     }
-    if (m->h_loss) (void)hipHostFree(m->h_loss);
     if (m->h_out) (void)hipHostFree(m->h_out);
     delete m;
     return PA_OK;
