@@ -1453,21 +1453,15 @@ namespace {
 // by the first resampling, so tuning leaves no trace in the runs.  The timed
 // launches draw a fresh state and do a few sweeps at beta = 0.44.
 // Waves per block chosen by autotune, kept for the life of the process per
-// (device architecture, lattice sizes, store, update, waves of the group's
-// populations rounded up to a power of two): later batches of the same shape
-// skip the timed search.
+// (device architecture, store, update, lattice sizes with their waves): later
+// batches of the same shape skip the timed search.
 struct TuneKey {
     std::string arch;
-    int L, layout;
-    int upd;
-    int64_t waves;
+    int layout, upd;
+    host::LaunchMix mix;
     bool operator<(const TuneKey& o) const
     {
-        if (arch != o.arch) return arch < o.arch;
-        if (L != o.L) return L < o.L;
-        if (layout != o.layout) return layout < o.layout;
-        if (upd != o.upd) return upd < o.upd;
-        return waves < o.waves;
+        return std::tie(arch, layout, upd, mix) < std::tie(o.arch, o.layout, o.upd, o.mix);
     }
 };
 std::mutex g_tune_mu;
@@ -1494,14 +1488,12 @@ pa_status autotune(pa_batch* b)
             g.wpb = w;
             continue;
         }
-        int64_t waves = 0;
+        host::LaunchMix mix;
         for (int r = 0; r < b->nruns; ++r) {
             const RunHost& h = b->runs[(size_t)r];
-            if (in_group(h.p, g)) waves += (h.p.R + reps_per_wave(h.p.L) - 1) / reps_per_wave(h.p.L);
+            if (in_group(h.p, g)) mix.add(h.p.L, (h.p.R + reps_per_wave(h.p.L) - 1) / reps_per_wave(h.p.L));
         }
-        int64_t bucket = 1;
-        while (bucket < waves) bucket <<= 1;
-        const TuneKey key{arch, g.L, g.layout, g.upd, bucket};
+        const TuneKey key{arch, g.layout, g.upd, mix.rounded()};
         {
             std::lock_guard<std::mutex> lk(g_tune_mu);
             const auto f = g_tune_cache.find(key);

@@ -36,6 +36,29 @@ bool spin_for(F there)
     }
 }
 
+// What a sweep launch over several populations holds, coarsely: for each lattice
+// size L = 16, 32, 64, 128, 256 the waves of its replicas, rounded up to a power
+// of two (0: none).  The best launch shape depends on both: waves of L = 16 hold
+// 16 replicas and of L = 64 one, and end at different times.
+struct LaunchMix {
+    int64_t waves[5] = {};
+    void add(int L, int64_t n) { waves[__builtin_ctz((unsigned)L) - 4] += n; }
+    LaunchMix rounded() const
+    {
+        LaunchMix m;
+        for (int i = 0; i < 5; ++i)
+            if (waves[i] > 0)
+                for (m.waves[i] = 1; m.waves[i] < waves[i];) m.waves[i] <<= 1;
+        return m;
+    }
+    bool operator<(const LaunchMix& o) const
+    {
+        for (int i = 0; i < 5; ++i)
+            if (waves[i] != o.waves[i]) return waves[i] < o.waves[i];
+        return false;
+    }
+};
+
 // Occupied window [bmin, bmax] of an energy histogram n[0..N].
 struct Hist {
     const uint32_t* n;
