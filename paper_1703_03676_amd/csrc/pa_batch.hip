@@ -486,8 +486,9 @@ struct RunLayout {
 
 struct BatchLayout {
     std::vector<RunLayout> runs;
-    size_t rundev, steps, results, feats, download, tables, items, model, total;
-    size_t download_bytes;  // results + all stats blocks and histograms
+    size_t rundev, steps, results, download, tables, items, model, total;
+    size_t feats;           // offset of the features in the host's download area, behind the rest
+    size_t download_bytes;  // results + all stats blocks and histograms, then the features
     size_t steps_bytes;     // step descriptors + table area
     size_t n_items;
 };
@@ -525,7 +526,7 @@ bool make_batch_layout(const pa_params* runs, int nruns, BatchLayout* bl)
         return at;
     };
     bl->runs.resize((size_t)nruns);
-    size_t dl = align_up(sizeof(ResultDev) * (size_t)nruns) + align_up(sizeof(FeatDev) * (size_t)nruns);
+    size_t dl = align_up(sizeof(ResultDev) * (size_t)nruns);
     size_t tbl = 0;
     for (int r = 0; r < nruns; ++r) {
         const pa_params& p = runs[r];
@@ -551,13 +552,13 @@ bool make_batch_layout(const pa_params* runs, int nruns, BatchLayout* bl)
         rl.tbl_words = (size_t)rl.nbins * 2;
         tbl += rl.tbl_words;
     }
-    bl->download_bytes = dl;
+    bl->feats = dl;
+    bl->download_bytes = dl + sizeof(FeatDev) * (size_t)nruns;
     bl->steps_bytes = align_up(sizeof(StepDev) * (size_t)nruns) + tbl * 4;
     bl->rundev = take(sizeof(RunDev) * (size_t)nruns);
     bl->steps = take(bl->steps_bytes);
     bl->download = take(dl);
-    bl->results = bl->download;  // results lead the download area, then the features
-    bl->feats = bl->download + align_up(sizeof(ResultDev) * (size_t)nruns);
+    bl->results = bl->download;  // results lead the download area
     bl->model = take(sizeof(ModelDev));
     // items: parents/statistics, copy chunks, and sweep items of every candidate shape
     size_t n_items = 0;
@@ -679,7 +680,7 @@ struct RunHost {
     FeatDev feat;
     double last_dbeta = 0.0;
     int32_t proposals = 0, accepted = 0;
-    int64_t alpha_evals = 0;   // overlap evaluations made to choose the temperatures
+    int64_t alpha_evals = 0;   // overlaps compared with the target to choose the temperatures
     double choose_s = 0.0;     // host seconds spent choosing them
     std::vector<float> pair_x, pair_t;  // (features, ln(step sigma_E)) from the bisection
 };
@@ -696,7 +697,6 @@ struct pa_batch {
     StepDev* d_steps = nullptr;
     uint32_t* d_tables = nullptr;
     ResultDev* d_results = nullptr;
-    FeatDev* d_feats = nullptr;
     ModelDev* d_model = nullptr;
     bool model_set = false;
     uint8_t* d_download = nullptr;
@@ -837,8 +837,7 @@ pa_status enqueue_step(pa_batch* b, bool with_copy)
     for (const Group& g : b->groups)
         BCHK(launch_group(g, items + g.item_off, g.n_items, g.wpb, b->d_rundev, b->d_steps, b->d_results, s));
     hipLaunchKernelGGL(b_stats, dim3((unsigned)b->n_parent_items), dim3(kBlock), 0, s, items + b->parent_off,
-                       b->d_rundev, b->d_steps, b->d_results, b->d_model, (uint8_t*)b->h_download_dev,
-                       (size_t)(b->lo.feats - b->lo.download));
+                       b->d_rundev, b->d_steps, b->d_results, b->d_model, (uint8_t*)b->h_download_dev, b->lo.feats);
     BCHK(hipGetLastError());
     return PA_OK;
 }
@@ -881,7 +880,7 @@ void read_stats(pa_batch* b, int r)
     const RunLayout& rl = b->lo.runs[(size_t)r];
     std::memcpy(&h.h_stats, b->h_download + rl.stats_off, sizeof(DevStats));
     h.h_hist = reinterpret_cast<const uint32_t*>(b->h_download + rl.stats_off + sizeof(DevStats));
-    std::memcpy(&h.feat, b->h_download + (b->lo.feats - b->lo.download) + sizeof(FeatDev) * (size_t)r,
+    std::memcpy(&h.feat, b->h_download + b->lo.feats + sizeof(FeatDev) * (size_t)r,
                 sizeof(FeatDev));
 }
 
@@ -1020,7 +1019,6 @@ static pa_status batch_init(const pa_params* runs, const pa_schedule* sched, int
     b->d_tables = reinterpret_cast<uint32_t*>(ws + bl.tables);
     b->d_download = ws + bl.download;
     b->d_results = reinterpret_cast<ResultDev*>(ws + bl.results);
-    b->d_feats = reinterpret_cast<FeatDev*>(ws + bl.feats);
     b->d_model = reinterpret_cast<ModelDev*>(ws + bl.model);
     b->d_items = reinterpret_cast<Item*>(ws + bl.items);
     b->runs.resize((size_t)nruns);

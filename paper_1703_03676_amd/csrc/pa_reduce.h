@@ -71,7 +71,7 @@ __device__ __forceinline__ void fill_parents(uint32_t* __restrict__ parent, uint
     }
 }
 
-// Population statistics, first pass, for the replicas [i0, i0 + kBlock) of// Population statistics, first pass, for the replicas [i0, i0 + kBlock) of
+// Population statistics, first pass, for the replicas [i0, i0 + kBlock) of
 // one block (i < n only): the energy histogram n(b), b = (E + 2N) / 4, and, if
 // `record`, the per-energy accumulators of multi-histogram reweighting are
 // added to the population's arrays; the energy range and the exact sums of E,
