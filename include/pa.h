@@ -24,6 +24,8 @@
  *     is enqueued on it.  Calls that return host values (pa_resample's info,
  *     pa_adapt_beta, pa_observables, pa_reweight, the download hooks)
  *     return when the work queued on it that they depend on has been done.
+ *     The calling thread polls host memory for it for up to a millisecond and
+ *     then blocks on the stream, so a waiting call keeps a core busy that long.
  *   - Spin convention: +1 / -1; J = 1, h = 0; E = -sum over the 2N bonds;
  *     M = sum of spins.  Energies are multiples of 4 in [-2N, 2N].
  *   - Random numbers: Philox4x32-10 keyed by the 64-bit seed, with counters
@@ -273,10 +275,10 @@ pa_status pa_set_tie_queue_cap(pa_run* r, int32_t cap);
  * histogram and integer moment sums of each new population).  They are taken
  * in the epilogue of the sweep that makes the population (every wave adds its
  * replicas with device atomics, then one block sums them) or in a separate
- * pass over E and M.  PA_STATS_AUTO (the
- * default) takes the epilogue where it measured faster: one replica per wave
- * (L >= 64) and R <= 32768, or L = 256.  PA_STATS_EPILOGUE and PA_STATS_PASS
- * force one of them.  Results do not depend on the choice.
+ * pass over E and M.  PA_STATS_AUTO (the default) takes the epilogue where it
+ * measured faster: one replica per wave (L >= 64) and R <= 32768, or L = 256.
+ * PA_STATS_EPILOGUE and PA_STATS_PASS force one of them.  Results do not
+ * depend on the choice.
  * Errors: PA_EINVAL (unknown mode), PA_ESTATE. */
 typedef enum { PA_STATS_AUTO = 0, PA_STATS_EPILOGUE = 1, PA_STATS_PASS = 2 } pa_stats_path;
 pa_status pa_set_stats_path(pa_run* r, int32_t mode);
@@ -285,9 +287,10 @@ pa_status pa_set_stats_path(pa_run* r, int32_t mode);
  * Every run has its own parameters (L, R, seed, run_id, layout, flags) and
  * schedule.  One pa_batch_step advances every unfinished run by one
  * temperature step (choose beta_{i+1}, resample, theta sweeps, measure) with
- * one batched launch per phase and one host wait for the whole batch.  Each run follows exactly the same
- * arithmetic and random streams as a single run with the same parameters and
- * schedule, so its results are bit-identical to that run's. */
+ * one batched launch per phase and one host wait for the whole batch.  Each
+ * run follows exactly the same arithmetic and random streams as a single run
+ * with the same parameters and schedule, so its results are bit-identical to
+ * that run's. */
 
 typedef enum {
     PA_STEP_FIXED = 0,     /* beta_i = i * dbeta, last step clamped to beta_f (Sec. 2.1) */
@@ -340,11 +343,11 @@ typedef struct pa_batch pa_batch;  /* opaque host handle */
 size_t pa_batch_workspace_bytes(const pa_params* runs, int32_t nruns);
 
 /* Start nruns runs at beta_0 = 0 (Sec. 2.1 step 1) and measure them once.
- * `hip_stream` may be NULL: the batch then creates its own stream.  The sweep's work-group shape (waves per
- * block, one per launch: L <= 64 together, 128, 256, each with its store and
- * update) is chosen by timing the
- * candidates 1, 2, 4 and 8 on the batch's spare buffers.  Errors: PA_EINVAL
- * (invalid run parameters or schedule, nruns < 1), PA_ENOMEM, PA_EHIP. */
+ * `hip_stream` may be NULL: the batch then creates its own stream.  The
+ * sweep's work-group shape (waves per block, one per launch: L <= 64 together,
+ * 128, 256, each with its store and update) is chosen by timing the candidates
+ * 1, 2, 4 and 8 on the batch's spare buffers.  Errors: PA_EINVAL (invalid run
+ * parameters or schedule, nruns < 1), PA_ENOMEM, PA_EHIP. */
 pa_status pa_batch_init(const pa_params* runs, const pa_schedule* sched, int32_t nruns, void* d_workspace,
                         size_t bytes, void* hip_stream, pa_batch** out);
 
@@ -411,10 +414,12 @@ pa_status pa_batch_training_pairs(const pa_batch* b, float* x, float* t, int32_t
  * is exp(prop - x[1]). */
 pa_status pa_batch_features(const pa_batch* b, int32_t run, float* x, int32_t* valid, float* prop);
 
-/* Cost of choosing one run's temperatures so far: the number of overlap
- * evaluations alpha(beta_i, beta') of Sec. 2.3 (a bisection makes 51 per step
- * unless beta_f is reached at once, an accepted learned proposal 1, a
- * rejected one 1 before its bisection) and the host seconds spent choosing
+/* Cost of choosing one run's temperatures so far: the number of overlaps
+ * alpha(beta_i, beta') of Sec. 2.3 that were compared with the target (a
+ * bisection compares 51 per step unless beta_f is reached at once, an accepted
+ * learned proposal 1, a rejected one 1 before its bisection; a bisection
+ * decides most of its comparisons from about ten quickly computed values and
+ * evaluates about eight overlaps exactly) and the host seconds spent choosing
  * (fixed and follower runs: 0). */
 pa_status pa_batch_choice_stats(const pa_batch* b, int32_t run, int64_t* alpha_evals, double* host_seconds);
 

@@ -227,15 +227,15 @@ def observables_static(L, E, M, beta=0.0, lnZ=0.0, lnQ=0.0, stream=None):
     """pa_observables_static: observables of the population whose energies and
     magnetisations are the int32 device tensors E and M (same length R), with
     no allocation in the library (its static device array holds the
-    statistics).  Returns the observables as a dict."""
+    sums).  Returns the observables as a dict."""
     import torch
     if E.dtype != torch.int32 or M.dtype != torch.int32 or not E.is_cuda or not M.is_cuda:
         raise PaError(PA_EINVAL, "E and M must be int32 device tensors")
     if E.dim() != 1 or E.shape != M.shape or not E.is_contiguous() or not M.is_contiguous():
         raise PaError(PA_EINVAL, "E and M must be contiguous 1-d tensors of equal length")
     if E.shape[0] > PA_STATIC_MAX_R:
-        raise PaError(PA_EINVAL, "pa_observables_static takes at most %d replicas (its static device scratch "
-                                 "is sized for that); got %d" % (PA_STATIC_MAX_R, E.shape[0]))
+        raise PaError(PA_EINVAL, "pa_observables_static takes at most %d replicas; got %d"
+                      % (PA_STATIC_MAX_R, E.shape[0]))
     s = stream if stream is not None else torch.cuda.current_stream(E.device)
     o = Obs()
     with torch.cuda.device(E.device):
@@ -488,7 +488,7 @@ class Batch:
         _check(lib().pa_batch_set_tie_queue_cap(self.h, int(cap)))
 
     def choice_stats(self, run):
-        """(overlap evaluations, host seconds) spent choosing run's temperatures."""
+        """(overlaps compared with the target, host seconds) spent choosing run's temperatures."""
         n, t = ctypes.c_int64(), ctypes.c_double()
         _check(lib().pa_batch_choice_stats(self.h, int(run), ctypes.byref(n), ctypes.byref(t)))
         return n.value, t.value
