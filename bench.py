@@ -28,15 +28,20 @@ if ROOT not in sys.path:
 L, R, THETA, DBETA, NSTEPS = 64, 20000, 100, 0.005, 200
 
 # ALU roofline of the sweep:
-#   peak: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.3e12 VALU lane-slots/s
-#   (one full-rate 32-bit VALU operation on one lane = one slot; the
-#   32x32->64 multiply runs at full rate on gfx950).
 #   work per attempted flip: the minimal evaluation of the chain's random
 #   numbers for a 32-site word is the first 2 Philox4x32-10 blocks (8 bit planes
 #   decide a site except with probability 2^-8), 10 rounds x (2 multiplies +
 #   2 three-input xors) = 40 slots each, plus about 32 slots of bit-sliced
-#   neighbour, class and comparison logic: (2*40 + 32) / 32 = 3.5 slots.
-VALU_PEAK_SLOTS = 256 * 4 * 16 * 2.4e9
+#   neighbour, class and comparison logic: (2*40 + 32) / 32 = 3.5 slots (one slot:
+#   one 32-bit VALU operation on one lane).
+#   peak: 256 CUs x 4 SIMDs x 64 lanes x 2.4 GHz over the cycles a SIMD takes per
+#   wave instruction in that mix.  gfx950 issues instructions of two waves
+#   together where their operands are all in vector registers: 2.4 cycles measured
+#   for a three-input xor (4.2 with a scalar operand), 4.25 for the 32x32->64
+#   multiply either way.  40 multiplies and 72 others: 342.8 cycles for 112
+#   instructions, 51.4e12 slots/s.
+MULTIPLY_CYCLES, LOGIC_CYCLES = 4.25, 2.4
+VALU_PEAK_SLOTS = 256 * 4 * 64 * 2.4e9 * 112 / (40 * MULTIPLY_CYCLES + 72 * LOGIC_CYCLES)
 HBM_PEAK = 8.0e12  # bytes/s
 SLOTS_PER_FLIP = 3.5
 PROFILE = os.path.join(ROOT, "profiles", "sweep_kernel_L64_R20000_theta100.md")
@@ -642,12 +647,14 @@ def main():
             "kernel": "sweep_kernel<64,%s>" % ("bits" if layouts[0] == "interleaved" else layouts[0]),
             "achieved": round(achieved / 1e12, 3),
             "peak": round(VALU_PEAK_SLOTS / 1e12, 2),
-            "unit": "Tops/s (VALU lane-slots, %.1f per attempted flip)" % SLOTS_PER_FLIP,
+            "unit": "Tops/s (VALU lane-slots, %.1f per attempted flip; peak at %.2f cycles per multiply and %.1f "
+                    "per other wave instruction and SIMD)" % (SLOTS_PER_FLIP, MULTIPLY_CYCLES, LOGIC_CYCLES),
             "frac": round(achieved / VALU_PEAK_SLOTS, 4),
             "traffic": traffic,
             # counters of the same kernel (committed profile): VALU instructions per
-            # 32-site word and half sweep, and what they make of the issue peak at
-            # the measured launch time (4 cycles per wave64 instruction)
+            # 32-site word and half sweep, and what they make of one instruction per
+            # 4 cycles and SIMD at the measured launch time (above 1: instructions of
+            # two waves issued together)
             "valu_instr_per_word": valu_per_word,
             "valu_issue_frac": (round(valu_per_word * head["sweep_flips_avg"] / 32 / 64 * 4
                                       / (head["sweep_ms_avg"] * 1e-3 * 2.4e9 * 1024), 4)
