@@ -1166,17 +1166,33 @@ struct Progress {
     }
 };
 
+// Energies, magnetisations and spins of a wave after its sweeps (register path).
+template <int L, bool INT8>
+__device__ __forceinline__ void write_regs(const SweepArgs& a, int wave, const LaneInfo& li, const uint32_t (&s0)[1],
+                                           const uint32_t (&s1)[1])
+{
+    const uint32_t v = (uint32_t)li.gl;
+    const Neighbours<L, 0> nb(s1, li.lane, li.gl);
+    const Nb n = nb.get(s1, 0);
+    const uint32_t anti = __popc(s0[0] ^ n.up) + __popc(s0[0] ^ n.dn) + __popc(s0[0] ^ n.same) + __popc(s0[0] ^ n.side);
+    const uint32_t downs = __popc(s0[0]) + __popc(s1[0]);
+    write_EM<L>(a, li, anti, downs);
+    if constexpr (INT8)
+        store_wave_int8<L>(a, wave, li.lane, v, s0[0], s1[0]);
+    else if (li.valid)
+        store_word<L, INT8>(a, li.j, v, s0[0], s1[0]);
+}
+
 // Register-resident sweep: each lane owns one word per colour (L <= 64).
 // LCG: the in-line LCG variant; the word's seeds for both colours of a sweep
 // come from one Philox block (outputs x and y).
 template <int L, bool INT8, bool HB, bool LCG, bool PRIO>
-__device__ __forceinline__ void sweep_regs(const SweepArgs& a, int wave)
+__device__ __forceinline__ void sweep_regs(const SweepArgs& a, int wave, const LaneInfo& li,
+                                           const Progress<PRIO>& progress)
 {
     using Gm = Geo<L>;
     static_assert(Gm::K == 1, "one word per lane");
-    const Progress<PRIO> progress(a.nsweeps, a.one_round != 0);
-    LaneInfo li = lane_info<L>(a, wave, threadIdx.x);
-    uint32_t v = (uint32_t)li.gl;
+    const uint32_t v = (uint32_t)li.gl;
     uint32_t s0[1], s1[1];
     if (a.init) {
         s0[0] = init_word<L>(0, v, li.j, a);
@@ -1200,23 +1216,19 @@ __device__ __forceinline__ void sweep_regs(const SweepArgs& a, int wave)
         }
     }
     // the replica's number and its addresses are taken from the thread's number
-    // again: kept through the sweeps they need more registers than eight waves
-    // leave, and went to scratch memory
-    uint32_t thread = threadIdx.x;
-    __asm__("" : "+v"(thread));
-    li = lane_info<L>(a, wave, thread);
-    v = (uint32_t)li.gl;
-    const Neighbours<L, 0> nb(s1, li.lane, li.gl);
-    const Nb n = nb.get(s1, 0);
-    const uint32_t anti = __popc(s0[0] ^ n.up) + __popc(s0[0] ^ n.dn) + __popc(s0[0] ^ n.same) + __popc(s0[0] ^ n.side);
-    const uint32_t downs = __popc(s0[0]) + __popc(s1[0]);
-    write_EM<L>(a, li, anti, downs);
-    if constexpr (INT8)
-        store_wave_int8<L>(a, wave, li.lane, v, s0[0], s1[0]);
-    else if (li.valid)
-        store_word<L, INT8>(a, li.j, v, s0[0], s1[0]);
+    // again where a wave holds several replicas or the store is int8: kept through
+    // the sweeps they need more registers than eight waves leave, and went to
+    // scratch memory.  The bit store of L = 64 keeps them: taken again there they
+    // fit as well, but the loop came out slower (100 sweeps, R = 20000: heat bath
+    // 1003 us against 987, LCG 1438 against 1424)
+    if constexpr (Gm::REPW > 1 || INT8) {
+        uint32_t thread = threadIdx.x;
+        __asm__("" : "+v"(thread));
+        write_regs<L, INT8>(a, wave, lane_info<L>(a, wave, thread), s0, s1);
+    } else {
+        write_regs<L, INT8>(a, wave, li, s0, s1);
+    }
 }
-
 
 // Sweep of a launch of few waves (L = 16 and 32): four lanes share a word, each
 // with one of its four Philox blocks, so with four of the 16 planes.  A wave that
@@ -1640,11 +1652,13 @@ template <int L, bool INT8, bool HB, bool LCG = false, bool PRIO = true>
 __device__ __forceinline__ void sweep_waves(const SweepArgs& a, int wave0, uint32_t* lds)
 {
     using Gm = Geo<L>;
-    const int wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = (int)(threadIdx.x & 63u), wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wave = wave0 + wib;
     if (wave * Gm::RPWV >= a.n_rep) return;  // uniform per wave
     if constexpr (Gm::K == 1) {
-        sweep_regs<L, INT8, HB, LCG, PRIO>(a, wave);
+        const Progress<PRIO> progress(a.nsweeps, a.one_round != 0);
+        const LaneInfo li = lane_info<L>(a, wave, (uint32_t)lane);
+        sweep_regs<L, INT8, HB, LCG, PRIO>(a, wave, li, progress);
     } else {
         sweep_lds<L, INT8, HB, LCG, PRIO>(a, (uint32_t)__builtin_amdgcn_readfirstlane(wave),
                                           lds + wib * Gm::WAVE_LDS_WORDS);
