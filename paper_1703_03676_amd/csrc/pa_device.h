@@ -594,7 +594,8 @@ __device__ __forceinline__ uint32_t shift_in_le(uint32_t acc, uint32_t x, uint32
 // 50 in the 528 instructions of a sweep with a block per comparison.  They and
 // the waits are lost time where a wave has its SIMD to itself, and free
 // where others fill them; there the shorter blocks mix better with the
-// multiplications (20 sweeps of L = 64, R = 30000: 441 us by these, 459 by pairs).
+// multiplications (20 sweeps, with wave priorities, by these and by pairs: L = 64,
+// R = 9800 149, 180 us; L = 16, R = 200000 188, 199).
 __device__ __forceinline__ void shift_in_pair(uint32_t& m2, uint32_t& m4, uint32_t x, uint32_t y, uint32_t t2,
                                               uint32_t t4)
 {

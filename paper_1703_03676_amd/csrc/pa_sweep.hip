@@ -88,19 +88,19 @@ constexpr int kQuadWaves = 4096;
 
 // Launches of the LCG update without wave priorities and with its comparisons in
 // pairs (shift_in_pair): up to one wave per SIMD, which priorities cannot help,
-// and, in the bit store of L = 16 and 64, launches whose last round would be a
-// thin one (up to a quarter), since waves kept together leave all of it to the
-// end.  Launches of 20 sweeps in us, with priorities and without.  One wave per
-// SIMD: L = 16, R = 300 23.4, 22.6, int8 24.1, 20.6; L = 64, R = 300 29.5, 25.5;
-// L = 128, R = 300 121, 102; two: L = 64, R = 1400 39.3, 41.0.  A thin last round:
-// L = 64, R = 9000 163, 146, R = 10000 176, 161, in the int8 store 153, 164;
-// L = 16, R = 160000 170, 153; but L = 32, R = 36000 133, 142.  A long queue:
-// L = 64, R = 30000 441, 459.
+// and, in the bit store of L = 16, launches whose last round would be a thin one
+// (up to a quarter), since waves kept together leave all of it to the end.
+// Launches of 20 sweeps in us, with priorities and without.  One wave per SIMD:
+// L = 16, R = 300 24.6, 23.9, int8 24.8, 21.8; L = 64, R = 300 31.1, 30.4; L = 128,
+// R = 300 124, 104; two: L = 64, R = 1400 40.2, 42.9.  A thin last round: L = 16,
+// R = 145000 146, 138, R = 160000 160, 153, in the int8 store 151, 164; but L = 32,
+// R = 36000 134, 141, and L = 64, R = 9000 135, 140.  A long queue: L = 16,
+// R = 200000 188, 196; L = 64, R = 26000 382, 379.
 template <int L, bool INT8>
 bool lcg_without_priorities(int waves)
 {
     constexpr int ALL = sweep_resident_waves<L>();
-    return waves <= 1024 || ((L == 16 || L == 64) && !INT8 && waves > ALL && waves <= ALL / 4 * 5);
+    return waves <= 1024 || (L == 16 && !INT8 && waves > ALL && waves <= ALL / 4 * 5);
 }
 
 template <int L, bool INT8, int U>
