@@ -92,3 +92,20 @@ def test_lcg_where_the_waves_just_exceed_the_gpu(L, R, layout):
     o.sweep(1)
     _same(g, o)
     g.close()
+
+
+@pytest.mark.parametrize("L,R", [(16, 16384), (16, 16385), (32, 4096), (32, 4097), (64, 1024), (64, 1025), (128, 1024),
+                                 (128, 1025), (256, 1024), (256, 1025)])
+@pytest.mark.parametrize("layout", ["int8", "bits"])
+def test_lcg_around_one_wave_per_simd(L, R, layout):
+    # up to 1024 waves the comparisons go in pairs and without wave priorities
+    print("case lcg 1024 waves L=%d R=%d %s" % (L, R, layout), flush=True)
+    spins = np.tile(inputs.mixed_spins(16, L, seed=L + 1), (R // 16 + 1, 1, 1))[:R]
+    g = pa.Run(L, R, seed=72, layout=layout, lcg=True)
+    o = oracle.Run(L, R, seed=72, lcg=True)
+    g.upload_population(spins, step=1, sweeps=2, beta=0.44)
+    o.set_population(spins, step=1, sweeps=2, beta=0.44)
+    g.sweep(1)
+    o.sweep(1)
+    _same(g, o)
+    g.close()
